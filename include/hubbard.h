@@ -161,12 +161,12 @@ int hubbard_set_basis_limit(hubbard_h h, size_t bytes);
 /* Seed of the start vector used by hubbard_lanczos (default 12043425). */
 int hubbard_set_seed(hubbard_h h, uint64_t seed);
 
-/* y = H x (Sec. 4.3: H_up (x) I, I (x) H_dn and the interaction term; two
- * passes over the rows of the dim_up x dim_dn view, the down-spin hops and the
- * interaction from rows staged in LDS, then the up-spin hops as row
- * combinations).  x, y: device arrays of dim elements in J order, double under
+/* y = H x (Sec. 4.3: H_up (x) I, I (x) H_dn and the interaction term; one
+ * launch where x takes at most 192 MB, else two passes over the rows of the
+ * dim_up x dim_dn view, the down-spin hops and the interaction from rows staged
+ * in LDS, then the up-spin hops as row combinations).  x, y: device arrays of dim elements in J order, double under
  * HUBBARD_FP64 and float under HUBBARD_MIXED; y is overwritten and must not
- * overlap x.  Asynchronous on the handle's stream.  When the rows of x or y do
+ * overlap x.  Asynchronous on the handle's stream.  When two passes run and the rows of x or y do
  * not start on 128 bytes (dim_dn not a multiple of 16 doubles or 32 floats)
  * and the up-spin rows have at most 64 hops, the product routes through two work vectors at the stride ld_pref that the
  * handle allocates on the first such call (2 * dim_up * ld_pref elements of the

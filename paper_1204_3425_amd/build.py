@@ -13,8 +13,8 @@ ARCH = "gfx950"
 # -packed-fp32-ops: keep the compiler from emitting packed FP32 instructions
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH,
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-result"]
-SOURCES = ["builder.cpp", "tridiag.cpp", "capi.cpp", "kernels.hip", "hv.hip", "batch.hip", "batch.cpp", "server.cpp",
-           "observables.hip", "propagate.hip"]
+SOURCES = ["builder.cpp", "tridiag.cpp", "capi.cpp", "kernels.hip", "hv.hip:8", "hv.hip:4", "batch.hip", "batch.cpp",
+           "server.cpp", "observables.hip", "propagate.hip", "tile.hip"]  # hv.hip once per element size
 
 
 def build(verbose: bool = False) -> str:
@@ -22,8 +22,10 @@ def build(verbose: bool = False) -> str:
     objs = []
     procs = []
     for src in SOURCES:
-        obj = os.path.join(BUILD, src.replace(".", "_") + ".o")
-        cmd = [HIPCC] + COMMON + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+        obj = os.path.join(BUILD, src.replace(".", "_").replace(":", "_") + ".o")
+        src, _, elem = src.partition(":")
+        flags = COMMON + (["-DHUB_HV_ELEM=" + elem] if elem else [])
+        cmd = [HIPCC] + flags + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))

@@ -114,7 +114,7 @@ static void free_device(hubbard *h)
     DeviceTables &d = h->dev;
     void *ptrs[] = {d.states_up, d.states_dn, d.up_rows, d.dn_cols, d.nnz_up, d.nnz_dn,
                     d.dn_groups64, d.dn_groups32, d.dn_nq, d.dn_groups16, d.dn_nq8, d.dn_pidx, d.dn_nidx, d.dn_pn, d.up_blk, d.up_nint, d.up_next,
-                    d.up_bstart, d.up_line, d.up_cnt, d.tcls};
+                    d.up_bstart, d.up_line, d.up_cnt, d.tcls, d.up_tile, d.dn_slots, d.dn_slot_amp, d.dn_slot_nq};
     for (void *p : ptrs)
         if (p)
             (void)hipFree(p);
@@ -250,6 +250,67 @@ static void upload_blocked_up(hubbard *h, size_t &total)
     d.up_max_block = longest;
 }
 
+// Tables of the one-launch H.v: the up entries in slots (see DeviceTables), and
+// for per-bond handles the down entries in slots of one amplitude: class c
+// takes as many slots as the column with most hops of that class needs.
+constexpr int64_t kMaxTileRow = 32767;  // 16-bit entries
+
+static void upload_tile(hubbard *h, const std::vector<uint32_t> &rows, size_t &total)
+{
+    DeviceTables &d = h->dev;
+    const int64_t du = h->up.dim, ddn = h->dn.dim;
+    // rows that fit in LDS, and sectors the form may take (see make_tile_plan)
+    if (ddn > kMaxTileRow || (h->dim * 4 > kTileMaxBytes && (int)h->tcls.size() <= kTwoPassClasses))
+        return;
+    const int w = std::max(1, h->up.width), w8 = (w + 7) / 8 * 8;
+    std::vector<uint32_t> up((size_t)du * (size_t)w8, 0u);
+    for (int64_t r = 0; r < du; r++) {
+        const int nnz = h->up.row_nnz[(size_t)r];
+        for (int k = 0; k < w8; k++)
+            up[(size_t)r * (size_t)w8 + (size_t)k] =
+                nnz ? rows[(size_t)r * (size_t)h->up.width + (size_t)std::min(k, nnz - 1)] : (uint32_t)r;
+    }
+    d.up_tile = upload<uint32_t>(up.data(), up.size() * 4, total);
+    d.up_tile_w = w8;
+    if (h->tcls.empty())
+        return;
+    const int ncls = (int)h->tcls.size();
+    std::vector<int> first((size_t)ncls + 1, 0), cnt((size_t)ncls);
+    std::vector<int> most((size_t)ncls, 0);
+    for (int64_t r = 0; r < ddn; r++) {
+        std::fill(cnt.begin(), cnt.end(), 0);
+        for (int k = 0; k < h->dn.row_nnz[(size_t)r]; k++)
+            cnt[h->bond_cls[h->dn.bond[(size_t)k * (size_t)ddn + (size_t)r]]]++;
+        for (int c = 0; c < ncls; c++)
+            most[(size_t)c] = std::max(most[(size_t)c], cnt[(size_t)c]);
+    }
+    for (int c = 0; c < ncls; c++)
+        first[(size_t)c + 1] = first[(size_t)c] + most[(size_t)c];
+    const int ng = std::max(1, (first[(size_t)ncls] + 7) / 8);
+    std::vector<double> amp((size_t)std::max(ng, 2) * 8, 0.0);
+    for (int c = 0; c < ncls; c++)
+        for (int k = first[(size_t)c]; k < first[(size_t)c + 1]; k++)
+            amp[(size_t)k] = h->tcls[(size_t)c];
+    std::vector<uint16_t> g((size_t)ng * (size_t)ddn * 8, (uint16_t)ddn);
+    std::vector<uint8_t> nq((size_t)((ddn + 63) / 64), 0);
+    for (int64_t r = 0; r < ddn; r++) {
+        std::fill(cnt.begin(), cnt.end(), 0);
+        uint8_t &need = nq[(size_t)(r / 64)];
+        for (int k = 0; k < h->dn.row_nnz[(size_t)r]; k++) {
+            const size_t src = (size_t)k * (size_t)ddn + (size_t)r;
+            const int c = h->bond_cls[h->dn.bond[src]];
+            const int at = first[(size_t)c] + cnt[(size_t)c]++;
+            g[((size_t)(at / 8) * (size_t)ddn + (size_t)r) * 8 + (size_t)(at % 8)] =
+                (uint16_t)((uint32_t)h->dn.col[src] | (h->dn.sgn[src] < 0 ? 0x8000u : 0u));
+            need = (uint8_t)std::max<int>(need, at / 8 + 1);
+        }
+    }
+    d.dn_slots = upload<uint16_t>(g.data(), g.size() * 2, total);
+    d.dn_slot_amp = upload<double>(amp.data(), amp.size() * 8, total);
+    d.dn_slot_nq = upload<uint8_t>(nq.data(), nq.size(), total);
+    d.dn_slot_groups = ng;
+}
+
 static void upload_tables(hubbard *h)
 {
     DeviceTables &d = h->dev;
@@ -270,6 +331,7 @@ static void upload_tables(hubbard *h)
             rows[(size_t)r * (size_t)h->up.width + (size_t)k] = pack(h->up, src);
         }
     d.up_rows = upload<uint32_t>(rows.data(), rows.size() * 4, total);
+    upload_tile(h, rows, total);
     // down table column-major (lanes of a wave read consecutive rows d)
     std::vector<uint32_t> cols((size_t)h->dn.dim * (size_t)std::max(1, h->dn.width), 0u);
     for (int64_t r = 0; r < h->dn.dim; r++)
@@ -417,6 +479,12 @@ static HvArgs hv_args(const hubbard *h)
     a.up_line_w = h->dev.up_line_w;
     a.up_line_ipad = h->dev.up_line_ipad;
     a.up_cnt = h->dev.up_cnt;
+    a.up_tile = h->dev.up_tile;
+    a.up_tile_w = h->dev.up_tile_w;
+    a.dn_slots = reinterpret_cast<const uint4 *>(h->dev.dn_slots);
+    a.dn_slot_amp = h->dev.dn_slot_amp;
+    a.dn_slot_nq = h->dev.dn_slot_nq;
+    a.dn_slot_groups = h->dev.dn_slot_groups;
     a.dim_up = h->up.dim;
     a.dim_dn = h->dn.dim;
     a.w_up = h->up.width;
@@ -1310,6 +1378,16 @@ static int apply_impl(hubbard_h h, const void *x, int64_t ldx, void *y, int64_t 
     const HvPlan pl = make_hv_plan(a, (int)es);
     if (!pl.two_pass && (ldx != ddn || ldy != ddn))
         fail(HUBBARD_EINVAL, "rows too wide for the staged kernels: only dense rows (ld = dim_dn) are supported");
+    const TilePlan tp = make_tile_plan(a, (int)es);
+    if (tp.ok) {
+        if (h->precision == HUBBARD_FP64)
+            launch_hv_tile<double>(a, tp, static_cast<const double *>(x), ldx, nullptr, static_cast<double *>(y), ldy,
+                                   HV_STORE, 0.0, TileStep(), 0, h->stream);
+        else
+            launch_hv_tile<float>(a, tp, static_cast<const float *>(x), ldx, nullptr, static_cast<float *>(y), ldy,
+                                  HV_STORE, 0.0, TileStep(), 0, h->stream);
+        return HUBBARD_OK;
+    }
     // rows not on 128 bytes: the H.v routes through two padded work vectors
     // (the row pass writes them, the up-spin pass reads them and writes y)
     const int64_t slw = 128 / (int64_t)es;

@@ -1602,6 +1602,7 @@ size_t row_lds(int64_t ddn)
 
 }  // namespace
 
+#if HUB_HV_ELEM == 8
 HvPlan make_hv_plan(const HvArgs &a, int elem_bytes)
 {
     HvPlan pl;
@@ -1657,6 +1658,7 @@ HvPlan make_hv_plan(const HvArgs &a, int elem_bytes)
     }
     return pl;
 }
+#endif
 
 template <typename T, int RPB>
 static void launch_rows_rpb(const RowArgs &ra, bool g16, bool gt, const HvPlan &pl, const T *x, int64_t ldx, T *y,
@@ -1706,7 +1708,7 @@ static void launch_rows_rpb(const RowArgs &ra, bool g16, bool gt, const HvPlan &
 
 // The FP64 row pass takes handles of one amplitude whose rows need the whole
 // LDS (one row per workgroup) and fit kRow64Max elements.
-static bool row64_ok(const HvArgs &a, const HvPlan &pl)
+[[maybe_unused]] static bool row64_ok(const HvArgs &a, const HvPlan &pl)
 {
     // rows of up to 13 elements per thread are staged through registers
     return a.tcls == nullptr && a.dn_pidx != nullptr && pl.rows_rpb == 1 && a.w_dn <= 32 &&
@@ -1748,7 +1750,7 @@ static void launch_rows64_mode(const Row64Args &ra, int np, int nn, const HvPlan
         launch_rows64_groups<MODE, false, 13>(ra, np, nn, pl, x, ldx, y, ldy, alpha, coef, s);
 }
 
-static void launch_rows64(const HvArgs &a, const HvPlan &pl, const double *x, int64_t ldx, double *y, int64_t ldy,
+[[maybe_unused]] static void launch_rows64(const HvArgs &a, const HvPlan &pl, const double *x, int64_t ldx, double *y, int64_t ldy,
                           int mode, double alpha, const double *coef, hipStream_t s, double *xc, int64_t ldc,
                           const HvDefl &defl, double *yo, int64_t ldyo)
 {
@@ -1783,7 +1785,7 @@ static void launch_rows64(const HvArgs &a, const HvPlan &pl, const double *x, in
 // The FP32 row pass on row pairs (hv_rows32x2_kernel): the same tables and
 // conditions as the FP64 row pass (one amplitude, 16-bit indices, at most 32
 // hops per column), any mode but the deflated step; one workgroup per CU.
-static bool rows32x2_ok(const HvArgs &a, int mode)
+[[maybe_unused]] static bool rows32x2_ok(const HvArgs &a, int mode)
 {
     return a.tcls == nullptr && a.dn_pidx != nullptr && a.w_dn <= 32 && a.dim_dn <= 13 * kRowThreads &&
            mode != HV_FUSED_DEFL;
@@ -1825,7 +1827,7 @@ static void launch_rows32x2_mode(const Row32Args &ra, int np, int nn, const floa
         launch_rows32x2_groups<MODE, false, 13>(ra, np, nn, x, ldx, y, ldy, alpha, coef, s);
 }
 
-static void launch_rows32x2(const HvArgs &a, const float *x, int64_t ldx, float *y, int64_t ldy, int mode,
+[[maybe_unused]] static void launch_rows32x2(const HvArgs &a, const float *x, int64_t ldx, float *y, int64_t ldy, int mode,
                             double alpha, const double *coef, hipStream_t s, float *xc, int64_t ldc, float *yo,
                             int64_t ldyo)
 {
@@ -1915,17 +1917,25 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
         RowArgs rh = ra;
         if (yout)
             rh.yo = yout + o;
-        if (sizeof(T) == 8 && row64_ok(a, pl))
-            launch_rows64(a, pl, reinterpret_cast<const double *>(x + o), ldx, reinterpret_cast<double *>(yr + o), ldyr,
-                          mode, alpha, coef, s, reinterpret_cast<double *>(ra.xc), ra.ldc, dfl,
-                          reinterpret_cast<double *>(rh.yo), ldy);
-        else if (sizeof(T) == 4 && rows32x2_ok(a, mode))
-            launch_rows32x2(a, reinterpret_cast<const float *>(x + o), ldx, reinterpret_cast<float *>(yr + o), ldyr,
-                            mode, alpha, coef, s, reinterpret_cast<float *>(ra.xc), ra.ldc,
-                            reinterpret_cast<float *>(rh.yo), ldy);
-        else if (pl.rows_rpb == 3)
-            launch_rows_rpb<T, 3>(rh, g16, gt, pl, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s);
-        else if (pl.rows_rpb == 2)
+        bool done = false;
+        if constexpr (sizeof(T) == 8) {
+            done = row64_ok(a, pl);
+            if (done)
+                launch_rows64(a, pl, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s, static_cast<T *>(ra.xc), ra.ldc,
+                              dfl, static_cast<T *>(rh.yo), ldy);
+        } else {
+            done = rows32x2_ok(a, mode);
+            if (done)
+                launch_rows32x2(a, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s, static_cast<T *>(ra.xc), ra.ldc,
+                                static_cast<T *>(rh.yo), ldy);
+            else if (pl.rows_rpb == 3) {
+                launch_rows_rpb<T, 3>(rh, g16, gt, pl, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s);
+                done = true;
+            }
+        }
+        if (done)
+            continue;
+        if (pl.rows_rpb == 2)
             launch_rows_rpb<T, 2>(rh, g16, gt, pl, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s);
         else
             launch_rows_rpb<T, 1>(rh, g16, gt, pl, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s);
@@ -2076,11 +2086,15 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
     return pl.slab_grid;
 }
 
+// The two element types are compiled as two objects (HUB_HV_ELEM), in parallel.
+#if HUB_HV_ELEM == 8
 template int launch_hv2<double>(const HvArgs &, const HvPlan &, const double *, int64_t, double *, int64_t, double *,
                                 int64_t, int, double, const double *, double *, hipStream_t, double *, double *,
                                 const HvDefl *, double *, int64_t);
+#else
 template int launch_hv2<float>(const HvArgs &, const HvPlan &, const float *, int64_t, float *, int64_t, float *,
                                int64_t, int, double, const double *, double *, hipStream_t, float *, float *,
                                const HvDefl *, float *, int64_t);
+#endif
 
 }  // namespace hub

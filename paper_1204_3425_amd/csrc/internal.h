@@ -89,6 +89,17 @@ struct DeviceTables {
     // slots past a row's internal count, up to the largest count of its group,
     // hold the block's zero row
     uint32_t *up_line = nullptr, *up_cnt = nullptr;
+    // one-launch H.v: the up entries as up_tile_w slots per row (a multiple of
+    // eight; slots past a row's count repeat its last hop), and for per-bond
+    // handles the down entries in slots of one amplitude each: groups of eight
+    // 16-bit entries like dn_groups16, the amplitude of every slot, and the
+    // groups needed by the 64 columns of a wave
+    uint32_t *up_tile = nullptr;
+    int up_tile_w = 0;
+    uint16_t *dn_slots = nullptr;
+    double *dn_slot_amp = nullptr;
+    uint8_t *dn_slot_nq = nullptr;
+    int dn_slot_groups = 0;
     size_t bytes = 0;
     double *tcls = nullptr;  // amplitude of each class (per-bond amplitudes only)
     int up_line_w = 32;      // slots per row of up_line (32 or 64)
@@ -165,6 +176,12 @@ struct HvArgs {
     int64_t dim_up, dim_dn;
     int32_t w_up, w_dn;
     double t, U;
+    const uint32_t *up_tile = nullptr;  // one-launch H.v (null: not built)
+    int up_tile_w = 0;
+    const uint4 *dn_slots = nullptr;
+    const double *dn_slot_amp = nullptr;
+    const uint8_t *dn_slot_nq = nullptr;
+    int dn_slot_groups = 0;
 };
 
 // Launch shape of the two-pass H.v for one element size (hv.hip).
@@ -232,6 +249,41 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
                int64_t lds_, int mode, double alpha, const double *coef, double *partials, hipStream_t s,
                T *xpad = nullptr, T *ypad = nullptr, const HvDefl *defl = nullptr, T *yout = nullptr,
                int64_t pair = 0);
+
+// tile.hip: the one-launch H.v of small and medium sectors.  It reads the x rows
+// of the up-spin hops from the Infinity Cache, so x has to fit there beside what
+// else is live (192 MB of the 256).  Dense apply, two-pass / one launch in us:
+// FP64 3x4 6u6d (853,776 states) 36.4 / 16.6, 14-site ring (11.8 M) 156 / 98,
+// 4x4 8u4d (23.4 M) 390 / 342, 4x4 6u5d (35 M, 280 MB) 551 / 547, 4x4 6u6d (64 M)
+// 1076 / 1224; FP32 14-site ring 96 / 60, 4x4 6u5d 326 / 273, 6u6d 598 / 625.
+// Handles of more than four amplitude classes have no two-pass form and take it
+// at any size where a row fits in LDS.
+constexpr int64_t kTileMaxBytes = (int64_t)192 << 20;
+struct TilePlan {
+    bool ok = false;
+    int threads = 64, grid = 8, nseg = 1, span = 64;
+    size_t lds = 0;
+};
+// Scalars of Lanczos step j (0-based): b[j] = |x_j| of the stored vector x_j =
+// b_j f_j, formed from the partial sums norm2 of its square (1 for a start
+// vector taken as unit), a[j] = a_{j+1} of Alg. 1; host_b: a and b interleaved
+// in mapped host memory (null: not wanted).
+struct TileStep {
+    const double *norm2 = nullptr;
+    int n_norm2 = 0;
+    double *part = nullptr;  // partial sums of q.x (HV_RESIDUAL: of z.z, then of x.Hx)
+    double *b = nullptr;
+    double *host_b = nullptr;
+    int j = 0;
+    int unit = 0;
+};
+TilePlan make_tile_plan(const HvArgs &a, int elem_bytes);
+// HV_STORE: out = H x.  HV_LANCZOS: out = H x / b_j - b_j / b_{j-1} prev (prev
+// unread in step 0).  HV_RESIDUAL: partial sums only.  pair > 0: both halves
+// of a complex vector at that element offset, partial sums covering both.
+template <typename T>
+void launch_hv_tile(const HvArgs &a, const TilePlan &pl, const T *x, int64_t ldx, const T *prev, T *out, int64_t ldy,
+                    int mode, double shift, const TileStep &st, int64_t pair, hipStream_t s);
 
 template <typename T>
 void launch_axpy_norm(T *w, const T *v, const double *coef, int64_t n, double *partials, int nblocks, hipStream_t s);
