@@ -72,7 +72,7 @@ typedef struct {
     int32_t w_up, w_dn;          /* ELL widths = max entries per row (Sec. 4.2, Fig. ELL) */
     int64_t nnz_up, nnz_dn;      /* stored hopping entries per spin */
     size_t device_bytes;         /* device memory held by the handle (tables + states) */
-    size_t vector_bytes;         /* device memory one Lanczos run allocates (work vectors) */
+    size_t vector_bytes;         /* device memory of one Lanczos run (work vectors) */
     int64_t ld_pref;             /* row stride (elements) of the library's own vectors */
 } hubbard_info_t;
 
@@ -136,7 +136,9 @@ int hubbard_build(int sites, const int32_t *edges, int n_edges, int n_up, int n_
 int hubbard_build_bonds(int sites, const int32_t *edges, const double *t, int n_edges, int n_up, int n_dn, double U,
                         hubbard_h *out);
 
-/* Releases the handle and its device memory.  NULL is accepted. */
+/* Releases the handle and its device memory: its tables, and the device
+ * buffers of its calls that it keeps for the next one (at most 1 GiB per handle,
+ * 8 GiB over all handles).  NULL is accepted. */
 int hubbard_free(hubbard_h h);
 
 /* Stream for every later call on this handle (a hipStream_t; NULL = the null

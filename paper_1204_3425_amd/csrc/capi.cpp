@@ -15,10 +15,12 @@
 // behind the device, computes the lowest eigenvalue of T_j (eq. Tmatrix) and
 // applies the energy test of Sec. 2.2.
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <exception>
 #include <memory>
 #include <string>
 #include <vector>
@@ -59,49 +61,154 @@ static int guarded(F &&f)
     }
 }
 
-// Device buffer owned by RAII.
-struct DevBuf {
+void *Workspace::take(size_t bytes, size_t *got)
+{
+    bytes = (std::max<size_t>(bytes, 16) + 65535) / 65536 * 65536;
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        size_t best = dev_.size();
+        for (size_t k = 0; k < dev_.size(); k++)
+            if (dev_[k].bytes >= bytes && dev_[k].bytes <= 2 * bytes &&
+                (best == dev_.size() || dev_[k].bytes < dev_[best].bytes))
+                best = k;
+        if (best < dev_.size()) {
+            const Block b = dev_[best];
+            drop(best);
+            *got = b.bytes;
+            return b.p;
+        }
+    }
     void *p = nullptr;
-    DevBuf() = default;
-    explicit DevBuf(size_t bytes)
-    {
-        if (bytes)
-            HUB_HIP(hipMalloc(&p, bytes));
-    }
-    ~DevBuf()
-    {
-        if (p)
-            (void)hipFree(p);
-    }
-    DevBuf(const DevBuf &) = delete;
-    DevBuf &operator=(const DevBuf &) = delete;
-    template <typename T>
-    T *as() const { return static_cast<T *>(p); }
-};
+    *got = bytes;
+    if (hipMalloc(&p, bytes) == hipSuccess)
+        return p;
+    (void)hipGetLastError();
+    release();
+    HUB_HIP(hipMalloc(&p, bytes));
+    return p;
+}
 
-// Pinned host memory, mapped and coherent: kernels may write it directly
-// (through dev), and the host reads it once the writing work has completed.
-struct PinnedBuf {
+// bytes kept by all handles of the process
+static std::atomic<size_t> g_kept{0};
+
+void Workspace::drop(size_t k)
+{
+    held_ -= dev_[k].bytes;
+    g_kept -= dev_[k].bytes;
+    dev_.erase(dev_.begin() + (std::ptrdiff_t)k);
+}
+
+void Workspace::give(void *p, size_t bytes)
+{
+    if (bytes > kKeepBytes) {
+        (void)hipFree(p);
+        return;
+    }
+    std::lock_guard<std::mutex> lk(mu_);
+    dev_.push_back(Block{p, bytes});
+    held_ += bytes;
+    g_kept += bytes;
+    while (!dev_.empty() && (held_ > kKeepBytes || g_kept.load() > kKeepAll)) {
+        (void)hipFree(dev_.front().p);
+        drop(0);
+    }
+}
+
+void *Workspace::take_host(size_t bytes, size_t *got)
+{
+    bytes = (bytes + 16383) / 16384 * 16384;
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        for (size_t k = 0; k < host_.size(); k++)
+            if (host_[k].bytes >= bytes) {
+                void *p = host_[k].p;
+                *got = host_[k].bytes;
+                host_.erase(host_.begin() + (std::ptrdiff_t)k);
+                return p;
+            }
+    }
     void *p = nullptr;
-    void *dev = nullptr;
-    explicit PinnedBuf(size_t bytes)
+    *got = bytes;
+    HUB_HIP(hipHostMalloc(&p, bytes, hipHostMallocMapped | hipHostMallocCoherent));
+    return p;
+}
+
+void Workspace::give_host(void *p, size_t bytes)
+{
     {
-        HUB_HIP(hipHostMalloc(&p, bytes, hipHostMallocMapped | hipHostMallocCoherent));
-        HUB_HIP(hipHostGetDevicePointer(&dev, p, 0));
+        std::lock_guard<std::mutex> lk(mu_);
+        // one or two small blocks serve every call
+        if (host_.size() < 2 && bytes <= (1 << 20)) {
+            host_.push_back(Block{p, bytes});
+            return;
+        }
     }
-    ~PinnedBuf()
-    {
-        if (p)
-            (void)hipHostFree(p);
+    (void)hipHostFree(p);
+}
+
+void Workspace::release()
+{
+    std::lock_guard<std::mutex> lk(mu_);
+    for (const Block &b : dev_)
+        (void)hipFree(b.p);
+    for (const Block &b : host_)
+        (void)hipHostFree(b.p);
+    g_kept -= held_;
+    dev_.clear();
+    host_.clear();
+    held_ = 0;
+}
+
+DevBuf::DevBuf(size_t n, Workspace *w) : ws(w)
+{
+    if (!n)
+        return;
+    bytes = n;
+    if (ws)
+        p = ws->take(n, &bytes);
+    else
+        HUB_HIP(hipMalloc(&p, n));
+}
+
+DevBuf::~DevBuf()
+{
+    if (!p)
+        return;
+    if (!ws) {
+        (void)hipFree(p);
+        return;
     }
-    PinnedBuf(const PinnedBuf &) = delete;
-    PinnedBuf &operator=(const PinnedBuf &) = delete;
-    template <typename T>
-    T *as() const { return static_cast<T *>(p); }
-};
+    // a call that ends in an error may have left work in flight
+    if (std::uncaught_exceptions() > 0)
+        (void)hipDeviceSynchronize();
+    ws->give(p, bytes);
+}
+
+PinnedBuf::PinnedBuf(size_t n, Workspace *w) : bytes(n), ws(w)
+{
+    if (ws)
+        p = ws->take_host(n, &bytes);
+    else
+        HUB_HIP(hipHostMalloc(&p, n, hipHostMallocMapped | hipHostMallocCoherent));
+    HUB_HIP(hipHostGetDevicePointer(&dev, p, 0));
+}
+
+PinnedBuf::~PinnedBuf()
+{
+    if (!p)
+        return;
+    if (!ws) {
+        (void)hipHostFree(p);
+        return;
+    }
+    if (std::uncaught_exceptions() > 0)
+        (void)hipDeviceSynchronize();
+    ws->give_host(p, bytes);
+}
 
 static void free_device(hubbard *h)
 {
+    h->ws.release();
     if (h->apply_work) {
         (void)hipFree(h->apply_work);
         h->apply_work = nullptr;
@@ -242,9 +349,11 @@ static void upload_blocked_up(hubbard *h, size_t &total)
         d.up_line_w = W;
         d.up_line_ipad = ipad ? 1 : 0;
     }
-    d.up_blk = upload<uint32_t>(ent.data(), ent.size() * 4, total);
-    d.up_nint = upload<uint16_t>(nint.data(), nint.size() * 2, total);
-    d.up_next = upload<uint16_t>(next.data(), next.size() * 2, total);
+    if (up.width > 64) {
+        d.up_blk = upload<uint32_t>(ent.data(), ent.size() * 4, total);
+        d.up_nint = upload<uint16_t>(nint.data(), nint.size() * 2, total);
+        d.up_next = upload<uint16_t>(next.data(), next.size() * 2, total);
+    }
     d.up_bstart = upload<int32_t>(bstart.data(), bstart.size() * 4, total);
     d.up_nblocks = nb;
     d.up_max_block = longest;
@@ -254,6 +363,10 @@ static void upload_blocked_up(hubbard *h, size_t &total)
 // for per-bond handles the down entries in slots of one amplitude: class c
 // takes as many slots as the column with most hops of that class needs.
 constexpr int64_t kMaxTileRow = 32767;  // 16-bit entries
+// Sectors up to this size (and rows of at most 64 KB in FP64) take the
+// one-launch form in every call and precision; the server batches them.
+constexpr int64_t kTileOnlyDim = 16000000;
+static_assert(kTileOnlyDim * 8 <= kTileStepBytes && kTileOnlyDim * 8 <= kTileMaxBytes, "");
 
 static void upload_tile(hubbard *h, const std::vector<uint32_t> &rows, size_t &total)
 {
@@ -350,10 +463,14 @@ static void upload_tables(hubbard *h)
             return;
         }
     }
+    // Sectors whose every call takes the one-launch form need no two-pass tables
+    // (a server's run of a larger sector takes the two-pass form).
+    const int64_t ddn = h->dn.dim;
+    d.tile_only = d.up_tile && h->dim <= kTileOnlyDim && ddn * 8 <= 64 * 1024;
+    const bool tile_only = d.tile_only;
     // class bits of an entry of the down table (per-bond handles)
     auto dn_cls = [&](size_t src) -> uint32_t { return gen ? (uint32_t)h->bond_cls[h->dn.bond[src]] : 0u; };
     // row-pass groups: entry k of column d at ((k/4) * dim_dn + d) * 4 + k%4
-    const int64_t ddn = h->dn.dim;
     const int ng = (h->dn.width + 3) / 4;
     d.dn_ngroups = ng;
     std::vector<uint8_t> nq((size_t)((ddn + 63) / 64), 0);
@@ -363,6 +480,8 @@ static void upload_tables(hubbard *h)
         slot = (uint8_t)std::max<int>(slot, need);
     }
     for (int es : {8, 4}) {
+        if (tile_only)
+            break;
         std::vector<uint32_t> g((size_t)std::max(ng, 1) * (size_t)ddn * 4, (uint32_t)(ddn * es));
         for (int64_t r = 0; r < ddn; r++)
             for (int k = 0; k < h->dn.row_nnz[(size_t)r]; k++) {
@@ -397,7 +516,7 @@ static void upload_tables(hubbard *h)
         }
         d.dn_groups16 = upload<uint16_t>(g.data(), g.size() * 2, total);
         d.dn_nq8 = upload<uint8_t>(nq8.data(), nq8.size(), total);
-        if (ddn <= kRow64Max) {
+        if (ddn <= kRow64Max && !tile_only) {
             // the FP64 row pass: per column the + hops in groups of eight and
             // the - hops in groups of four (ascending column order within each)
             const int64_t nchunk = (ddn + 63) / 64;
@@ -439,7 +558,8 @@ static void upload_tables(hubbard *h)
             d.dn_nn = nnm;
         }
     }
-    upload_blocked_up(h, total);
+    if (!tile_only)
+        upload_blocked_up(h, total);
     d.bytes = total;
 }
 
@@ -525,6 +645,7 @@ constexpr int64_t kFusedMinDim = 1 << 16;
 // vectors as a run needs them and reusable by the next run of the same call.
 constexpr size_t kBasisChunk = 32;
 struct BasisPool {
+    Workspace *ws = nullptr;
     std::vector<std::unique_ptr<DevBuf>> chunks;
     size_t vb = 0;  // bytes per vector
     // the padding of the rows (bytes pad_off..pitch of each row, rows per vector):
@@ -534,14 +655,26 @@ struct BasisPool {
     int64_t rows = 0;
     size_t capacity() const { return chunks.size() * kBasisChunk; }
     void *slot(size_t j) const { return static_cast<char *>(chunks[j / kBasisChunk]->p) + (j % kBasisChunk) * vb; }
-    // room for vector j within budget (bytes the pool may hold in total); false when it cannot grow
-    bool reserve(size_t j, size_t budget, hipStream_t s)
+    // room for vector j within limit (bytes the pool may hold in total); false
+    // when it cannot grow.  Memory from the device leaves 2 GiB of it free.
+    bool reserve(size_t j, size_t limit, hipStream_t s)
     {
+        const size_t cb = kBasisChunk * vb, spare = (size_t)2 << 30;
         while (j >= capacity()) {
-            if ((chunks.size() + 1) * kBasisChunk * vb > budget)
+            if ((chunks.size() + 1) * cb > limit)
                 return false;
+            if (cb > kKeepBytes || !seen_free || free_left < cb + spare) {
+                // (re)read the free memory; small chunks go by the last reading
+                size_t fr = 0, tot = 0;
+                HUB_HIP(hipMemGetInfo(&fr, &tot));
+                seen_free = true;
+                free_left = fr;
+                if (fr < cb + spare)
+                    return false;
+            }
+            free_left -= cb;
             try {
-                chunks.emplace_back(new DevBuf(kBasisChunk * vb));
+                chunks.emplace_back(new DevBuf(cb, ws));
             } catch (const Error &) {
                 (void)hipGetLastError();
                 return false;
@@ -552,6 +685,8 @@ struct BasisPool {
         }
         return true;
     }
+    bool seen_free = false;
+    size_t free_left = 0;
 };
 
 // Lower eigenvectors to project out of every Lanczos vector (FP64, dense J
@@ -561,34 +696,72 @@ struct Deflation {
     int nd = 0;
 };
 
+// whether Lanczos steps take the one-launch form where its plan allows it
+static bool tile_steps(const HvArgs &a, int elem_bytes)
+{
+#ifdef HUB_DEV
+    if (getenv("NO_TILE")) return false;
+    if (getenv("ALL_TILE")) return true;
+#endif
+    return a.dim_up * a.dim_dn * elem_bytes <= kTileStepBytes || (a.tcls && a.ncls > kTwoPassClasses);
+}
+
 template <typename T>
 static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, const Deflation &dfl = Deflation(),
-                        BasisPool *pool_in = nullptr)
+                        BasisPool *pool_in = nullptr, bool two_vectors = false)
 {
     const int64_t n = h->dim;
     const HvArgs args = hv_args(h);
     hipStream_t s = h->stream;
     const HvPlan plan = make_hv_plan(args, sizeof(T));
     const HvPlan plan64 = make_hv_plan(args, sizeof(double));
-    const int64_t ld = plan.ld;                 // padded row stride of the two work vectors
+    // Small and medium sectors take the one-launch H.v: a step is that launch
+    // and the update (TileStep), with the scalars formed inside them.
+    const TilePlan tplan = make_tile_plan(args, sizeof(T));
+    const TilePlan tplan64 = make_tile_plan(args, sizeof(double));
+    const bool tile = tplan.ok && tile_steps(args, sizeof(T)) && (!two_vectors || h->dev.tile_only);
+    // padded row stride of the work vectors
+    const int64_t ld = tile ? (h->dn.dim + 63) / 64 * 64 : plan.ld;
     const int64_t npad = h->up.dim * ld;
     const int hb = plan.nparts;
     const int sb = stream_blocks(npad);
     const int max_iter = o.max_iter;
 
-    // one allocation for both work vectors; after the replay it is reused as
-    // the FP64 scratch of the residual (2 * npad * sizeof(T) >= npad * 8 bytes)
-    // with psi requested it also holds the FP64 residual's two padded vectors
-    DevBuf work(std::max(2 * sizeof(T), o.psi ? (size_t)16 : (size_t)0) * (size_t)npad);
-    T *vecs[2] = {work.as<T>(), work.as<T>() + npad};
+    // one allocation for both work vectors (three in the one-launch form);
+    // after the replay it is reused as the FP64 scratch of the residual
+    // (2 * npad * sizeof(T) >= npad * 8 bytes); with psi requested it also holds
+    // the FP64 residual's two padded vectors
+    std::unique_ptr<DevBuf> work;
+    T *vecs[3] = {nullptr, nullptr, nullptr};
+    auto need_work = [&] {
+        if (work)
+            return;
+        work.reset(new DevBuf(std::max((tile ? 3 : 2) * sizeof(T), o.psi && !tplan64.ok ? (size_t)16 : (size_t)0) *
+                                  (size_t)npad,
+                              &h->ws));
+        for (int k = 0; k < (tile ? 3 : 2); k++)
+            vecs[k] = work->as<T>() + k * npad;
+    };
     const int nd = dfl.nd;
     const int db = defl_blocks(h->up.dim);
+    // the one-launch form's sums: of the H.v (two sets where lower vectors are
+    // projected out in the step, whose sums the next step reads again), reduced
+    // ones, of the norms (two sets) and of the separate projection
+    const bool tdefl = nd > 0 && nd <= kTileDefl;
+    const int tsets = tdefl ? 2 : 1, tper = 1 + (tdefl ? 2 * nd : 0);
+    const int tnb = nd > 0 ? tile_defl_blocks(h->up.dim) : tile_update_blocks(npad, sizeof(T));
+    const int tparts = tsets * tper * (tplan.grid + 1);
     DevBuf partials(sizeof(double) *
-                    (size_t)(std::max((3 + 2 * kFusedDefl) * std::max(std::max(hb, plan64.nparts), sb), nd * db) + 64));
-    DevBuf scal(sizeof(double) * (8 + kMaxDeflate + 1) + sizeof(double) * 2 * (size_t)(max_iter + 1));
+                    (size_t)(std::max({(3 + 2 * kFusedDefl) * std::max(std::max(hb, plan64.nparts), sb), nd * db,
+                                       tparts + (2 + nd) * std::max(tnb, tile_update_blocks(npad, sizeof(T))),
+                                       2 * tplan64.grid}) +
+                             64),
+                    &h->ws);
+    DevBuf scal(sizeof(double) * (8 + kMaxDeflate + 1) + sizeof(double) * 2 * (size_t)(max_iter + 1), &h->ws);
     double *S = scal.as<double>();
     double *D = S + 8;  // projections psi_l . q of the deflated step
-    PinnedBuf host(sizeof(double) * (2 * (size_t)(max_iter + 1) + 8));
+    double *B = D + kMaxDeflate + 1;  // norms |x_j| of the one-launch form
+    PinnedBuf host(sizeof(double) * (2 * (size_t)(max_iter + 1) + 8), &h->ws);
     double *hh = host.as<double>();
     // the reductions write a_j, b_{j+1} straight to host memory (no copy per step)
     double *hist = static_cast<double *>(host.dev);
@@ -619,7 +792,49 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
         launch_reduce(partials.as<double>(), nb, nb, nd, D, s);
         launch_defl_update<double>(q, dfl.psi, D, nd, n, h->up.dim, h->dn.dim, h->dn.dim, partials.as<double>(), s);
     };
+    const int tnn = std::max(tnb, tile_update_blocks(npad, sizeof(T)));
+    double *tnorm = partials.as<double>() + tparts, *tdots = tnorm + 2 * tnn;
+    auto tile_scalars = [&](int j0) {
+        TileStep st;
+        const bool direct = tplan.grid <= kTileDirectParts;
+        auto set = [&](int j) {
+            return partials.as<double>() + (size_t)(j % tsets) * (size_t)tper * (size_t)(tplan.grid + 1) +
+                   (direct ? 0 : (size_t)tper * (size_t)tplan.grid);
+        };
+        st.norm2 = tnorm + (j0 & 1) * tnn;
+        st.n_norm2 = tnb;
+        st.norm2_out = tnorm + ((j0 + 1) & 1) * tnn;
+        st.part = set(j0);
+        st.part_prev = set(j0 + 1);  // of two sets the other one
+        st.n_part = direct ? tplan.grid : 1;
+        st.b = B;
+        st.hist = hist;
+        st.j = j0;
+        st.unit = nd == 0;
+        return st;
+    };
+    // step j0: x_j0 in C, x_{j0-1} in Pm (not read in step 0), x_{j0+1} to Q
+    auto tile_step = [&](T *C, const T *Pm, T *Q, int j0) {
+        TileStep st = tile_scalars(j0);
+        double *raw = partials.as<double>() + (size_t)(j0 % tsets) * (size_t)tper * (size_t)(tplan.grid + 1);
+        launch_hv_tile<T>(args, tplan, C, ld, Q, ld, HV_LANCZOS, 0.0, raw, s, tdefl ? dfl.psi : nullptr,
+                          tdefl ? nd : 0);
+        if (st.part != raw)
+            launch_reduce(raw, tplan.grid, tplan.grid, tper, const_cast<double *>(st.part), s);
+        launch_tile_update<T>(Q, C, Pm, h->up.dim, h->dn.dim, ld, 1, st, s, tdefl ? dfl.psi : nullptr,
+                              tdefl ? nd : 0);
+        if (nd > kTileDefl)
+            launch_tile_project<T>(Q, dfl.psi, nd, h->up.dim, h->dn.dim, ld, tdots, st.norm2_out, s);
+        if (j0 + 1 == max_iter)
+            launch_tile_scalar(tile_scalars(j0 + 1), 0, s);  // b of the last step
+    };
     auto start_pass = [&](T *C, T *P) {
+        if (tile) {
+            launch_start_fill<T>(given, seed, inv_norm, C, nullptr, h->up.dim, h->dn.dim, ld, s);
+            if (nd > 0)
+                launch_tile_project<T>(C, dfl.psi, nd, h->up.dim, h->dn.dim, ld, tdots, tnorm, s);
+            return;
+        }
         launch_start_fill<T>(given, seed, inv_norm, C, P, h->up.dim, h->dn.dim, ld, s);
         if (nd > 0) {
             // f_1 = P f / |P f|: the stored vector keeps its norm, S[0] = 1/|P f|
@@ -642,7 +857,7 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
     // sum_l g_l psi_l while it forms f_{j+1} (so P is applied to q - a_j f_j
     // as in the unfused step, with no pass of its own).
     const bool fused_defl = nd >= 1 && nd <= kFusedDefl && !args.tcls && args.up_line;
-    const bool fused = (nd == 0 || fused_defl) && plan.two_pass && plan.blk_grid > 0 && n >= kFusedMinDim;
+    const bool fused = !tile && (nd == 0 || fused_defl) && plan.two_pass && plan.blk_grid > 0 && n >= kFusedMinDim;
     HvDefl hdefl;
     hdefl.psi = dfl.psi;
     hdefl.nd = nd;
@@ -685,7 +900,9 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
         launch_axpy_norm<T>(P, C, S + 3, npad, partials.as<double>(), sb, s);
         launch_reduce_step(partials.as<double>(), sb, RED_NORM, S, hist, j0, s);
     };
-    auto step = [&](T *C, T *P, int j0) { finish_step(C, P, hv_step(C, P), j0); };
+    auto step = [&](T *C, T *P, int j0) {
+        finish_step(C, P, hv_step(C, P), j0);
+    };
 
     // ---- first pass: run ahead of the host by `lookahead` steps
     const int lookahead = n >= (int64_t)4000000 ? 2 : 8;
@@ -710,7 +927,6 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
     BasisPool local_pool;
     BasisPool &pool = pool_in ? *pool_in : local_pool;
     bool resident = o.psi != nullptr;
-    size_t basis_budget = 0;
     if (resident) {
         const size_t vb = sizeof(T) * (size_t)npad;
         if (pool.vb != vb) {
@@ -721,16 +937,13 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
             }
             pool.vb = vb;
             pool.pitch = sizeof(T) * (size_t)ld;
-            pool.pad_off = sizeof(T) * (size_t)h->dn.dim;
+            // the one-launch H.v writes the padding of its result rows itself
+            pool.pad_off = tile ? pool.pitch : sizeof(T) * (size_t)h->dn.dim;
             pool.rows = h->up.dim;
         }
-        size_t fr = 0, tot = 0;
-        HUB_HIP(hipMemGetInfo(&fr, &tot));
-        const size_t reserve = (size_t)2 << 30;
-        const size_t held = pool.chunks.size() * kBasisChunk * vb;
-        basis_budget = std::min(held + (fr > reserve ? fr - reserve : 0), h->basis_limit);
+        pool.ws = &h->ws;
     }
-    DevBuf scales(o.psi ? sizeof(double) * (size_t)max_iter : 0);
+    const size_t basis_budget = h->basis_limit;
     auto keep = [&](const T *C, int j0) {
         if (!resident)
             return;
@@ -741,36 +954,47 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
             return;
         }
         HUB_HIP(hipMemcpyAsync(pool.slot((size_t)j0), C, pool.vb, hipMemcpyDeviceToDevice, s));
-        HUB_HIP(hipMemcpyAsync(scales.as<double>() + j0, S, sizeof(double), hipMemcpyDeviceToDevice, s));
     };
-    // Fused steps with psi requested (line layout) form each Lanczos vector in
-    // its slot: step j's row pass forms f_j in slot j from the q that step j-1
-    // left there and the H.v result goes to slot j + 1, so keeping a vector
+    // Fused steps (line layout) and the one-launch form, with psi requested,
+    // form each Lanczos vector in its slot: the fused step's row pass forms f_j
+    // in slot j from the q that step j-1 left there, the one-launch form's update
+    // forms it there, and the H.v result goes to slot j + 1, so keeping a vector
     // costs no copy.  When the pool cannot grow, the two live vectors move to
     // the work vectors and the run goes on as without psi (psi by replay).
-    bool inslot = resident && fused && args.up_line && pool.reserve(1, basis_budget, s);
+    bool inslot = resident && (tile || (fused && args.up_line)) && pool.reserve(1, basis_budget, s);
+    if (!inslot || !tile)
+        need_work();
     auto slotp = [&](int j) { return static_cast<T *>(pool.slot((size_t)j)); };
+    T *bufs[3] = {vecs[0], vecs[1], vecs[2]};
     auto leave_slots = [&](int j0) {
         // step j0 is next: q in slot j0, f_{j0-1} in slot j0 - 1
-        HUB_HIP(hipMemcpyAsync(vecs[j0 & 1], slotp(j0), pool.vb, hipMemcpyDeviceToDevice, s));
-        HUB_HIP(hipMemcpyAsync(vecs[(j0 + 1) & 1], slotp(j0 - 1), pool.vb, hipMemcpyDeviceToDevice, s));
+        need_work();
+        std::copy(vecs, vecs + 3, bufs);
+        const int nb = tile ? 3 : 2;
+        HUB_HIP(hipMemcpyAsync(vecs[j0 % nb], slotp(j0), pool.vb, hipMemcpyDeviceToDevice, s));
+        HUB_HIP(hipMemcpyAsync(vecs[(j0 + nb - 1) % nb], slotp(j0 - 1), pool.vb, hipMemcpyDeviceToDevice, s));
         HUB_HIP(hipStreamSynchronize(s));
         pool.chunks.clear();
         inslot = false;
         resident = false;
     };
 
-    T *bufs[2] = {vecs[0], vecs[1]};
     auto t0 = std::chrono::steady_clock::now();
     if (inslot)
         start_pass(slotp(0), bufs[1]);  // bufs[1]: zeros, the vector before f_1
     else
         start_pass(bufs[0], bufs[1]);
+    double start_scale = 1.0;  // 1 / |x_0|
     if (nd > 0) {
-        HUB_HIP(hipMemcpyAsync(hh, S, sizeof(double), hipMemcpyDeviceToHost, s));
+        if (tile) {
+            launch_tile_scalar(tile_scalars(0), 0, s);  // b_0
+        } else {
+            HUB_HIP(hipMemcpyAsync(hh, S, sizeof(double), hipMemcpyDeviceToHost, s));
+        }
         HUB_HIP(hipStreamSynchronize(s));
         // 1/|P f| of the unit start vector
-        if (!std::isfinite(hh[0]) || !(hh[0] > 0.0) || hh[0] > 1e8)
+        start_scale = tile ? 1.0 / hh[0] : hh[0];
+        if (!std::isfinite(start_scale) || !(start_scale > 0.0) || start_scale > 1e8)
             fail(HUBBARD_EINVAL, "the start vector lies in the span of the lower states");
     }
     out.a.clear();
@@ -782,16 +1006,20 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
     while (!stop) {
         if (launched < max_iter) {
             const int j0 = launched;  // 0-based step index
-            T *C = bufs[j0 & 1], *P = bufs[(j0 + 1) & 1];
             if (inslot && !pool.reserve((size_t)j0 + 1, basis_budget, s))
                 leave_slots(j0);
-            if (inslot) {
+            T *C = bufs[j0 & 1], *P = bufs[(j0 + 1) & 1];
+            if (tile && !inslot) {
+                keep(bufs[j0 % 3], j0);
+                tile_step(bufs[j0 % 3], bufs[(j0 + 2) % 3], bufs[(j0 + 1) % 3], j0);
+            } else if (tile) {
+                tile_step(slotp(j0), slotp(j0 > 0 ? j0 - 1 : 0), slotp(j0 + 1), j0);
+            } else if (inslot) {
                 const int np = hv_step_slot(slotp(j0), j0 > 0 ? slotp(j0 - 1) : bufs[1], slotp(j0 + 1));
-                HUB_HIP(hipMemcpyAsync(scales.as<double>() + j0, S, sizeof(double), hipMemcpyDeviceToDevice, s));
                 // q is in slot j0 + 1, f_j0 in slot j0
                 finish_step(slotp(j0), slotp(j0 + 1), np, j0);
             } else if (fused) {
-                // f_j exists once the step's row pass has formed it; S[0] still holds 1/s_j
+                // f_j exists once the step's row pass has formed it
                 const int np = hv_step(C, P);
                 keep(C, j0);
                 finish_step(C, P, np, j0);
@@ -802,10 +1030,12 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
             HUB_HIP(hipEventRecord(ev[(size_t)(j0 % nev)], s));
             launched++;
         }
-        while (checked < launched && (launched - checked > lookahead || launched == max_iter)) {
+        // in the one-launch form step j0 + 1 completes step j0 (it forms b_{j0+1})
+        const int behind = tile && launched < max_iter ? 1 : 0;
+        while (checked < launched - behind && (launched - checked > lookahead || launched == max_iter)) {
             const int j0 = checked;
-            HUB_HIP(hipEventSynchronize(ev[(size_t)(j0 % nev)]));
-            const double a = hh[2 * j0], b = hh[2 * j0 + 1];
+            HUB_HIP(hipEventSynchronize(ev[(size_t)(std::min(j0 + (tile ? 1 : 0), launched - 1) % nev)]));
+            const double a = hh[2 * j0 + (tile ? 1 : 0)], b = hh[2 * j0 + 1 + (tile ? 1 : 0)];
             out.a.push_back(a);
             out.b.push_back(b);
             const int j = j0 + 1;
@@ -851,17 +1081,19 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
     const int m = out.m;
     std::vector<double> y((size_t)m);
     tridiag_lowest_vector(out.a.data(), out.b.data(), m, out.e0, y.data());
+    // psi = sum_j (y_j / |x_j|) x_j over the stored vectors x_j = |x_j| f_j
+    for (int j = 0; j < m; j++)
+        y[(size_t)j] *= j == 0 ? start_scale : 1.0 / out.b[(size_t)j - 1];
     out.psi_resident = resident && pool.capacity() >= (size_t)m;
     if (out.psi_resident) {
         // ---- psi = sum_j y_j f_j from the resident vectors
         std::vector<const T *> ptrs((size_t)m);
         for (int j = 0; j < m; j++)
             ptrs[(size_t)j] = static_cast<const T *>(pool.slot((size_t)j));
-        DevBuf dptr(sizeof(const T *) * (size_t)m), dy(sizeof(double) * (size_t)m);
+        DevBuf dptr(sizeof(const T *) * (size_t)m, &h->ws), dy(sizeof(double) * (size_t)m, &h->ws);
         HUB_HIP(hipMemcpyAsync(dptr.p, ptrs.data(), sizeof(const T *) * (size_t)m, hipMemcpyHostToDevice, s));
         HUB_HIP(hipMemcpyAsync(dy.p, y.data(), sizeof(double) * (size_t)m, hipMemcpyHostToDevice, s));
-        launch_psi_combine<T>(o.psi, dptr.as<const T *>(), dy.as<double>(), scales.as<double>(), m, h->up.dim,
-                              h->dn.dim, ld, s);
+        launch_psi_combine<T>(o.psi, dptr.as<const T *>(), dy.as<double>(), m, h->up.dim, h->dn.dim, ld, s);
         HUB_HIP(hipStreamSynchronize(s));
     } else {
         // ---- second pass: replay the identical recurrence and accumulate psi
@@ -869,18 +1101,26 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
             HUB_HIP(hipStreamSynchronize(s));
             pool.chunks.clear();
         }
+        need_work();
+        std::copy(vecs, vecs + 3, bufs);
         start_pass(bufs[0], bufs[1]);
         for (int j0 = 0; j0 < m; j0++) {
+            if (tile) {
+                launch_psi_acc<T>(o.psi, bufs[j0 % 3], y[(size_t)j0], h->up.dim, h->dn.dim, ld, j0 == 0, s);
+                if (j0 + 1 < m)
+                    tile_step(bufs[j0 % 3], bufs[(j0 + 2) % 3], bufs[(j0 + 1) % 3], j0);
+                continue;
+            }
             T *C = bufs[j0 & 1], *P = bufs[(j0 + 1) & 1];
             if (fused) {
-                // f_j exists once the step's row pass has formed it; S[0] still holds 1/s_j
+                // f_j exists once the step's row pass has formed it
                 const int np = hv_step(C, P);
-                launch_psi_acc<T>(o.psi, C, y[(size_t)j0], S, h->up.dim, h->dn.dim, ld, j0 == 0, s);
+                launch_psi_acc<T>(o.psi, C, y[(size_t)j0], h->up.dim, h->dn.dim, ld, j0 == 0, s);
                 if (j0 + 1 < m)
                     finish_step(C, P, np, j0);
                 continue;
             }
-            launch_psi_acc<T>(o.psi, C, y[(size_t)j0], S, h->up.dim, h->dn.dim, ld, j0 == 0, s);
+            launch_psi_acc<T>(o.psi, C, y[(size_t)j0], h->up.dim, h->dn.dim, ld, j0 == 0, s);
             if (j0 + 1 < m)
                 step(C, P, j0);
         }
@@ -899,10 +1139,17 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
         c = -c;
     launch_scale(o.psi, c, n, s);
     // FP64 residual |H psi - E0 psi| and Rayleigh quotient <psi|H|psi>
-    // rows of psi are dense: the row pass copies them to padded rows beside
-    // its result, for the up-spin pass
-    const int hb64 = launch_hv2<double>(args, plan64, o.psi, h->dn.dim, nullptr, 0, work.as<double>(), ld, HV_RESIDUAL,
-                                        out.e0, nullptr, partials.as<double>(), s, work.as<double>() + npad);
+    int hb64 = tplan64.grid;
+    if (tplan64.ok) {
+        launch_hv_tile<double>(args, tplan64, o.psi, h->dn.dim, nullptr, 0, HV_RESIDUAL, out.e0, partials.as<double>(),
+                               s);
+    } else {
+        // rows of psi are dense: the row pass copies them to padded rows beside
+        // its result, for the up-spin pass
+        need_work();
+        hb64 = launch_hv2<double>(args, plan64, o.psi, h->dn.dim, nullptr, 0, work->as<double>(), ld, HV_RESIDUAL,
+                                  out.e0, nullptr, partials.as<double>(), s, work->as<double>() + npad);
+    }
     launch_reduce(partials.as<double>(), hb64, hb64, 2, S + 4, s);
     HUB_HIP(hipMemcpyAsync(hh, S + 4, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
     HUB_HIP(hipStreamSynchronize(s));
@@ -950,16 +1197,16 @@ static int status_of(const LanczosOut &out, const hubbard_opts &o)
     return (out.stop == HUBBARD_STOP_MAXITER && o.tol >= 0.0) ? HUBBARD_ENOCONV : HUBBARD_OK;
 }
 
-int lanczos_impl(hubbard *h, const hubbard_opts &o, hubbard_result *res)
+int lanczos_impl(hubbard *h, const hubbard_opts &o, hubbard_result *res, bool two_vectors)
 {
     validate_opts(o);
     use_device(h);
     auto t0 = std::chrono::steady_clock::now();
     LanczosOut out;
     if (o.precision == HUBBARD_FP64)
-        run_lanczos<double>(h, o, out);
+        run_lanczos<double>(h, o, out, Deflation(), nullptr, two_vectors);
     else
-        run_lanczos<float>(h, o, out);
+        run_lanczos<float>(h, o, out, Deflation(), nullptr, two_vectors);
     auto t1 = std::chrono::steady_clock::now();
     if (o.a_out)
         std::memcpy(o.a_out, out.a.data(), sizeof(double) * (size_t)out.m);
@@ -992,7 +1239,7 @@ int lowest_states_impl(hubbard *h, int k, const hubbard_opts &o, double *E, doub
     std::unique_ptr<DevBuf> own;
     double *base = psi;
     if (!base) {
-        own.reset(new DevBuf(sizeof(double) * (size_t)k * (size_t)h->dim));
+        own.reset(new DevBuf(sizeof(double) * (size_t)k * (size_t)h->dim, &h->ws));
         base = own->as<double>();
     }
     int worst = HUBBARD_OK;
@@ -1045,7 +1292,9 @@ int propagate_impl(hubbard *h, double *re, double *im, double t, int n_steps, in
     const HvArgs args = hv_args(h);
     hipStream_t s = h->stream;
     const HvPlan plan = make_hv_plan(args, sizeof(double));
-    const int64_t ld = plan.ld, npad = h->up.dim * ld, stride = 2 * npad;
+    const TilePlan tplan = make_tile_plan(args, sizeof(double));
+    const bool tile = tplan.ok && tile_steps(args, sizeof(double));
+    const int64_t ld = tile ? (h->dn.dim + 63) / 64 * 64 : plan.ld, npad = h->up.dim * ld, stride = 2 * npad;
     const int64_t du = h->up.dim, dd = h->dn.dim;
     // the Krylov basis, resident: slot m receives the last H.v of a step.  The
     // unfused H.v runs with beta = 0 on the old contents of a slot, so they start
@@ -1053,9 +1302,11 @@ int propagate_impl(hubbard *h, double *re, double *im, double t, int n_steps, in
     // only row elements, so there slot 1 and the rows' padding (which the
     // fix-up of a flagged step reads) are the parts cleared.
     const size_t bbytes = sizeof(double) * (size_t)stride * (size_t)(m + 1);
-    DevBuf basis(bbytes);
-    const bool fused = plan.two_pass && plan.blk_grid > 0 && args.up_line;
-    if (fused) {
+    DevBuf basis(bbytes, &h->ws);
+    const bool fused = !tile && plan.two_pass && plan.blk_grid > 0 && args.up_line;
+    if (tile) {
+        // the one-launch H.v writes whole padded rows of its result slot
+    } else if (fused) {
         HUB_HIP(hipMemsetAsync(static_cast<double *>(basis.p) + stride, 0, sizeof(double) * (size_t)stride, s));
         if (ld > dd)
             HUB_HIP(hipMemset2DAsync(static_cast<double *>(basis.p) + dd, sizeof(double) * (size_t)ld, 0,
@@ -1063,10 +1314,12 @@ int propagate_impl(hubbard *h, double *re, double *im, double t, int n_steps, in
     } else {
         HUB_HIP(hipMemsetAsync(basis.p, 0, bbytes, s));
     }
-    DevBuf partials(sizeof(double) * (size_t)(std::max(6 * plan.nparts, 4096) + 64));
-    DevBuf scal(sizeof(double) * 4 * (size_t)(m + 2));
-    DevBuf gamd(sizeof(double) * 2 * (size_t)m);
-    PinnedBuf host(sizeof(double) * (4 * (size_t)(m + 2) + 2 * (size_t)m));
+    // one-launch form: sums of the H.v (and their reduced one), two sets of norms
+    const int tgrid = 2 * tplan.grid, tnn = std::max(4096, tile_update_blocks(stride, sizeof(double)));
+    DevBuf partials(sizeof(double) * (size_t)(std::max({6 * plan.nparts, 4096, tgrid + 1 + 2 * tnn}) + 64), &h->ws);
+    DevBuf scal(sizeof(double) * 4 * (size_t)(m + 2), &h->ws);
+    DevBuf gamd(sizeof(double) * 2 * (size_t)m, &h->ws);
+    PinnedBuf host(sizeof(double) * (4 * (size_t)(m + 2) + 2 * (size_t)m), &h->ws);
     double *sh = host.as<double>(), *gh = sh + 4 * (m + 2);
     double *sc = scal.as<double>(), *B = basis.as<double>(), *part = partials.as<double>();
     auto slot = [&](int j) { return B + (size_t)j * (size_t)stride; };
@@ -1080,10 +1333,33 @@ int propagate_impl(hubbard *h, double *re, double *im, double t, int n_steps, in
     // hist (a_j, b_{j+1}) and the scale of each w_j in scl.  Other plans keep
     // the separate update pass.
     const int sb = stream_blocks(stride);
-    DevBuf fsc(sizeof(double) * (8 + kMaxDeflate + 1 + 2 * (size_t)m + (size_t)m + 8));
+    DevBuf fsc(sizeof(double) * (8 + kMaxDeflate + 1 + 2 * (size_t)m + (size_t)m + 8), &h->ws);
     double *S = fsc.as<double>(), *hist = S + 8 + kMaxDeflate + 1, *scl = hist + 2 * m;
-    int nb = launch_prop_load(re, im, B, npad, du, dd, ld, part, s);
-    if (fused)
+    double *tnorm = part + tgrid + 1, *thist = static_cast<double *>(host.dev);
+    double *npart = tile ? tnorm : part;  // sums of |psi|^2
+    int nb = launch_prop_load(re, im, B, npad, du, dd, ld, npart, s);
+    // Krylov step j of the one-launch form: q = H w_j over both halves, then the update
+    int n_norm = nb;  // sums in the current norm set
+    auto tile_scalars = [&](int j) {
+        TileStep st;
+        st.norm2 = tnorm + (j & 1) * tnn;
+        st.n_norm2 = n_norm;
+        st.norm2_out = tnorm + ((j + 1) & 1) * tnn;
+        st.part = part + (tgrid > kTileDirectParts ? tgrid : 0);
+        st.n_part = tgrid > kTileDirectParts ? 1 : tgrid;
+        st.b = sc;
+        st.hist = thist;
+        st.j = j;
+        return st;
+    };
+    auto tile_hv = [&](int j) {
+        launch_hv_tile<double>(args, tplan, slot(j), ld, slot(j + 1), ld, HV_LANCZOS, 0.0, part, s, nullptr, 0, npad);
+        if (tgrid > kTileDirectParts)
+            launch_reduce(part, tgrid, tgrid, 1, part + tgrid, s);
+    };
+    if (tile)
+        ;  // the first update forms |psi|
+    else if (fused)
         launch_reduce_step(part, nb, RED_START, S, nullptr, 0, s);
     else
         launch_prop_reduce(part, nb, PROP_START, sc, 0, s);
@@ -1094,6 +1370,18 @@ int propagate_impl(hubbard *h, double *re, double *im, double t, int n_steps, in
         // the round after the last step only measures <H> of the final state
         const int msteps = k < n_steps ? m : 1;
         for (int j = 0; j < msteps; j++) {
+            if (tile) {
+                tile_hv(j);
+                if (k == n_steps) {
+                    launch_tile_scalar(tile_scalars(0), 1, s);
+                    break;
+                }
+                n_norm = launch_tile_update<double>(slot(j + 1), slot(j), slot(j > 0 ? j - 1 : 0), du, dd, ld, 2,
+                                                    tile_scalars(j), s);
+                if (j + 1 == m)
+                    launch_tile_scalar(tile_scalars(m), 0, s);  // b_m
+                continue;
+            }
             if (fused) {
                 // w_j is formed by this step's row pass; S[0] = 1/|w_j| until the reduction
                 HUB_HIP(hipMemcpyAsync(scl + j, S, sizeof(double), hipMemcpyDeviceToDevice, s));
@@ -1119,7 +1407,18 @@ int propagate_impl(hubbard *h, double *re, double *im, double t, int n_steps, in
             nb = launch_prop_update(slot(j + 1), slot(j), j > 0 ? slot(j - 1) : nullptr, sc, j, stride, part, s);
             launch_prop_reduce(part, nb, PROP_NORM, sc, j, s);
         }
-        if (fused) {
+        if (tile) {
+            // the same host view as the unfused form: {s_j, -, a_j, b_{j+1}} per step
+            HUB_HIP(hipStreamSynchronize(s));
+            std::vector<double> th(host.as<double>(), host.as<double>() + 2 * msteps + 1);
+            for (int j = 0; j < msteps; j++) {
+                const double bj = th[2 * (size_t)j];
+                sh[4 * j] = bj > 1e-300 ? 1.0 / bj : 0.0;
+                sh[4 * j + 1] = 0.0;
+                sh[4 * j + 2] = th[2 * (size_t)j + 1];
+                sh[4 * j + 3] = k < n_steps ? th[2 * (size_t)j + 2] : 0.0;
+            }
+        } else if (fused) {
             // the same host view as the unfused form: {s_j, -, a_j, b_{j+1}} per step
             std::vector<double> fh(3 * (size_t)msteps);
             HUB_HIP(hipMemcpyAsync(fh.data(), hist, sizeof(double) * 2 * (size_t)msteps, hipMemcpyDeviceToHost, s));
@@ -1172,8 +1471,11 @@ int propagate_impl(hubbard *h, double *re, double *im, double t, int n_steps, in
         // the caller's halves receive the state after the last step only
         const bool last = k == n_steps - 1;
         nb = launch_prop_combine(B, nv, stride, npad, gamd.as<double>(), last ? re : nullptr, last ? im : nullptr, du,
-                                 dd, ld, part, s);
-        if (fused)
+                                 dd, ld, npart, s);
+        n_norm = nb;
+        if (tile)
+            ;  // the next step's first update forms |psi|
+        else if (fused)
             launch_reduce_step(part, nb, RED_START, S, nullptr, 0, s);
         else
             launch_prop_reduce(part, nb, PROP_START, sc, 0, s);
@@ -1381,11 +1683,11 @@ static int apply_impl(hubbard_h h, const void *x, int64_t ldx, void *y, int64_t 
     const TilePlan tp = make_tile_plan(a, (int)es);
     if (tp.ok) {
         if (h->precision == HUBBARD_FP64)
-            launch_hv_tile<double>(a, tp, static_cast<const double *>(x), ldx, nullptr, static_cast<double *>(y), ldy,
-                                   HV_STORE, 0.0, TileStep(), 0, h->stream);
+            launch_hv_tile<double>(a, tp, static_cast<const double *>(x), ldx, static_cast<double *>(y), ldy, HV_STORE,
+                                   0.0, nullptr, h->stream);
         else
-            launch_hv_tile<float>(a, tp, static_cast<const float *>(x), ldx, nullptr, static_cast<float *>(y), ldy,
-                                  HV_STORE, 0.0, TileStep(), 0, h->stream);
+            launch_hv_tile<float>(a, tp, static_cast<const float *>(x), ldx, static_cast<float *>(y), ldy, HV_STORE,
+                                  0.0, nullptr, h->stream);
         return HUBBARD_OK;
     }
     // rows not on 128 bytes: the H.v routes through two padded work vectors
@@ -1547,8 +1849,8 @@ int hubbard_observables(hubbard_h h, const double *psi, double *dens, double *co
         const int NS = obs_ns_max(h->sites);
         const int ps = 3 * NS * NS + 1;
         const int np = obs_partial_count(h->sites, h->up.dim, h->dn.dim);
-        DevBuf part(sizeof(double) * (size_t)np * (size_t)ps);
-        DevBuf sums(sizeof(double) * (size_t)ps);
+        DevBuf part(sizeof(double) * (size_t)np * (size_t)ps, &h->ws);
+        DevBuf sums(sizeof(double) * (size_t)ps, &h->ws);
         launch_observables(psi, h->dev.states_up, h->dev.states_dn, h->sites, h->up.dim, h->dn.dim,
                            part.as<double>(), sums.as<double>(), kObsDefaultBlocks, h->stream);
         std::vector<double> r((size_t)ps);
@@ -1590,9 +1892,14 @@ int hubbard_info(hubbard_h h, hubbard_info_t *info)
         r.nnz_up = h->up.nnz;
         r.nnz_dn = h->dn.nnz;
         r.device_bytes = h->dev.bytes;
-        const HvPlan pl = make_hv_plan(hv_args(h), h->precision == HUBBARD_FP64 ? 8 : 4);
+        const HvArgs a = hv_args(h);
+        const int es = h->precision == HUBBARD_FP64 ? 8 : 4;
+        const HvPlan pl = make_hv_plan(a, es);
         r.ld_pref = pl.ld;
-        r.vector_bytes = (size_t)h->up.dim * (size_t)pl.ld * (h->precision == HUBBARD_FP64 ? 16 : 8);
+        // three vectors in the one-launch form, on padded rows
+        const bool tile = make_tile_plan(a, es).ok && tile_steps(a, es);
+        const int64_t ldv = tile ? (h->dn.dim + 63) / 64 * 64 : pl.ld;
+        r.vector_bytes = (size_t)(tile ? 3 : 2) * (size_t)es * (size_t)h->up.dim * (size_t)ldv;
         *info = r;
         return HUBBARD_OK;
     });

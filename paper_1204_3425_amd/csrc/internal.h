@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -100,10 +101,71 @@ struct DeviceTables {
     double *dn_slot_amp = nullptr;
     uint8_t *dn_slot_nq = nullptr;
     int dn_slot_groups = 0;
+    bool tile_only = false;  // no two-pass tables: every call takes the one-launch form
     size_t bytes = 0;
     double *tcls = nullptr;  // amplitude of each class (per-bond amplitudes only)
     int up_line_w = 32;      // slots per row of up_line (32 or 64)
     int up_line_ipad = 0;
+};
+
+// Device and pinned host buffers a handle keeps between its calls.  A solve
+// that allocates its vectors anew each time is bound by it once it is repeated:
+// the 227 MB chunks of a resident basis (3x4 6u6d) cost 1 ms a call in hipMalloc
+// and hipFree, and 16 ms after some two hundred calls, when the driver no longer
+// keeps up with clearing freed memory (2.9 -> 19.4 ms a solve).  Blocks given
+// back are kept up to kKeepBytes per handle and kKeepAll over all handles of the
+// process, a handle's oldest going first, and freed with the handle.  take() hands out a kept block of at least the size asked
+// for and at most twice that, else allocates (freeing the kept blocks if the
+// device is full).  Safe from several threads; the work that used a block has
+// to be complete when it is given back.
+constexpr size_t kKeepBytes = (size_t)1 << 30, kKeepAll = (size_t)8 << 30;
+class Workspace {
+  public:
+    void *take(size_t bytes, size_t *got);
+    void give(void *p, size_t bytes);
+    void *take_host(size_t bytes, size_t *got);
+    void give_host(void *p, size_t bytes);
+    void release();
+    ~Workspace() { release(); }
+
+  private:
+    struct Block {
+        void *p;
+        size_t bytes;
+    };
+    void drop(size_t k);
+    std::mutex mu_;
+    std::vector<Block> dev_, host_;
+    size_t held_ = 0;
+};
+
+// Device buffer, from a handle's workspace or (null) an allocation of its own.
+struct DevBuf {
+    void *p = nullptr;
+    size_t bytes = 0;
+    Workspace *ws = nullptr;
+    DevBuf() = default;
+    explicit DevBuf(size_t n, Workspace *w = nullptr);
+    ~DevBuf();
+    DevBuf(const DevBuf &) = delete;
+    DevBuf &operator=(const DevBuf &) = delete;
+    template <typename T>
+    T *as() const { return static_cast<T *>(p); }
+};
+
+// Pinned host memory, mapped and coherent: kernels may write it directly
+// (through dev), and the host reads it once the writing work has completed.
+struct PinnedBuf {
+    void *p = nullptr;
+    void *dev = nullptr;
+    size_t bytes = 0;
+    Workspace *ws = nullptr;
+    explicit PinnedBuf(size_t n, Workspace *w = nullptr);
+    ~PinnedBuf();
+    PinnedBuf(const PinnedBuf &) = delete;
+    PinnedBuf &operator=(const PinnedBuf &) = delete;
+    template <typename T>
+    T *as() const { return static_cast<T *>(p); }
 };
 
 }  // namespace hub
@@ -129,13 +191,16 @@ struct hubbard {
     void *apply_work = nullptr;
     size_t apply_work_bytes = 0;
     hipEvent_t apply_ev = nullptr;
+    hub::Workspace ws;
 };
 
 namespace hub {
 
 // capi.cpp: the single-instance Lanczos driver (throws hub::Error)
 void validate_opts(const hubbard_opts &o);
-int lanczos_impl(hubbard *h, const hubbard_opts &o, hubbard_result *res);
+// two_vectors: the run holds no more than two work vectors (the server's
+// footprint rule counts two)
+int lanczos_impl(hubbard *h, const hubbard_opts &o, hubbard_result *res, bool two_vectors = false);
 
 // builder.cpp
 void build_spin_table(int sites, const std::vector<int32_t> &edges, int n, SpinTable &out);
@@ -259,31 +324,58 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
 // Handles of more than four amplitude classes have no two-pass form and take it
 // at any size where a row fits in LDS.
 constexpr int64_t kTileMaxBytes = (int64_t)192 << 20;
+// Lanczos steps (vectors of one H.v, two launches a step against the fused
+// two-pass step's five; us a step, fused / one-launch form): FP64 3x4 4u4d 30.3 /
+// 17.4, 3x4 6u6d 48.4 / 29.1, 14-site ring 180 / 162, 4x4 5u5d (19 M, 153 MB) 415 /
+// 384, 4x4 8u4d (187 MB) 429 / 503; FP32 14-site ring 114 / 98, 4x4 8u4d 264 / 242.
+constexpr int64_t kTileStepBytes = (int64_t)160 << 20;
 struct TilePlan {
     bool ok = false;
     int threads = 64, grid = 8, nseg = 1, span = 64;
     size_t lds = 0;
 };
-// Scalars of Lanczos step j (0-based): b[j] = |x_j| of the stored vector x_j =
-// b_j f_j, formed from the partial sums norm2 of its square (1 for a start
-// vector taken as unit), a[j] = a_{j+1} of Alg. 1; host_b: a and b interleaved
-// in mapped host memory (null: not wanted).
+// Lanczos step j (0-based) in two launches: the H.v (HV_LANCZOS) writes q = H x_j
+// and partial sums of q.x_j; the update forms b_j = |x_j| from norm2, a_j from
+// those sums, x_{j+1} = q / b_j - (a_j / b_j) x_j - (b_j / b_{j-1}) x_{j-1} in
+// place of q, and the partial sums of its square (norm2_out).  b[j] holds |x_j|;
+// hist (may be mapped host memory): b_j at 2j, a_j at 2j + 1.  unit: x_0 is taken as a unit vector.  Where the
+// H.v writes more than kTileDirectParts sums the caller reduces them to one first.
+constexpr int kTileDirectParts = 4096;
+constexpr int kTileDefl = 4;  // lower vectors the two launches project out themselves
 struct TileStep {
-    const double *norm2 = nullptr;
+    const double *norm2 = nullptr;  // partial sums of |x_j|^2
     int n_norm2 = 0;
-    double *part = nullptr;  // partial sums of q.x (HV_RESIDUAL: of z.z, then of x.Hx)
+    double *norm2_out = nullptr;
+    const double *part = nullptr;       // sums of q.x_j, then psi_l.q and psi_l.x_j in turn (n_part each)
+    const double *part_prev = nullptr;  // those of step j - 1 (deflated steps)
+    int n_part = 0;
     double *b = nullptr;
-    double *host_b = nullptr;
+    double *hist = nullptr;
     int j = 0;
     int unit = 0;
 };
 TilePlan make_tile_plan(const HvArgs &a, int elem_bytes);
-// HV_STORE: out = H x.  HV_LANCZOS: out = H x / b_j - b_j / b_{j-1} prev (prev
-// unread in step 0).  HV_RESIDUAL: partial sums only.  pair > 0: both halves
-// of a complex vector at that element offset, partial sums covering both.
+// HV_STORE: out = H x.  HV_LANCZOS: as above, with nd <= kTileDefl dense lower
+// vectors psi.  HV_RESIDUAL: partial sums of |Hx - shift x|^2, then of x.Hx.
+// pl.grid sums of each (twice that with pair > 0: both halves of a complex
+// vector at that element offset).
 template <typename T>
-void launch_hv_tile(const HvArgs &a, const TilePlan &pl, const T *x, int64_t ldx, const T *prev, T *out, int64_t ldy,
-                    int mode, double shift, const TileStep &st, int64_t pair, hipStream_t s);
+void launch_hv_tile(const HvArgs &a, const TilePlan &pl, const T *x, int64_t ldx, T *out, int64_t ldy, int mode,
+                    double shift, double *part, hipStream_t s, const double *psi = nullptr, int nd = 0,
+                    int64_t pair = 0);
+// vectors of halves * dim_up rows at stride ld (16-byte aligned, ld a multiple
+// of four); xp is not read in step 0.  Returns the number of partial sums.
+template <typename T>
+int launch_tile_update(T *q, const T *x, const T *xp, int64_t dim_up, int64_t dim_dn, int64_t ld, int halves,
+                       const TileStep &st, hipStream_t s, const double *psi = nullptr, int nd = 0);
+// q <- q - sum_l (psi_l.q) psi_l and the partial sums of |q|^2; dots: nd * tile_defl_blocks values
+template <typename T>
+int launch_tile_project(T *q, const double *psi, int nd, int64_t dim_up, int64_t dim_dn, int64_t ld, double *dots,
+                        double *norm2, hipStream_t s);
+// b_j of the vector stored last (what 0), or a_j of an H.v no update follows (what 1)
+void launch_tile_scalar(const TileStep &st, int what, hipStream_t s);
+int tile_update_blocks(int64_t n, int elem_bytes);
+int tile_defl_blocks(int64_t dim_up);
 
 template <typename T>
 void launch_axpy_norm(T *w, const T *v, const double *coef, int64_t n, double *partials, int nblocks, hipStream_t s);
@@ -302,16 +394,16 @@ void launch_start_norm2(const double *given, uint64_t seed, int64_t n, double *p
 template <typename T>
 void launch_start_fill(const double *given, uint64_t seed, double c, T *out, T *zero, int64_t dim_up, int64_t dim_dn,
                        int64_t ld, hipStream_t s);
-// psi[r*dim_dn + d] (+)= y_j * coef[0] * v[r*ld + d]
+// psi[r*dim_dn + d] (+)= c * v[r*ld + d]
 template <typename T>
-void launch_psi_acc(double *psi, const T *v, double yj, const double *coef, int64_t dim_up, int64_t dim_dn, int64_t ld,
-                    bool first, hipStream_t s);
+void launch_psi_acc(double *psi, const T *v, double c, int64_t dim_up, int64_t dim_dn, int64_t ld, bool first,
+                    hipStream_t s);
 void launch_psi_stats(const double *psi, const double *given, uint64_t seed, int64_t n, double *partials, int nblocks,
                       hipStream_t s);
-// psi[r*dim_dn + d] = sum_{j < m} y[j] * scale[j] * vecs[j][r*ld + d] (the resident Lanczos vectors)
+// psi[r*dim_dn + d] = sum_{j < m} c[j] * vecs[j][r*ld + d] (the resident Lanczos vectors)
 template <typename T>
-void launch_psi_combine(double *psi, const T *const *vecs, const double *y, const double *scale, int m, int64_t dim_up,
-                        int64_t dim_dn, int64_t ld, hipStream_t s);
+void launch_psi_combine(double *psi, const T *const *vecs, const double *c, int m, int64_t dim_up, int64_t dim_dn,
+                        int64_t ld, hipStream_t s);
 void launch_scale(double *v, double c, int64_t n, hipStream_t s);
 void launch_reduce(const double *partials, int n, int stride, int count, double *out, hipStream_t s);
 // observables.hip: unnormalised sums UU, DD, C (NS x NS each, NS = obs_ns_max)

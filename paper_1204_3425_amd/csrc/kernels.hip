@@ -580,14 +580,12 @@ template int launch_defl_update<float>(float *, const double *, const double *, 
 
 int defl_blocks(int64_t dim_up) { return row_blocks(dim_up); }
 
-// psi += y_j * (1/s) * v, where v holds s f_j and 1/s is the device scalar
-// coef[0] (the ground-state vector sum_j y_j f_j of the replayed recurrence).
+// psi += c v, where v holds s f_j and c = y_j / s (the ground-state vector
+// sum_j y_j f_j of the replayed recurrence).
 template <typename T>
-__global__ __launch_bounds__(256) void psi_acc_kernel(double *__restrict__ psi, const T *__restrict__ v, double yj,
-                                                      const double *__restrict__ coef, int64_t dim_up, int64_t dim_dn,
-                                                      int64_t ld, int first)
+__global__ __launch_bounds__(256) void psi_acc_kernel(double *__restrict__ psi, const T *__restrict__ v, double c,
+                                                      int64_t dim_up, int64_t dim_dn, int64_t ld, int first)
 {
-    const double c = yj * coef[0];
     ROW_LOOP(r, d, dim_up, dim_dn)
     {
         const double add = c * (double)v[r * ld + d];
@@ -597,24 +595,21 @@ __global__ __launch_bounds__(256) void psi_acc_kernel(double *__restrict__ psi, 
 }
 
 template <typename T>
-void launch_psi_acc(double *psi, const T *v, double yj, const double *coef, int64_t dim_up, int64_t dim_dn, int64_t ld,
-                    bool first, hipStream_t s)
+void launch_psi_acc(double *psi, const T *v, double c, int64_t dim_up, int64_t dim_dn, int64_t ld, bool first,
+                    hipStream_t s)
 {
-    hipLaunchKernelGGL(psi_acc_kernel<T>, dim3(row_blocks(dim_up)), dim3(256), 0, s, psi, v, yj, coef, dim_up, dim_dn,
-                       ld, first ? 1 : 0);
+    hipLaunchKernelGGL(psi_acc_kernel<T>, dim3(row_blocks(dim_up)), dim3(256), 0, s, psi, v, c, dim_up, dim_dn, ld,
+                       first ? 1 : 0);
     HUB_HIP(hipGetLastError());
 }
-template void launch_psi_acc<double>(double *, const double *, double, const double *, int64_t, int64_t, int64_t, bool,
-                                     hipStream_t);
-template void launch_psi_acc<float>(double *, const float *, double, const double *, int64_t, int64_t, int64_t, bool,
-                                    hipStream_t);
+template void launch_psi_acc<double>(double *, const double *, double, int64_t, int64_t, int64_t, bool, hipStream_t);
+template void launch_psi_acc<float>(double *, const float *, double, int64_t, int64_t, int64_t, bool, hipStream_t);
 
-// psi = sum_j y_j (1/s_j) v_j over the resident Lanczos vectors, summed in the
+// psi = sum_j c_j v_j over the resident Lanczos vectors, summed in the
 // order of the replayed accumulation
 template <typename T>
 __global__ __launch_bounds__(256) void psi_combine_kernel(double *__restrict__ psi, const T *const *__restrict__ vecs,
-                                                          const double *__restrict__ y,
-                                                          const double *__restrict__ scale, int m, int64_t dim_up,
+                                                          const double *__restrict__ c, int m, int64_t dim_up,
                                                           int64_t dim_dn, int64_t ld)
 {
     ROW_LOOP(r, d, dim_up, dim_dn)
@@ -622,23 +617,23 @@ __global__ __launch_bounds__(256) void psi_combine_kernel(double *__restrict__ p
         double acc = 0.0;
 #pragma unroll 8
         for (int j = 0; j < m; j++)
-            acc += (y[j] * scale[j]) * (double)vecs[j][r * ld + d];
+            acc += c[j] * (double)vecs[j][r * ld + d];
         psi[r * dim_dn + d] = acc;
     }
 }
 
 template <typename T>
-void launch_psi_combine(double *psi, const T *const *vecs, const double *y, const double *scale, int m, int64_t dim_up,
-                        int64_t dim_dn, int64_t ld, hipStream_t s)
+void launch_psi_combine(double *psi, const T *const *vecs, const double *c, int m, int64_t dim_up, int64_t dim_dn,
+                        int64_t ld, hipStream_t s)
 {
-    hipLaunchKernelGGL(psi_combine_kernel<T>, dim3(row_blocks(dim_up)), dim3(256), 0, s, psi, vecs, y, scale, m,
-                       dim_up, dim_dn, ld);
+    hipLaunchKernelGGL(psi_combine_kernel<T>, dim3(row_blocks(dim_up)), dim3(256), 0, s, psi, vecs, c, m, dim_up,
+                       dim_dn, ld);
     HUB_HIP(hipGetLastError());
 }
-template void launch_psi_combine<double>(double *, const double *const *, const double *, const double *, int, int64_t,
-                                         int64_t, int64_t, hipStream_t);
-template void launch_psi_combine<float>(double *, const float *const *, const double *, const double *, int, int64_t,
-                                        int64_t, int64_t, hipStream_t);
+template void launch_psi_combine<double>(double *, const double *const *, const double *, int, int64_t, int64_t,
+                                         int64_t, hipStream_t);
+template void launch_psi_combine<float>(double *, const float *const *, const double *, int, int64_t, int64_t, int64_t,
+                                        hipStream_t);
 
 // partial sums of psi.psi and psi.f1
 __global__ __launch_bounds__(256) void psi_stats_kernel(const double *__restrict__ psi, const double *__restrict__ given,

@@ -279,7 +279,7 @@ void solo_loop(hubbard_server *S)
         }
         int rc;
         try {
-            rc = lanczos_impl(job->h, opts_of(job->req), &job->done.result);
+            rc = lanczos_impl(job->h, opts_of(job->req), &job->done.result, true);
         } catch (const Error &e) {
             rc = e.code;
         }

@@ -44,9 +44,17 @@ __device__ inline double with_sign(double v, uint32_t sg)
 // no barrier is spent on it.
 __device__ inline double wave_total(const double *__restrict__ part, int n)
 {
+    // eight loads in flight (past the end: element 0, not added)
     double s = 0.0;
-    for (int i = threadIdx.x & 63; i < n; i += 64)
-        s += part[i];
+    for (int i = threadIdx.x & 63; i < n; i += 8 * 64) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            v[u] = part[i + 64 * u < n ? i + 64 * u : 0];
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            s += i + 64 * u < n ? v[u] : 0.0;
+    }
     for (int off = 32; off > 0; off >>= 1)
         s += __shfl_xor(s, off, 64);
     return s;
@@ -77,51 +85,129 @@ struct TileArgs {
     int dim_dn, w_up, gmax;  // slots per up row, groups per column
     int nseg, span;          // workgroups per row, columns of each (a multiple of 64)
     double t, U;
-    int64_t pair;  // element offset of the second half of a complex vector (gridDim.y = 2)
+    int64_t pair;            // element offset of the second half of a complex vector (gridDim.y = 2)
+    const double *psi;       // deflated step: nd dense vectors, vector l at psi + l * pdim
+    int nd;
+    int64_t pdim;
 };
+
+// Sum over the workgroup of N values, one of each per thread (fixed order), in
+// thread 0.
+template <int N>
+__device__ inline void tile_sums(double (&v)[N], double (*red)[N])
+{
+#pragma unroll
+    for (int k = 0; k < N; k++)
+        for (int off = 32; off > 0; off >>= 1)
+            v[k] += __shfl_down(v[k], off, 64);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int k = 0; k < N; k++)
+            red[threadIdx.x >> 6][k] = v[k];
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < (int)(blockDim.x >> 6); w++)
+#pragma unroll
+            for (int k = 0; k < N; k++)
+                v[k] += red[w][k];
+}
 
 // GT: per-bond amplitudes.  The entries of all columns are laid out in slots
 // of one amplitude each, so a slot's amplitude is a scalar; up-spin entries
 // carry the class in bits 24..30.
-template <typename T, int MODE, bool GT>
-__global__ __launch_bounds__(1024) void hv_tile_kernel(TileArgs p, const uint4 *__restrict__ dn,
+// dn: [g][d] -> eight 16-bit entries (element index | sign << 15), dn_nq: groups
+// per 64 columns, dn_amp: amplitude of each slot (GT, eight per group); up_rows:
+// w_up slots per row, those past its count repeating its last hop; tcls:
+// amplitude of each class (GT).  ND: room for lower vectors of a deflated step.
+template <typename T, int MODE, bool GT, int ND>
+__global__ __launch_bounds__(1024, (sizeof(T) == 8 || GT || ND > 0) ? 4 : 8) void hv_tile_kernel(TileArgs p, const uint4 *__restrict__ dn,
                                                        const uint8_t *__restrict__ dn_nq,
                                                        const double *__restrict__ dn_amp,
                                                        const uint32_t *__restrict__ up_rows,
                                                        const double *__restrict__ tcls,
                                                        const uint32_t *__restrict__ states_dn,
-                                                       const T *__restrict__ x, int64_t ldx, const T *prev, T *out,
-                                                       int64_t ldy, double shift, TileStep st)
+                                                       const T *__restrict__ x, int64_t ldx, T *__restrict__ out,
+                                                       int64_t ldy, double shift, double *__restrict__ part)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T *xs = reinterpret_cast<T *>(smem_raw);
-    __shared__ double red[16];
     const int ddn = p.dim_dn, nth = (int)blockDim.x, tid = (int)threadIdx.x;
     if (blockIdx.y) {
         x += p.pair;
         out += p.pair;
-        prev += p.pair;
     }
     // workgroup i runs on XCD i mod 8: each XCD takes a contiguous range of
     // rows, so the rows that neighbouring rows hop to are in its L2.  Where rows
     // are few, nseg workgroups share a row, each taking a range of its columns.
     const int unit = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-    const int64_t r = unit / p.nseg;
-    const int c0 = (unit % p.nseg) * p.span, c1 = min(c0 + p.span, ddn);
-    const bool mine = r < p.dim_up;
-    double acc0 = 0.0, acc1 = 0.0;
-    T a_s = (T)1, b_s = (T)0;
-    if (mine) {
-        const T *xr = x + r * ldx;
-        for (int d0 = 0; d0 < ddn; d0 += 4 * nth) {
-            T v[4];
+    const bool mine = unit < p.nseg * p.dim_up;
+    const int64_t r = mine ? unit / p.nseg : 0;
+    const int c0 = mine ? (unit % p.nseg) * p.span : 0, c1 = mine ? min(c0 + p.span, ddn) : c0;
+
+    const T tm = (T)(-p.t), U = (T)p.U;
+    constexpr uint32_t cmask = GT ? kClassColMask : 0x7fffffffu;
+    constexpr int UB = 8;  // up-spin rows in flight before the down-spin gathers
+    // down-spin gathers at once, and up-spin rows in flight after the first
+    // eight: with eight of each an FP64 wave needs 75 registers (14-site ring
+    // 99 -> 95 us with four); FP32 has room (4x4 t-t' 4u4d 61 us, with four 74)
+    constexpr int GB = sizeof(T) == 8 ? 4 : 8, LB = GB;
+    const uint32_t su = p.states_up[r];
+    const int nu = p.nnz_up[r];
+    const uint32_t *__restrict__ urow = up_rows + r * p.w_up;
+    // amplitude of an up-spin entry (GT)
+    auto amp_of = [&](uint32_t e) -> T { return GT ? -(T)tcls[(e >> 24) & 0x7fu] : (T)1; };
+    // the first hops of the row, in scalars for all of its columns
+    uint32_t ue[UB];
+    T uc[UB];
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
+    for (int u = 0; u < UB; u++) {
+        ue[u] = urow[u];
+        uc[u] = amp_of(ue[u]);
+    }
+    // amplitudes of the first two groups of slots
+    T sa[16];
+    if (GT)
+#pragma unroll
+        for (int u = 0; u < 16; u++)
+            sa[u] = -(T)dn_amp[u];
+    auto row_at = [&](uint32_t e, uint32_t off) -> T {
+        const T *row = x + (int64_t)(e & cmask) * ldx;
+        return *reinterpret_cast<const T *>(reinterpret_cast<const unsigned char *>(row) + off);
+    };
+    // A column's entries, configuration and first up-spin rows.  Every load is
+    // issued (columns past the end read the last one, groups past the table
+    // group 0, slots past a row's count its last hop's row again, all unused),
+    // so the wait counters stay exact.
+    uint4 e4[2];
+    uint32_t sd;
+    int nq;
+    T uv[UB];
+    auto fetch = [&](int d) {
+        const int dc = d < ddn ? d : ddn - 1;
+#pragma unroll
+        for (int g = 0; g < 2; g++)
+            e4[g] = dn[(size_t)(g < p.gmax ? g : 0) * (size_t)ddn + (size_t)dc];
+        nq = (int)dn_nq[dc >> 6];
+        sd = states_dn[dc];
+#pragma unroll
+        for (int u = 0; u < UB; u++)
+            uv[u] = row_at(ue[u], (uint32_t)dc * (uint32_t)sizeof(T));
+    };
+    // the row itself, and the first column's loads behind it, before the barrier
+    {
+        const T *xr = x + r * ldx;
+        constexpr int CH = 4;
+        for (int d0 = 0; d0 < ddn; d0 += CH * nth) {
+            T v[CH];
+#pragma unroll
+            for (int u = 0; u < CH; u++) {
                 const int d = d0 + u * nth + tid;
                 v[u] = d < ddn ? xr[d] : (T)0;
             }
+            if (d0 == 0)
+                fetch(c0 + tid);
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
+            for (int u = 0; u < CH; u++) {
                 const int d = d0 + u * nth + tid;
                 if (d < ddn)
                     xs[d] = v[u];
@@ -129,136 +215,309 @@ __global__ __launch_bounds__(1024) void hv_tile_kernel(TileArgs p, const uint4 *
         }
         if (tid == 0)
             xs[ddn] = (T)0;  // the zero slot that padding entries point at
-    }
-    if (MODE == HV_LANCZOS) {
-        // the scalars of step j: b_j is the norm of x (its partial sums), a
-        // start vector of unit norm excepted; alpha = 1/b_j, beta = -b_j/b_{j-1}
-        const double bj = st.j == 0 && st.unit ? 1.0 : sqrt(wave_total(st.norm2, st.n_norm2));
-        const double bm = st.j > 0 ? st.b[st.j - 1] : 1.0;
-        a_s = (T)recip_norm(bj);
-        b_s = (T)(st.j > 0 ? -bj * recip_norm(bm) : 0.0);
-        if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
-            st.b[st.j] = bj;
-            if (st.host_b)
-                st.host_b[2 * st.j] = bj;
-        }
+        // the result rows' padding, which the update pass reads
+        if (MODE == HV_LANCZOS && mine && c1 == ddn && ddn + tid < ldy)
+            out[r * ldy + ddn + tid] = (T)0;
     }
     __syncthreads();
-    if (mine) {
-        const T tm = (T)(-p.t), U = (T)p.U;
-        constexpr uint32_t cmask = GT ? kClassColMask : 0x7fffffffu;
-        constexpr int UB = 8;  // up-spin loads in flight before the down-spin gathers
-        const uint32_t su = p.states_up[r];
-        const int nu = p.nnz_up[r];
-        const uint32_t *__restrict__ urow = up_rows + r * p.w_up;
-        // factor of an up-spin entry: its sign (-t multiplies the sum), or -+ its amplitude
-        auto coeff = [&](uint32_t e) -> T {
-            if (GT) {
-                const T a = (T)tcls[(e >> 24) & 0x7fu];
-                return (e >> 31) ? a : -a;
-            }
-            return (e >> 31) ? (T)-1 : (T)1;
-        };
-        // the first hops of the row, in scalars for all of its columns
-        uint32_t ue[UB];
-        T uc[UB];
+    // partial sums: q.x (and psi_l.q, psi_l.x of a deflated step), or z.z and x.Hx
+    constexpr int NA = MODE == HV_RESIDUAL ? 2 : 1 + 2 * ND;
+    double acc[NA];
 #pragma unroll
-        for (int u = 0; u < UB; u++) {
-            ue[u] = urow[u];
-            uc[u] = coeff(ue[u]);
-        }
-        // amplitudes of the first two groups of slots
-        T sa[16];
-        if (GT)
+    for (int k = 0; k < NA; k++)
+        acc[k] = 0.0;
+    for (int d0 = c0; d0 < c1; d0 += nth) {
+        const int d = d0 + tid;
+        const bool ok = d < c1;
+        const int dc = ok ? d : ddn - 1;
+        // psi_l at this element, in flight while the hops are summed
+        double pv[ND > 0 ? ND : 1];
+        if (ND > 0)
 #pragma unroll
-            for (int u = 0; u < 16; u++)
-                sa[u] = -(T)dn_amp[u];
-        for (int d = c0 + tid; d < c1; d += nth) {
-            const uint32_t off = (uint32_t)d * (uint32_t)sizeof(T);
-            auto row_at = [&](uint32_t e) -> T {
-                const T *row = x + (int64_t)(e & cmask) * ldx;
-                return *reinterpret_cast<const T *>(reinterpret_cast<const unsigned char *>(row) + off);
-            };
-            // the down-spin entries first, then the first up-spin rows, which
-            // stay in flight while the down-spin hops are summed; every load is
-            // issued (groups past a column chunk's count read group 0, slots
-            // past a row's count its last hop's row again, both unused), so the
-            // wait counters stay exact
-            uint4 e4[2];
+            for (int l = 0; l < ND; l++)
+                pv[l] = p.psi[(int64_t)(l < p.nd ? l : 0) * p.pdim + r * ddn + dc];
+        const T xv = xs[dc];
+        // the hops are summed first (with one amplitude as +-x, exact factors)
+        // and join the interaction term in one rounding
+        T h = (T)0, h1 = (T)0;
+        auto group = [&](const uint4 &e, auto &&amp) {
+            const uint32_t ev[4] = {e.x, e.y, e.z, e.w};
+            T v[8];
 #pragma unroll
-            for (int g = 0; g < 2; g++)
-                e4[g] = dn[(size_t)(g < p.gmax ? g : 0) * (size_t)ddn + (size_t)d];
-            const int nq = __builtin_amdgcn_readfirstlane((int)dn_nq[d >> 6]);
-            const uint32_t sd = states_dn[d];
-            T uv[UB];
+            for (int b = 0; b < 8; b += GB) {
 #pragma unroll
-            for (int u = 0; u < UB; u++)
-                uv[u] = row_at(ue[u]);
-            const T xv = xs[d];
-            // the hops are summed first (with one amplitude as +-x, exact
-            // factors) and join the interaction term in one rounding
-            T h = (T)0, h1 = (T)0;
-            auto group = [&](const uint4 &e, auto &&amp) {
-                const uint32_t ev[4] = {e.x, e.y, e.z, e.w};
-                T v[8];
-#pragma unroll
-                for (int u = 0; u < 8; u++)
+                for (int u = b; u < b + GB; u++)
                     v[u] = xs[(ev[u >> 1] >> ((u & 1) * 16)) & 0x7fffu];
 #pragma unroll
-                for (int u = 0; u < 8; u++) {
-                    T &acc = (u & 1) ? h1 : h;
+                for (int u = b; u < b + GB; u++) {
+                    T &a = (u & 1) ? h1 : h;
                     const T w = with_sign(v[u], entry_sign(ev[u >> 1], u & 1));
-                    acc = GT ? fma(amp(u), w, acc) : acc + w;
+                    a = GT ? fma(amp(u), w, a) : a + w;
                 }
-            };
-#pragma unroll
-            for (int g = 0; g < 2; g++)
-                if (g < nq)
-                    group(e4[g], [&](int u) { return sa[8 * g + u]; });
-            for (int g = 2; g < nq; g++)
-                group(dn[(size_t)g * (size_t)ddn + (size_t)d], [&](int u) { return -(T)dn_amp[8 * g + u]; });
-#pragma unroll
-            for (int u = 0; u < UB; u++)
-                if (u < nu) {
-                    T &acc = (u & 1) ? h1 : h;
-                    acc = fma(uc[u], uv[u], acc);
-                }
-            for (int k = UB; k < nu; k += 4) {
-                T v[4];
-#pragma unroll
-                for (int u = 0; u < 4; u++)
-                    v[u] = row_at(urow[k + u]);
-#pragma unroll
-                for (int u = 0; u < 4; u++)
-                    if (k + u < nu)
-                        h = fma(coeff(urow[k + u]), v[u], h);
             }
-            const T ud = U * (T)__popc(su & sd);
-            h = GT ? fma(ud, xv, h + h1) : fma(tm, h + h1, ud * xv);
-            const int64_t J = r * ldy + d;
-            if (MODE == HV_STORE) {
-                out[J] = h;
-            } else if (MODE == HV_LANCZOS) {
-                const T w = st.j > 0 ? a_s * h + b_s * prev[J] : a_s * h;
-                out[J] = w;
-                acc0 += (double)w * (double)xv;
+        };
+        const int nqs = __builtin_amdgcn_readfirstlane(nq);
+#pragma unroll
+        for (int g = 0; g < 2; g++)
+            if (g < nqs)
+                group(e4[g], [&](int u) { return sa[8 * g + u]; });
+        for (int g = 2; g < nqs; g++)
+            group(dn[(size_t)g * (size_t)ddn + (size_t)dc], [&](int u) { return -(T)dn_amp[8 * g + u]; });
+        // up-spin hops, eight rows in flight; a last, partial batch selects
+        // (branching over single hops would let the compiler move each load
+        // into its branch, one wait per hop)
+        const uint32_t off = (uint32_t)dc * (uint32_t)sizeof(T);
+        auto add = [&](auto &v, int k, auto &&ent, auto &&amp) {
+            constexpr int N = (int)(sizeof(v) / sizeof(T));
+            auto one = [&](int u, T a) {
+                const T w = with_sign(v[u], ent(u) & 0x80000000u);
+                return GT ? fma(amp(u), w, a) : a + w;
+            };
+            if (k + N <= nu) {
+#pragma unroll
+                for (int u = 0; u < N; u++) {
+                    T &a = (u & 1) ? h1 : h;
+                    a = one(u, a);
+                }
             } else {
+#pragma unroll
+                for (int u = 0; u < N; u++) {
+                    T &a = (u & 1) ? h1 : h;
+                    const T w = one(u, a);
+                    a = k + u < nu ? w : a;
+                }
+            }
+        };
+        auto later = [&](int k) {
+            T v2[LB];
+#pragma unroll
+            for (int u = 0; u < LB; u++)
+                v2[u] = row_at(urow[k + u], off);
+            if (k == UB)
+                add(uv, 0, [&](int u) { return ue[u]; }, [&](int u) { return uc[u]; });
+            add(v2, k, [&](int u) { return urow[k + u]; }, [&](int u) { return amp_of(urow[k + u]); });
+        };
+        if (nu > UB) {
+            later(UB);
+            for (int k = UB + LB; k < nu; k += LB)
+                later(k);
+        } else {
+            add(uv, 0, [&](int u) { return ue[u]; }, [&](int u) { return uc[u]; });
+        }
+        const T ud = U * (T)__popc(su & sd);
+        h = GT ? fma(ud, xv, h + h1) : fma(tm, h + h1, ud * xv);
+        if (d0 + nth < c1)
+            fetch(d + nth);
+        if (ok) {
+            if (MODE != HV_RESIDUAL)
+                out[r * ldy + d] = h;
+            if (MODE == HV_LANCZOS) {
+                acc[0] += (double)h * (double)xv;
+#pragma unroll
+                for (int l = 0; l < ND; l++) {
+                    acc[1 + 2 * l] += (double)h * pv[l];
+                    acc[2 + 2 * l] += (double)xv * pv[l];
+                }
+            } else if (MODE == HV_RESIDUAL) {
                 const double z = (double)h - shift * (double)xv;
-                acc0 += z * z;
-                acc1 += (double)xv * (double)h;
+                acc[0] += z * z;
+                acc[NA - 1] += (double)xv * (double)h;
             }
         }
     }
     if (MODE != HV_STORE) {
-        const int b = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-        const double s0 = tile_sum(acc0, red);
+        __shared__ double red[16][NA];
+        tile_sums<NA>(acc, red);
+        const int b = (int)(blockIdx.y * gridDim.x + blockIdx.x), nb = (int)(gridDim.x * gridDim.y);
         if (tid == 0)
-            st.part[b] = s0;
-        if (MODE == HV_RESIDUAL) {
-            const double s1 = tile_sum(acc1, red);
-            if (tid == 0)
-                st.part[gridDim.x * gridDim.y + b] = s1;
+#pragma unroll
+            for (int k = 0; k < NA; k++)
+                if (MODE == HV_RESIDUAL || k <= 2 * p.nd)
+                    part[(int64_t)k * nb + b] = acc[k];
+    }
+}
+
+// The other half of a step.  With x_j = b_j f_j stored, q = H x_j and the sums
+// part (q.x) and norm2 (|x_j|^2) known, b_j = |x_j|, a_j = q.x / b_j^2 and
+//     x_{j+1} = q / b_j - (a_j / b_j) x_j - (b_j / b_{j-1}) x_{j-1}
+// (formed in FP64, rounded once), with the partial sums of |x_{j+1}|^2.  Every
+// workgroup forms the scalars itself from the same sums in the same order, so
+// no launch is spent on them and the H.v needs none: on sectors of this size a
+// launch, and a chain of dependent loads in front of the H.v, cost as much as
+// the arithmetic.  A deflated step (ND > 0) takes sum_l g_l psi_l off as well,
+// g_l = psi_l.x_{j+1} from the H.v's sums psi_l.q and psi_l.x_j of this step and
+// psi_l.x_{j-1} of the one before: without the last two, which are rounding
+// errors of the earlier projections, those would grow from step to step.
+constexpr int kUpdThreads = 256;
+
+template <typename T, int ND>
+__global__ __launch_bounds__(kUpdThreads) void tile_update_kernel(T *__restrict__ q, const T *__restrict__ x,
+                                                                  const T *__restrict__ xp, int64_t dim_up,
+                                                                  int64_t dim_dn, int64_t ld, int halves, TileStep st,
+                                                                  const double *__restrict__ psi, int nd)
+{
+    constexpr int E = 16 / (int)sizeof(T), NW = kUpdThreads / 64, NT = 2 + 3 * ND;
+    typedef __attribute__((ext_vector_type(E))) T vec;
+    __shared__ double tot[NT];
+    __shared__ double red[NW];
+    const int wave = (int)threadIdx.x >> 6;
+    // the first vectors are loaded before the sums, which they do not need
+    const int64_t nv = (int64_t)halves * dim_up * ld / E, stride = (int64_t)gridDim.x * kUpdThreads;
+    vec *qv = reinterpret_cast<vec *>(q);
+    const vec *xv = reinterpret_cast<const vec *>(x), *pv = reinterpret_cast<const vec *>(st.j > 0 ? xp : x);
+    int64_t i = (int64_t)blockIdx.x * kUpdThreads + threadIdx.x;
+    vec qn, xn, pn;
+    auto load = [&](int64_t at) {
+        const int64_t k = at < nv ? at : nv - 1;
+        qn = qv[k];
+        xn = xv[k];
+        pn = pv[k];
+    };
+    if (ND == 0)
+        load(i);
+    // the sums, one per wave at a time
+    for (int k = wave; k < 2 + 3 * nd; k += NW) {
+        double s = 0.0;
+        if (k == 0)
+            s = st.j > 0 || !st.unit ? wave_total(st.norm2, st.n_norm2) : 1.0;
+        else if (k == 1)
+            s = wave_total(st.part, st.n_part);
+        else if ((k - 2) % 3 < 2)  // psi_l.q, psi_l.x_j
+            s = wave_total(st.part + (int64_t)(1 + 2 * ((k - 2) / 3) + (k - 2) % 3) * st.n_part, st.n_part);
+        else if (st.j > 0)  // psi_l.x_{j-1}
+            s = wave_total(st.part_prev + (int64_t)(2 + 2 * ((k - 2) / 3)) * st.n_part, st.n_part);
+        if ((threadIdx.x & 63) == 0)
+            tot[k] = s;
+    }
+    __syncthreads();
+    const double bj = sqrt(tot[0]), s = recip_norm(bj), a = tot[1] * s * s;
+    const double c = a * s, e = st.j > 0 ? bj * recip_norm(st.b[st.j - 1]) : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st.b[st.j] = bj;
+        st.hist[2 * st.j] = bj;
+        st.hist[2 * st.j + 1] = a;
+    }
+    double acc = 0.0;
+    if constexpr (ND == 0) {
+        // e is 0 in step 0, where x stands in for the vector before it
+        while (i < nv) {
+            vec w;
+#pragma unroll
+            for (int k = 0; k < E; k++) {
+                w[k] = (T)(s * (double)qn[k] - c * (double)xn[k] - e * (double)pn[k]);
+                acc += (double)w[k] * (double)w[k];
+            }
+            qv[i] = w;
+            i += stride;
+            if (i < nv)
+                load(i);
         }
+    } else {
+        double g[ND];
+#pragma unroll
+        for (int l = 0; l < ND; l++)
+            g[l] = l < nd ? s * tot[2 + 3 * l] - c * tot[3 + 3 * l] - e * tot[4 + 3 * l] : 0.0;
+        const int64_t dim = dim_up * dim_dn;
+        for (int64_t r = blockIdx.x; r < dim_up; r += gridDim.x)
+            for (int64_t d = threadIdx.x; d < dim_dn; d += kUpdThreads) {
+                const int64_t i = r * ld + d;
+                const double pn = st.j > 0 ? (double)xp[i] : 0.0;
+                double v = s * (double)q[i] - c * (double)x[i] - e * pn;
+                double w[ND];
+#pragma unroll
+                for (int l = 0; l < ND; l++)
+                    w[l] = psi[(int64_t)(l < nd ? l : 0) * dim + r * dim_dn + d];
+#pragma unroll
+                for (int l = 0; l < ND; l++)
+                    v -= g[l] * w[l];
+                const T t = (T)v;
+                q[i] = t;
+                acc += (double)t * (double)t;
+            }
+    }
+    const double sum = tile_sum(acc, red);
+    if (threadIdx.x == 0)
+        st.norm2_out[blockIdx.x] = sum;
+}
+
+// Projection of a vector in FP64 (rows at stride ld, psi_l dense), for the
+// start vector and for steps with more lower vectors than the kernels above
+// take: partial sums of psi_l.q, then q <- q - sum_l (psi_l.q) psi_l with the
+// partial sums of |q|^2.
+template <typename T>
+__global__ __launch_bounds__(kUpdThreads) void tile_defl_dots_kernel(const T *__restrict__ q,
+                                                                     const double *__restrict__ psi, int nd,
+                                                                     int64_t dim_up, int64_t dim_dn, int64_t ld,
+                                                                     double *__restrict__ dots)
+{
+    __shared__ double red[kUpdThreads / 64];
+    double acc[kMaxDeflate];
+#pragma unroll
+    for (int l = 0; l < kMaxDeflate; l++)
+        acc[l] = 0.0;
+    const int64_t dim = dim_up * dim_dn;
+    for (int64_t r = blockIdx.x; r < dim_up; r += gridDim.x)
+        for (int64_t d = threadIdx.x; d < dim_dn; d += kUpdThreads) {
+            const double v = (double)q[r * ld + d];
+            const double *p = psi + r * dim_dn + d;
+#pragma unroll
+            for (int l = 0; l < kMaxDeflate; l++)
+                if (l < nd)
+                    acc[l] += v * p[l * dim];
+        }
+    for (int l = 0; l < nd; l++) {
+        const double sl = tile_sum(acc[l], red);
+        if (threadIdx.x == 0)
+            dots[(int64_t)l * gridDim.x + blockIdx.x] = sl;
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kUpdThreads) void tile_defl_update_kernel(T *__restrict__ q,
+                                                                       const double *__restrict__ psi, int nd,
+                                                                       int64_t dim_up, int64_t dim_dn, int64_t ld,
+                                                                       const double *__restrict__ dots,
+                                                                       double *__restrict__ norm2)
+{
+    __shared__ double red[kUpdThreads / 64];
+    __shared__ double c[kMaxDeflate];
+    for (int l = (int)threadIdx.x >> 6; l < nd; l += kUpdThreads / 64) {
+        const double s = wave_total(dots + (int64_t)l * gridDim.x, (int)gridDim.x);
+        if ((threadIdx.x & 63) == 0)
+            c[l] = s;
+    }
+    __syncthreads();
+    const int64_t dim = dim_up * dim_dn;
+    double acc = 0.0;
+    for (int64_t r = blockIdx.x; r < dim_up; r += gridDim.x)
+        for (int64_t d = threadIdx.x; d < dim_dn; d += kUpdThreads) {
+            double v = (double)q[r * ld + d];
+            const double *p = psi + r * dim_dn + d;
+#pragma unroll
+            for (int l = 0; l < kMaxDeflate; l++)
+                if (l < nd)
+                    v -= c[l] * p[l * dim];
+            const T t = (T)v;
+            q[r * ld + d] = t;
+            acc += (double)t * (double)t;
+        }
+    const double s = tile_sum(acc, red);
+    if (threadIdx.x == 0)
+        norm2[blockIdx.x] = s;
+}
+
+// b_j of the vector stored last, which no update forms (and, for what 1, a_j
+// of an H.v that no update follows).
+__global__ __launch_bounds__(64) void tile_scalar_kernel(TileStep st, int what)
+{
+    const double b = sqrt(st.j > 0 || !st.unit ? wave_total(st.norm2, st.n_norm2) : 1.0);
+    const double s = recip_norm(b);
+    const double a = what ? wave_total(st.part, st.n_part) * s * s : 0.0;
+    if (threadIdx.x == 0) {
+        st.b[st.j] = b;
+        st.hist[2 * st.j] = b;
+        if (what)
+            st.hist[2 * st.j + 1] = a;
     }
 }
 
@@ -297,8 +556,8 @@ TilePlan make_tile_plan(const HvArgs &a, int elem_bytes)
 }
 
 template <typename T>
-void launch_hv_tile(const HvArgs &a, const TilePlan &pl, const T *x, int64_t ldx, const T *prev, T *out, int64_t ldy,
-                    int mode, double shift, const TileStep &st, int64_t pair, hipStream_t s)
+void launch_hv_tile(const HvArgs &a, const TilePlan &pl, const T *x, int64_t ldx, T *out, int64_t ldy, int mode,
+                    double shift, double *part, hipStream_t s, const double *psi, int nd, int64_t pair)
 {
     TileArgs p;
     const bool gt = a.tcls != nullptr;
@@ -313,23 +572,31 @@ void launch_hv_tile(const HvArgs &a, const TilePlan &pl, const T *x, int64_t ldx
     p.t = a.t;
     p.U = a.U;
     p.pair = pair;
+    p.psi = psi;
+    p.nd = nd;
+    p.pdim = a.dim_up * a.dim_dn;
     auto go = [&](auto kern) {
         if (pl.lds > 64 * 1024)
             HUB_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds));
         hipLaunchKernelGGL(kern, dim3(pl.grid, pair ? 2 : 1), dim3(pl.threads), pl.lds, s, p,
                            gt ? a.dn_slots : a.dn_groups16, gt ? a.dn_slot_nq : a.dn_nq8, a.dn_slot_amp, a.up_tile,
-                           a.tcls, a.states_dn, x, ldx, prev, out, ldy,
-                           shift, st);
+                           a.tcls, a.states_dn, x, ldx, out, ldy, shift, part);
         HUB_HIP(hipGetLastError());
     };
     auto by_mode = [&](auto gtc) {
         constexpr bool GT = decltype(gtc)::value;
         if (mode == HV_STORE)
-            go(hv_tile_kernel<T, HV_STORE, GT>);
-        else if (mode == HV_LANCZOS)
-            go(hv_tile_kernel<T, HV_LANCZOS, GT>);
+            go(hv_tile_kernel<T, HV_STORE, GT, 0>);
+        else if (mode == HV_RESIDUAL)
+            go(hv_tile_kernel<T, HV_RESIDUAL, GT, 0>);
+        else if (nd > 2)
+            go(hv_tile_kernel<T, HV_LANCZOS, GT, kTileDefl>);
+        else if (nd == 2)
+            go(hv_tile_kernel<T, HV_LANCZOS, GT, 2>);
+        else if (nd == 1)
+            go(hv_tile_kernel<T, HV_LANCZOS, GT, 1>);
         else
-            go(hv_tile_kernel<T, HV_RESIDUAL, GT>);
+            go(hv_tile_kernel<T, HV_LANCZOS, GT, 0>);
     };
     if (gt)
         by_mode(std::true_type());
@@ -337,9 +604,64 @@ void launch_hv_tile(const HvArgs &a, const TilePlan &pl, const T *x, int64_t ldx
         by_mode(std::false_type());
 }
 
-template void launch_hv_tile<double>(const HvArgs &, const TilePlan &, const double *, int64_t, const double *,
-                                     double *, int64_t, int, double, const TileStep &, int64_t, hipStream_t);
-template void launch_hv_tile<float>(const HvArgs &, const TilePlan &, const float *, int64_t, const float *, float *,
-                                    int64_t, int, double, const TileStep &, int64_t, hipStream_t);
+int tile_update_blocks(int64_t n, int elem_bytes)
+{
+    // two 16-byte vectors per thread or more, and no more partial sums than a
+    // wave adds up in a few loads
+    const int64_t b = (n * elem_bytes / 16 + 2 * kUpdThreads - 1) / (2 * kUpdThreads);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(b, 1024));
+}
+
+int tile_defl_blocks(int64_t dim_up) { return (int)std::min<int64_t>(dim_up, 1024); }
+
+template <typename T>
+int launch_tile_update(T *q, const T *x, const T *xp, int64_t dim_up, int64_t dim_dn, int64_t ld, int halves,
+                       const TileStep &st, hipStream_t s, const double *psi, int nd)
+{
+    const int nb = nd > 0 ? tile_defl_blocks(dim_up) : tile_update_blocks(halves * dim_up * ld, sizeof(T));
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(kUpdThreads), 0, s, q, x, xp, dim_up, dim_dn, ld, halves, st, psi, nd);
+    };
+    if (nd > 2)
+        go(tile_update_kernel<T, kTileDefl>);
+    else if (nd == 2)
+        go(tile_update_kernel<T, 2>);
+    else if (nd == 1)
+        go(tile_update_kernel<T, 1>);
+    else
+        go(tile_update_kernel<T, 0>);
+    HUB_HIP(hipGetLastError());
+    return nb;
+}
+
+template <typename T>
+int launch_tile_project(T *q, const double *psi, int nd, int64_t dim_up, int64_t dim_dn, int64_t ld, double *dots,
+                        double *norm2, hipStream_t s)
+{
+    const int nb = tile_defl_blocks(dim_up);
+    hipLaunchKernelGGL(tile_defl_dots_kernel<T>, dim3(nb), dim3(kUpdThreads), 0, s, q, psi, nd, dim_up, dim_dn, ld,
+                       dots);
+    HUB_HIP(hipGetLastError());
+    hipLaunchKernelGGL(tile_defl_update_kernel<T>, dim3(nb), dim3(kUpdThreads), 0, s, q, psi, nd, dim_up, dim_dn, ld,
+                       dots, norm2);
+    HUB_HIP(hipGetLastError());
+    return nb;
+}
+
+void launch_tile_scalar(const TileStep &st, int what, hipStream_t s)
+{
+    hipLaunchKernelGGL(tile_scalar_kernel, dim3(1), dim3(64), 0, s, st, what);
+    HUB_HIP(hipGetLastError());
+}
+
+#define HUB_TILE_INST(T)                                                                                             \
+    template void launch_hv_tile<T>(const HvArgs &, const TilePlan &, const T *, int64_t, T *, int64_t, int, double, \
+                                    double *, hipStream_t, const double *, int, int64_t);                            \
+    template int launch_tile_update<T>(T *, const T *, const T *, int64_t, int64_t, int64_t, int, const TileStep &,  \
+                                       hipStream_t, const double *, int);                                           \
+    template int launch_tile_project<T>(T *, const double *, int, int64_t, int64_t, int64_t, double *, double *,     \
+                                        hipStream_t);
+HUB_TILE_INST(double)
+HUB_TILE_INST(float)
 
 }  // namespace hub

@@ -1,4 +1,5 @@
-"""The one-launch H.v of small and medium sectors at its edges, against the oracle.
+"""The one-launch H.v of small and medium sectors at its edges, and the Lanczos
+and Krylov steps built on it, against the oracle.
 
 Shapes: rows of one element, of little more than one wave and of little more than
 one pass of the workgroup, a single row and few rows (several
@@ -111,3 +112,107 @@ def test_one_launch_apply_infinite_element():
     rest = ~hit
     rest[h.dim // 3] = False
     assert np.all(got[rest] == 0.0)
+
+
+STEP_CASES = [
+    # name, sites, edges, n_up, n_dn, amplitude classes
+    ("ring8", 8, workload.ring(8), 4, 4, 0),
+    ("odd_792x924", 12, workload.torus(3, 4), 5, 6, 0),
+    # 4,845 rows: more partial sums than the update adds up itself
+    ("4845_rows", 20, workload.ring(20), 4, 1, 0),
+    ("few_rows_shared", 13, workload.ring(13), 1, 6, 0),
+    # a class per bond: rows of 462 elements (not on 16 bytes when dense)
+    ("class_per_bond", 11, workload.ring(11), 5, 6, 11),
+]
+
+
+@pytest.mark.parametrize("name,sites,edges,nu,nd,ncls", STEP_CASES, ids=[c[0] for c in STEP_CASES])
+def test_one_launch_steps(name, sites, edges, nu, nd, ncls):
+    """Twelve steps against the oracle's Alg. 1.  Each a_j, b_{j+1} carries the
+    rounding of its sums, about sqrt(dim) eps of |H|, forward through the
+    recurrence: 64 sqrt(dim) eps relative, as for every coefficient test.  The
+    vectors kept in slots, in the three work vectors (basis limit 0) and moved
+    from the one to the other in mid-run give the same bits."""
+    print("steps", name, flush=True)
+    amps = _amps(edges, ncls, sites) if ncls else None
+    h = hb.hubbard_build_bonds(sites, edges, amps, nu, nd, 3.0) if amps else hb.hubbard_build(sites, edges, nu, nd, 1.0, 3.0)
+    m = oracle.Model(sites, edges, nu, nd, amps if amps else 1.0, 3.0)
+    ref = m.lanczos(oracle.start_vector(5, m.dim), tol=-1.0, max_iter=40, want_psi=True)
+    psi = torch.empty(h.dim, dtype=torch.float64, device=DEV)
+    r = hb.hubbard_lanczos_ex(h, tol=-1.0, max_iter=40, seed=5, psi=psi)
+    tol = 64 * np.sqrt(h.dim) * np.finfo(float).eps
+    scale = np.abs(ref["a"][:12]).max() + ref["b"][:12].max()
+    assert np.abs(r["a"][:12] - ref["a"][:12]).max() <= tol * scale
+    assert np.abs(r["b"][:12] - ref["b"][:12]).max() <= tol * scale
+    assert abs(r["E0"] - ref["E0"]) <= 1e-12 * max(1.0, abs(ref["E0"]))
+    assert r["psi_resident"] == 1
+    ld = (h.dim_dn + 63) // 64 * 64
+    for limit in (0, 33 * h.dim_up * ld * 8):  # no slots; one chunk of 32 vectors for 40 steps
+        hb.hubbard_set_basis_limit(h, limit)
+        again = torch.empty_like(psi)
+        q = hb.hubbard_lanczos_ex(h, tol=-1.0, max_iter=40, seed=5, psi=again)
+        assert q["psi_resident"] == 0
+        assert np.array_equal(q["a"], r["a"]) and np.array_equal(q["b"], r["b"])
+        assert float((again - psi).abs().max()) <= 1e-12
+    # both precisions of one handle share its kept buffers
+    mixed = hb.hubbard_lanczos_ex(h, tol=-1.0, max_iter=12, seed=5, precision=hb.HUBBARD_MIXED)
+    assert np.abs(mixed["a"] - ref["a"][:12]).max() <= 1e-4 * scale
+    assert np.array_equal(hb.hubbard_lanczos_ex(h, tol=-1.0, max_iter=40, seed=5)["a"], r["a"])
+
+
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 7])
+def test_one_launch_deflated_steps(k):
+    """One to six lower states: one, two and up to four are projected out inside
+    the two launches, more by the separate projection.  A ring of 9 sites with
+    random amplitudes has no degenerate levels (spacing above 1e-3)."""
+    print("deflated", k, flush=True)
+    edges = workload.ring(9)
+    amps = _amps(edges, 9, 31)
+    h = hb.hubbard_build_bonds(9, edges, amps, 3, 2, 2.0)
+    m = oracle.Model(9, edges, 3, 2, amps, 2.0)
+    w, V = m.lowest_states(k)
+    psi = torch.empty((k, h.dim), dtype=torch.float64, device=DEV)
+    E, _ = hb.hubbard_lowest_states(h, k, tol=1e-14, max_iter=600, psi=psi)
+    assert np.abs(E - w).max() <= 1e-10 * max(1.0, np.abs(w).max())
+    P = psi.cpu().numpy()
+    assert np.abs(P @ P.T - np.eye(k)).max() <= 1e-12
+
+
+def test_one_launch_propagation_many_rows():
+    """A Krylov step on 4,845 rows (the partial sums reduced first), against the
+    power series of exp(-i H t) from the oracle's H.v (terms below 1e-17)."""
+    h = hb.hubbard_build(20, workload.ring(20), 4, 1, 1.0, 3.0)
+    m = oracle.Model(20, workload.ring(20), 4, 1, 1.0, 3.0)
+    g = np.random.default_rng(3)
+    psi = g.uniform(-1, 1, h.dim) + 1j * g.uniform(-1, 1, h.dim)
+    psi /= np.linalg.norm(psi)
+    want, term = psi.copy(), psi.copy()
+    for n in range(1, 40):
+        term = -1j * 0.1 / n * (m.apply(np.ascontiguousarray(term.real)) + 1j * m.apply(np.ascontiguousarray(term.imag)))
+        want = want + term
+        if np.linalg.norm(term) < 1e-17:
+            break
+    re, im = torch.from_numpy(psi.real.copy()).to(DEV), torch.from_numpy(psi.imag.copy()).to(DEV)
+    r = hb.hubbard_propagate(h, re, im, 0.1, 1, 20)
+    got = re.cpu().numpy() + 1j * im.cpu().numpy()
+    assert r["err_est"] <= 1e-13
+    assert np.linalg.norm(got - want) <= 1e-11
+
+
+def test_kept_buffers_two_streams_and_a_batch_of_one_handle():
+    """A handle's kept buffers are not shared by work in flight: solves on two
+    streams in turn, and the same handle several times in one batch."""
+    h = hb.hubbard_build(10, workload.ring(10), 5, 5, 1.0, 4.0)
+    psi = torch.empty(h.dim, dtype=torch.float64, device=DEV)
+    first = hb.hubbard_lanczos_ex(h, tol=1e-10, seed=9, psi=psi)
+    want = psi.clone()
+    side = torch.cuda.Stream()
+    for s in (side, torch.cuda.current_stream(), side):
+        with torch.cuda.stream(s):
+            psi.zero_()
+            r = hb.hubbard_lanczos_ex(h, tol=1e-10, seed=9, psi=psi)
+        s.synchronize()
+        assert np.array_equal(r["a"], first["a"]) and torch.equal(psi, want)
+    one = hb.hubbard_lanczos_batch([h], tol=1e-10, seeds=[9])[0]
+    for r in hb.hubbard_lanczos_batch([h, h, h], tol=1e-10, seeds=[9, 9, 9]):
+        assert r["E0"] == one["E0"] and r["n_iter"] == one["n_iter"]
