@@ -1850,13 +1850,11 @@ int hubbard_observables(hubbard_h h, const double *psi, double *dens, double *co
         const int ps = 3 * NS * NS + 1;
         const int np = obs_partial_count(h->sites, h->up.dim, h->dn.dim);
         DevBuf part(sizeof(double) * (size_t)np * (size_t)ps, &h->ws);
-        DevBuf sums(sizeof(double) * (size_t)ps, &h->ws);
+        PinnedBuf sums(sizeof(double) * (size_t)ps, &h->ws);  // written by the last kernel, no copy
         launch_observables(psi, h->dev.states_up, h->dev.states_dn, h->sites, h->up.dim, h->dn.dim,
-                           part.as<double>(), sums.as<double>(), kObsDefaultBlocks, h->stream);
-        std::vector<double> r((size_t)ps);
-        HUB_HIP(hipMemcpyAsync(r.data(), sums.p, sizeof(double) * (size_t)ps, hipMemcpyDeviceToHost, h->stream));
+                           part.as<double>(), static_cast<double *>(sums.dev), kObsDefaultBlocks, h->stream);
         HUB_HIP(hipStreamSynchronize(h->stream));
-        observables_out(h, r.data(), dens, corr, docc);
+        observables_out(h, sums.as<double>(), dens, corr, docc);
         return HUBBARD_OK;
     });
 }

@@ -408,9 +408,9 @@ void launch_scale(double *v, double c, int64_t n, hipStream_t s);
 void launch_reduce(const double *partials, int n, int stride, int count, double *out, hipStream_t s);
 // observables.hip: unnormalised sums UU, DD, C (NS x NS each, NS = obs_ns_max)
 // and the norm of psi^2 into out[3 * NS * NS + 1]; part holds
-// obs_partial_count blocks of that size (the workgroups' partials and the
-// group sums of the reduction).  max_blocks bounds the accumulating workgroups.
-constexpr int kObsDefaultBlocks = 2048;
+// obs_partial_count blocks of that size.  max_blocks bounds the accumulating
+// workgroups (three on a CU fill its registers).
+constexpr int kObsDefaultBlocks = 768;
 int obs_ns_max(int sites);
 int obs_partial_count(int ns, int64_t dim_up, int64_t dim_dn, int max_blocks = kObsDefaultBlocks);
 void launch_observables(const double *psi, const uint32_t *states_up, const uint32_t *states_dn, int ns,

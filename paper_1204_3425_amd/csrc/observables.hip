@@ -7,26 +7,32 @@
 //   DD[i][j] = sum_J w_J bit_i(dn_d) bit_j(dn_d)     <n_{i dn} n_{j dn}>
 //   C[i][j]  = sum_J w_J bit_i(up_r) bit_j(dn_d)     <n_{i up} n_{j dn}>
 //   norm     = sum_J w_J
-// (unnormalised).  One pass reads psi once.  A workgroup of TW threads takes a
-// tile of 2 TW down configurations (two per thread) and a strided set of up rows.
-// Each thread sums, over those rows, w into q(x) and into A_i(x) for every site i
-// occupied in the row's up configuration (a branch that is uniform across the
-// workgroup, N_up adds per element).  Per row, the wave's total R of w is formed
-// by a butterfly and lane j adds bit_i(up_r) bit_j(up_r) R into column j of UU.
-// At the end the workgroup writes A and q to LDS and forms, one (i, j) pair per
-// thread, C[i][j] = sum_x A_i(x) bit_j(dn_x) and DD[i][j] = sum_x q(x) bit_i(dn_x)
-// bit_j(dn_x) over its tile.  Every workgroup writes one partial of
-// 3 * NS * NS + 1 values; a second kernel sums the partials in a fixed order,
+// (unnormalised).  One pass reads psi once, and its sums run on the matrix
+// cores: the occupation bits of four up rows are the 16 x 4 operand U (0 or 1, so
+// every product is exact), w of those rows in 16 columns the 4 x 16 operand, and
+//   A_i(x) = sum_r bit_i(up_r) w(r, x)
+// accumulates over the rows in FP64.  With the rows' totals R_r (a rotation sum
+// over the 16 lanes that hold a row) UU takes one more product per four rows, U
+// times (U^T R).  A tile of columns ends with C = sum_x A_i(x) bit_j(dn_x) and DD =
+// sum_x q(x) bit_i(dn_x) bit_j(dn_x), q(x) the column totals, again as products,
+// from LDS.  A workgroup takes a range of rows, its four waves every fourth
+// group of four, and one or more tiles of columns; it writes one partial of
+// 3 * NS * NS + 1 values and a second kernel sums the partials in a fixed order,
 // so the result is reproducible.
+//
+// What bounds it: reading psi (4x4 6u6d, 513 MB: 100 us at the 5.1 TB/s of a large
+// copy).  Per 512 elements a wave spends nine products of 16 x 16 x 4 and about
+// fifty vector instructions, half of what the memory allows.  The form before
+// this one added w to 16 sums per element on the vector units, with a wave
+// reduction and 16 conversions and products for UU per 128 elements, and took
+// 322 us (1.6 TB/s).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
-
-// wave-wide sum from the ROCm device library (DPP reduction, every lane gets it)
-extern "C" __device__ __attribute__((const)) double __ockl_wfred_add_f64(double);
 
 namespace hub {
 
@@ -36,245 +42,277 @@ constexpr int obs_partial_size()
     return 3 * NS * NS + 1;
 }
 
-// workgroup width; each thread takes kObsSlots down configurations, so a tile
-// is kObsSlots * TW wide.  The LDS image of A (NS x TW doubles, one slot at a
-// time) stays within 64 KB.
-constexpr int kObsSlots = 2;
+typedef __attribute__((ext_vector_type(4))) double d4;
+constexpr int kObsThreads = 256;
+// columns of a tile: its sums A take eight (NS = 16) or two times four accumulators
 template <int NS>
-constexpr int obs_threads()
+constexpr int obs_tile()
 {
-    return NS <= 16 ? 256 : 128;
+    return NS <= 16 ? 128 : 64;
 }
 
-template <int NS, int TW>
-__global__ __launch_bounds__(TW) void obs_accumulate_kernel(const double *__restrict__ psi,
-                                                            const uint32_t *__restrict__ states_up,
-                                                            const uint32_t *__restrict__ states_dn, int ns,
-                                                            int64_t dim_up, int64_t dim_dn, int ntiles, int nchunks,
-                                                            double *__restrict__ part)
+// v plus the values of the other 15 lanes of its row of 16 (in every lane)
+__device__ inline double row16_sum(double v)
 {
-    constexpr int NW = TW / 64, SL = kObsSlots;
-    __shared__ double a_lds[NS][TW];
-    __shared__ double q_lds[TW];
-    __shared__ uint32_t dn_lds[TW];
-    __shared__ double uu_lds[NS][NS];
-    __shared__ double nw[NW];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int tile = blockIdx.x % ntiles, chunk = blockIdx.x / ntiles;
-    int64_t x[SL];
-    bool have[SL];
-#pragma unroll
-    for (int s = 0; s < SL; s++) {
-        x[s] = ((int64_t)tile * SL + s) * TW + t;  // this thread's down configurations
-        have[s] = x[s] < dim_dn;
-    }
+    auto add = [&](auto ctrl) {
+        constexpr int C = decltype(ctrl)::value;
+        const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), C, 0xf, 0xf, false);
+        const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), C, 0xf, 0xf, false);
+        v += __hiloint2double(hi, lo);
+    };
+    // row rotations by 8, 4, 2 and 1
+    add(std::integral_constant<int, 0x128>());
+    add(std::integral_constant<int, 0x124>());
+    add(std::integral_constant<int, 0x122>());
+    add(std::integral_constant<int, 0x121>());
+    return v;
+}
 
-    double A[SL][NS], UU[NS], q[SL];
+// Operands of the 16 x 16 x 4 product (lane l): A[l % 16][l / 16], B[l / 16][l % 16];
+// element v of the accumulator is D[4 v + l / 16][l % 16].
+// E = 2: a lane loads two neighbouring columns (16 bytes; even dim_dn, psi on 16
+// bytes), which go to two accumulators; E = 1 otherwise.
+template <int NS, int E>
+__global__ __launch_bounds__(kObsThreads, NS <= 16 ? 3 : 2) void obs_accumulate_kernel(const double *__restrict__ psi,
+                                                                     const uint32_t *__restrict__ states_up,
+                                                                     const uint32_t *__restrict__ states_dn,
+                                                                     int64_t dim_up, int64_t dim_dn, int ntiles,
+                                                                     int ncols, int64_t rows_per,
+                                                                     double *__restrict__ part)
+{
+    constexpr int NH = NS / 16, XT = obs_tile<NS>(), NT = XT / 16, NL = NT / E, NW = kObsThreads / 64;
+    typedef typename std::conditional<E == 2, double2, double>::type V;
+    __shared__ double a_lds[NS][XT + 1];
+    __shared__ double q_lds[XT];
+    __shared__ uint32_t dn_lds[XT];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, kk = lane >> 4;
+    // workgroup: column range of tiles, row range
+    const int cg = blockIdx.x % ncols;
+    const int64_t rbeg = (int64_t)(blockIdx.x / ncols) * rows_per;
+    const int64_t rend = rbeg + rows_per < dim_up ? rbeg + rows_per : dim_up;
+    const int t0 = (int)((int64_t)cg * ntiles / ncols), t1 = (int)((int64_t)(cg + 1) * ntiles / ncols);
+    d4 UU[NH][NH], C[NH][NH], DD[NH][NH];
 #pragma unroll
-    for (int i = 0; i < NS; i++) {
-        UU[i] = 0.0;
+    for (int h = 0; h < NH; h++)
 #pragma unroll
-        for (int s = 0; s < SL; s++)
-            A[s][i] = 0.0;
-    }
-#pragma unroll
-    for (int s = 0; s < SL; s++)
-        q[s] = 0.0;
+        for (int g = 0; g < NH; g++)
+            UU[h][g] = C[h][g] = DD[h][g] = (d4)0.0;
     double norm = 0.0;
-    // lane j < ns keeps column j of UU; its own occupation as 0 or 1
-    const double lbit = lane < ns ? 1.0 : 0.0;
-    const int lsite = lane & 31;
-    auto row_step = [&](uint32_t up, const double *w) {
-        double R = 0.0;
+    for (int t = t0; t < t1; t++) {
+        const int64_t x0 = (int64_t)t * XT;
+        d4 A[NH][NT];
+        double q[NT];
 #pragma unroll
-        for (int s = 0; s < SL; s++) {
-            q[s] += w[s];
-            R += w[s];
+        for (int m = 0; m < NT; m++) {
+            q[m] = 0.0;
+#pragma unroll
+            for (int h = 0; h < NH; h++)
+                A[h][m] = (d4)0.0;
         }
-        // the up word is the same for the whole workgroup: its bits become 0/1
-        // factors instead of branches
+        // four rows from r, one per 16 lanes; past the range (and the columns) an
+        // element in range is read and weighted 0
+        auto load = [&](int64_t r, V (&v)[NL], uint32_t &up) {
+            const int64_t row = min(r + kk, dim_up - 1);
+            const double *p = psi + row * dim_dn;
 #pragma unroll
-        for (int i = 0; i < NS; i++) {
-            const double b = (double)((up >> i) & 1u);
-#pragma unroll
-            for (int s = 0; s < SL; s++)
-                A[s][i] = fma(b, w[s], A[s][i]);
-        }
-        R = __ockl_wfred_add_f64(R);  // the wave's total of the row
-        norm += R;
-        const double mine = lbit * (double)((up >> lsite) & 1u) * R;
-#pragma unroll
-        for (int i = 0; i < NS; i++)
-            UU[i] = fma((double)((up >> i) & 1u), mine, UU[i]);
-    };
-    // a contiguous range of rows (neighbouring rows share address-translation
-    // pages); four rows per round, the next round's loads issued before this
-    // round's arithmetic
-    const int64_t rpb = (dim_up + nchunks - 1) / nchunks;
-    const int64_t rbeg = chunk * rpb, rend = rbeg + rpb < dim_up ? rbeg + rpb : dim_up;
-    auto load = [&](int64_t r0, double (*v)[SL]) {
-#pragma unroll
-        for (int k = 0; k < 4; k++)
-#pragma unroll
-            for (int s = 0; s < SL; s++) {
-                const int64_t r = r0 + k;
-                v[k][s] = (have[s] && r < rend) ? psi[r * dim_dn + x[s]] : 0.0;
+            for (int m = 0; m < NL; m++) {
+                const int64_t x = x0 + (16 * m + n) * E;
+                v[m] = *reinterpret_cast<const V *>(p + (x < dim_dn ? x : 0));
             }
-    };
-    double v[4][SL], vn[4][SL];
-    int64_t r = rbeg;
-    if (r < rend)
-        load(r, v);
-    for (; r < rend; r += 4) {
-        if (r + 4 < rend)
-            load(r + 4, vn);
+            up = states_up[row];
+        };
+        V v[NL], vn[NL];
+        uint32_t up = 0, upn = 0;
+        int64_t r = rbeg + 4 * wave;
+        if (r < rend)
+            load(r, v, up);
+        for (; r < rend; r += 4 * NW) {
+            load(r + 4 * NW, vn, upn);
+            const bool ok = r + kk < rend;
+            double w[NT], R = 0.0;
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const int64_t rk = r + k;
-            if (rk < rend) {
-                double w[SL];
+            for (int m = 0; m < NL; m++) {
+                const bool in = ok && x0 + (16 * m + n) * E < dim_dn;
+                const double *e = reinterpret_cast<const double *>(&v[m]);
 #pragma unroll
-                for (int s = 0; s < SL; s++)
-                    w[s] = v[k][s] * v[k][s];
-                row_step(states_up[rk], w);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; k++)
-#pragma unroll
-            for (int s = 0; s < SL; s++)
-                v[k][s] = vn[k][s];
-    }
-
-    if (lane == 0)
-        nw[wave] = norm;
-    // the waves' UU columns, summed through LDS one wave at a time
-    for (int k = 0; k < NW; k++) {
-        if (wave == k && lane < NS) {
-#pragma unroll
-            for (int i = 0; i < NS; i++) {
-                const double u = lane < ns ? UU[i] : 0.0;
-                uu_lds[i][lane] = k == 0 ? u : uu_lds[i][lane] + u;
-            }
-        }
-        __syncthreads();
-    }
-    // C and DD over the tile, one slot's TW configurations at a time
-    double c[(NS * NS + TW - 1) / TW], dd[(NS * NS + TW - 1) / TW];
-#pragma unroll
-    for (int k = 0; k < (NS * NS + TW - 1) / TW; k++) {
-        c[k] = 0.0;
-        dd[k] = 0.0;
-    }
-#pragma unroll
-    for (int s = 0; s < SL; s++) {
-#pragma unroll
-        for (int i = 0; i < NS; i++)
-            a_lds[i][t] = A[s][i];
-        q_lds[t] = q[s];
-        dn_lds[t] = have[s] ? states_dn[x[s]] : 0u;
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < (NS * NS + TW - 1) / TW; k++) {
-            const int e = t + k * TW;
-            const int i = e / NS, j = e % NS;
-            if (e < NS * NS && i < ns && j < ns) {
-                const uint32_t bj = 1u << j, mask = (1u << i) | bj;
-                for (int y = 0; y < TW; y++) {
-                    const uint32_t b = dn_lds[y];
-                    c[k] += (b & bj) ? a_lds[i][y] : 0.0;
-                    dd[k] += (b & mask) == mask ? q_lds[y] : 0.0;
+                for (int k = 0; k < E; k++) {
+                    const double y = in ? e[k] : 0.0;
+                    w[m * E + k] = y * y;
+                    q[m * E + k] += w[m * E + k];
+                    R += w[m * E + k];
                 }
             }
+            R = row16_sum(R);
+            double u[NH];
+#pragma unroll
+            for (int h = 0; h < NH; h++)
+                u[h] = (double)((up >> (16 * h + n)) & 1u);
+#pragma unroll
+            for (int h = 0; h < NH; h++) {
+#pragma unroll
+                for (int m = 0; m < NT; m++)
+                    A[h][m] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[h], w[m], A[h][m], 0, 0, 0);
+#pragma unroll
+                for (int g = 0; g < NH; g++)
+                    UU[h][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[h], u[g] * R, UU[h][g], 0, 0, 0);
+            }
+#pragma unroll
+            for (int m = 0; m < NL; m++)
+                v[m] = vn[m];
+            up = upn;
+        }
+        // the waves' A and q added up in LDS, one wave at a time
+        for (int x = threadIdx.x; x < XT; x += kObsThreads)
+            dn_lds[x] = x0 + x < dim_dn ? states_dn[x0 + x] : 0u;
+        for (int k = 0; k < NW; k++) {
+            if (wave == k) {
+#pragma unroll
+                for (int m = 0; m < NT; m++) {
+                    const int x = (16 * (m / E) + n) * E + m % E;
+#pragma unroll
+                    for (int h = 0; h < NH; h++)
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {
+                            double &a = a_lds[16 * h + 4 * e + kk][x];
+                            a = k == 0 ? A[h][m][e] : a + A[h][m][e];
+                        }
+                    double s = q[m];
+                    s += __shfl_xor(s, 16, 64);
+                    s += __shfl_xor(s, 32, 64);
+                    if (kk == 0)
+                        q_lds[x] = k == 0 ? s : q_lds[x] + s;
+                }
+            }
+            __syncthreads();
+        }
+        // C and DD over the tile, four columns per product, the waves taking turns
+        for (int c = wave; c < XT / 4; c += NW) {
+            const int x = 4 * c + kk;
+            const uint32_t dn = dn_lds[x];
+            const double qx = q_lds[x];
+            double bit[NH];
+#pragma unroll
+            for (int h = 0; h < NH; h++)
+                bit[h] = (double)((dn >> (16 * h + n)) & 1u);
+#pragma unroll
+            for (int h = 0; h < NH; h++) {
+                const double ax = a_lds[16 * h + n][x];
+#pragma unroll
+                for (int g = 0; g < NH; g++) {
+                    C[h][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(ax, bit[g], C[h][g], 0, 0, 0);
+                    DD[h][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(qx * bit[h], bit[g], DD[h][g], 0, 0, 0);
+                }
+            }
+            if (n == 0)
+                norm += qx;
         }
         __syncthreads();
     }
+    // the waves' sums, one wave at a time, straight to the partial
     double *out = part + (int64_t)blockIdx.x * obs_partial_size<NS>();
+    __shared__ double nw[NW];
+    for (int off = 32; off > 0; off >>= 1)
+        norm += __shfl_down(norm, off, 64);
+    if (lane == 0)
+        nw[wave] = norm;
+    double *acc = &a_lds[0][0];  // NS * NS values
+    auto sum_out = [&](const d4 (&m)[NH][NH], int at) {
+        for (int k = 0; k < NW; k++) {
+            if (wave == k)
 #pragma unroll
-    for (int k = 0; k < (NS * NS + TW - 1) / TW; k++) {
-        const int e = t + k * TW;
-        if (e < NS * NS) {
-            out[e] = uu_lds[e / NS][e % NS];
-            out[NS * NS + e] = dd[k];
-            out[2 * NS * NS + e] = c[k];
+                for (int h = 0; h < NH; h++)
+#pragma unroll
+                    for (int g = 0; g < NH; g++)
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {
+                            double &a = acc[(16 * h + 4 * e + kk) * NS + 16 * g + n];
+                            a = k == 0 ? m[h][g][e] : a + m[h][g][e];
+                        }
+            __syncthreads();
         }
-    }
-    if (t == 0) {
-        double n = 0.0;
+        for (int e = threadIdx.x; e < NS * NS; e += kObsThreads)
+            out[at + e] = acc[e];
+        __syncthreads();
+    };
+    sum_out(UU, 0);
+    sum_out(DD, NS * NS);
+    sum_out(C, 2 * NS * NS);
+    if (threadIdx.x == 0) {
+        double s = 0.0;
         for (int k = 0; k < NW; k++)
-            n += nw[k];
-        out[3 * NS * NS] = n;
+            s += nw[k];
+        out[3 * NS * NS] = s;
     }
 }
 
-// Sum of the per-workgroup partials in two fixed-order levels: group g of
-// kObsGroups adds partials [g * nparts / G, (g + 1) * nparts / G) of element e
-// into grp[g][e]; then out[e] adds the groups in order.
-constexpr int kObsGroups = 32;
+// Sum of the per-workgroup partials in a fixed order: a workgroup takes eight
+// elements, 32 threads each adding every 32nd partial, then the 32 in order.
+constexpr int kObsSumElems = 8;
 
 __global__ __launch_bounds__(256) void obs_sum_kernel(const double *__restrict__ part, int nparts, int psize,
-                                                      double *__restrict__ grp)
+                                                      double *__restrict__ out)
 {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    const int g = blockIdx.y;
-    if (e >= psize)
-        return;
-    const int b0 = (int)((int64_t)g * nparts / kObsGroups), b1 = (int)((int64_t)(g + 1) * nparts / kObsGroups);
+    __shared__ double red[256 / kObsSumElems][kObsSumElems];
+    const int i = threadIdx.x % kObsSumElems, g = threadIdx.x / kObsSumElems, G = 256 / kObsSumElems;
+    const int e = blockIdx.x * kObsSumElems + i;
     double s = 0.0;
-    for (int b = b0; b < b1; b++)
-        s += part[(int64_t)b * psize + e];
-    grp[(int64_t)g * psize + e] = s;
-}
-
-__global__ __launch_bounds__(256) void obs_sum_groups_kernel(const double *__restrict__ grp, int psize,
-                                                             double *__restrict__ out)
-{
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= psize)
-        return;
-    double s = 0.0;
-    for (int g = 0; g < kObsGroups; g++)
-        s += grp[(int64_t)g * psize + e];
-    out[e] = s;
+    if (e < psize) {
+#pragma unroll 8
+        for (int b = g; b < nparts; b += G)
+            s += part[(int64_t)b * psize + e];
+    }
+    red[g][i] = s;
+    __syncthreads();
+    if (g == 0 && e < psize) {
+        s = red[0][i];
+        for (int k = 1; k < G; k++)
+            s += red[k][i];
+        out[e] = s;
+    }
 }
 
 int obs_ns_max(int sites) { return sites <= 16 ? 16 : 32; }
 
-static void obs_grid(int ns, int64_t dim_up, int64_t dim_dn, int &ntiles, int &nchunks, int max_blocks = 2048)
+// Workgroups: as many column ranges as there are tiles (one or more tiles
+// each), and row ranges of a multiple of 16 rows to make up max_blocks.
+static void obs_grid(int ns, int64_t dim_up, int64_t dim_dn, int &ntiles, int &ncols, int64_t &rows_per, int &nblocks,
+                     int max_blocks)
 {
-    const int tw = kObsSlots * (ns <= 16 ? obs_threads<16>() : obs_threads<32>());
-    ntiles = (int)((dim_dn + tw - 1) / tw);
-    int64_t nc = max_blocks / ntiles;
-    if (nc < 1)
-        nc = 1;
-    if (nc > dim_up)
-        nc = dim_up;
-    nchunks = (int)nc;
+    const int xt = ns <= 16 ? obs_tile<16>() : obs_tile<32>();
+    ntiles = (int)((dim_dn + xt - 1) / xt);
+    ncols = std::min(ntiles, max_blocks);
+    const int64_t nr = std::max<int64_t>(1, max_blocks / ncols);
+    rows_per = ((dim_up + nr - 1) / nr + 15) / 16 * 16;
+    nblocks = ncols * (int)((dim_up + rows_per - 1) / rows_per);
 }
 
 int obs_partial_count(int ns, int64_t dim_up, int64_t dim_dn, int max_blocks)
 {
-    int ntiles, nchunks;
-    obs_grid(ns, dim_up, dim_dn, ntiles, nchunks, max_blocks);
-    return ntiles * nchunks + kObsGroups;  // the workgroups' partials, then the group sums
+    int ntiles, ncols, nblocks;
+    int64_t rows_per;
+    obs_grid(ns, dim_up, dim_dn, ntiles, ncols, rows_per, nblocks, max_blocks);
+    return nblocks;
 }
 
 template <int NS>
-static void launch_obs(const double *psi, const uint32_t *states_up, const uint32_t *states_dn, int ns, int64_t dim_up,
+static void launch_obs(const double *psi, const uint32_t *states_up, const uint32_t *states_dn, int64_t dim_up,
                        int64_t dim_dn, double *part, double *out, int max_blocks, hipStream_t s)
 {
-    int ntiles, nchunks;
-    obs_grid(ns, dim_up, dim_dn, ntiles, nchunks, max_blocks);
-    const int nblocks = ntiles * nchunks;
-    constexpr int TW = obs_threads<NS>();
-    hipLaunchKernelGGL((obs_accumulate_kernel<NS, TW>), dim3(nblocks), dim3(TW), 0, s, psi, states_up, states_dn, ns,
-                       dim_up, dim_dn, ntiles, nchunks, part);
-    HUB_HIP(hipGetLastError());
+    int ntiles, ncols, nblocks;
+    int64_t rows_per;
+    obs_grid(NS, dim_up, dim_dn, ntiles, ncols, rows_per, nblocks, max_blocks);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(nblocks), dim3(kObsThreads), 0, s, psi, states_up, states_dn, dim_up, dim_dn,
+                           ntiles, ncols, rows_per, part);
+        HUB_HIP(hipGetLastError());
+    };
+    if (dim_dn % 2 == 0 && (uintptr_t)psi % 16 == 0)
+        go(obs_accumulate_kernel<NS, 2>);
+    else
+        go(obs_accumulate_kernel<NS, 1>);
     const int ps = obs_partial_size<NS>();
-    double *grp = part + (int64_t)nblocks * ps;
-    hipLaunchKernelGGL(obs_sum_kernel, dim3((ps + 255) / 256, kObsGroups), dim3(256), 0, s, part, nblocks, ps, grp);
-    HUB_HIP(hipGetLastError());
-    hipLaunchKernelGGL(obs_sum_groups_kernel, dim3((ps + 255) / 256), dim3(256), 0, s, grp, ps, out);
+    hipLaunchKernelGGL(obs_sum_kernel, dim3((ps + kObsSumElems - 1) / kObsSumElems), dim3(256), 0, s, part, nblocks, ps,
+                       out);
     HUB_HIP(hipGetLastError());
 }
 
@@ -282,9 +320,9 @@ void launch_observables(const double *psi, const uint32_t *states_up, const uint
                         int64_t dim_up, int64_t dim_dn, double *part, double *out, int max_blocks, hipStream_t s)
 {
     if (ns <= 16)
-        launch_obs<16>(psi, states_up, states_dn, ns, dim_up, dim_dn, part, out, max_blocks, s);
+        launch_obs<16>(psi, states_up, states_dn, dim_up, dim_dn, part, out, max_blocks, s);
     else
-        launch_obs<32>(psi, states_up, states_dn, ns, dim_up, dim_dn, part, out, max_blocks, s);
+        launch_obs<32>(psi, states_up, states_dn, dim_up, dim_dn, part, out, max_blocks, s);
 }
 
 // Scratch of the entry point that allocates nothing (hubbard_observables_noalloc):
@@ -314,14 +352,12 @@ double *obs_scratch(int device)
 
 int obs_noalloc_blocks(int ns, int64_t dim_up, int64_t dim_dn)
 {
+    (void)dim_up;
+    (void)dim_dn;
     const int ps = ns <= 16 ? obs_partial_size<16>() : obs_partial_size<32>();
-    // partials (blocks + groups) and the final sums must fit the scratch
-    const int64_t cap = (int64_t)(kObsScratchBytes / sizeof(double)) / ps - kObsGroups - 1;
-    int max_blocks = (int)std::min<int64_t>(2048, cap);
-    while (max_blocks > 1 && (int64_t)(obs_partial_count(ns, dim_up, dim_dn, max_blocks) + 1) * ps >
-                                 (int64_t)(kObsScratchBytes / sizeof(double)))
-        max_blocks--;
-    return max_blocks;
+    // partials and the final sums must fit the scratch
+    const int64_t cap = (int64_t)(kObsScratchBytes / sizeof(double)) / ps - 1;
+    return (int)std::min<int64_t>(kObsDefaultBlocks, cap);
 }
 
 }  // namespace hub
