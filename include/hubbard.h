@@ -321,7 +321,7 @@ int hubbard_start_raw(uint64_t seed, int64_t dim, double *f, void *hip_stream);
 /* Runs n independent Lanczos solves (one per handle, each with opts[i]) on the
  * current device, writing res[i].  Solves without a psi request whose rows fit
  * in 64 KB share their launches: every step of every such solve runs in the
- * same four kernel launches (Sec. 5 notes that small systems leave the GPU
+ * same two kernel launches (Sec. 5 notes that small systems leave the GPU
  * idle), and the Ritz value E_j and the stop tests of hubbard_lanczos_ex are
  * evaluated on the device, so the host reads results a few steps behind.  The
  * others run one after another.  A batched result does not depend on which

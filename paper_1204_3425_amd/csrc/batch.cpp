@@ -6,8 +6,8 @@
 // instance's {a_{j-1}, b_j, E_{j-1}, code} to a mailbox in mapped host memory;
 // the host reads them kLookahead steps behind (after that step's event), so it
 // never waits for the device inside a run.  Stopped instances skip later
-// steps; the descriptor table is rebuilt when instances join or when every
-// listed one has finished.
+// steps; the descriptor table is rebuilt when instances join and when half of
+// the listed ones or more have finished.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -21,16 +21,9 @@ namespace hub {
 
 namespace {
 
-struct Dev {
-    void *p = nullptr;
-    explicit Dev(size_t bytes) { HUB_HIP(hipMalloc(&p, bytes ? bytes : 16)); }
-    ~Dev()
-    {
-        if (p)
-            (void)hipFree(p);
-    }
-    Dev(const Dev &) = delete;
-    Dev &operator=(const Dev &) = delete;
+// Device buffer (from the handle's workspace where one is given).
+struct Dev : DevBuf {
+    explicit Dev(size_t bytes, Workspace *ws = nullptr) : DevBuf(std::max<size_t>(bytes, 16), ws) {}
 };
 
 // Pinned host memory that kernels write directly (mapped, coherent): the
@@ -52,12 +45,24 @@ struct Pinned {
     Pinned &operator=(const Pinned &) = delete;
 };
 
-constexpr int64_t kItemElems = 2048;  // target elements per work item
+// Target elements per H.v work item: 64 FP32 rings of 10 to 12 sites took 21.4 ms
+// at 2,048, 22.1 at 4,096 and 24 at 8,192 (fewer workgroups to hide the staging).
+constexpr int64_t kItemElems = 2048;
+// Elements per update item (a multiple of four).
+constexpr int64_t kUpdElems = 8192;
 
 int64_t rows_per_item(const hubbard *h)
 {
     int64_t r = kItemElems / std::max<int64_t>(1, h->dn.dim);
     return std::max<int64_t>(1, std::min<int64_t>(r, h->up.dim));
+}
+
+// Rows staged as pairs, with their negatives: up to 32 KB for two rows (longer
+// ones would leave a CU with under four workgroups), and vectors whose byte
+// offsets are 32-bit numbers.
+bool pair_rows(const hubbard *h, size_t es)
+{
+    return h->dev.dn_pair16 && (size_t)h->dn.dim * es <= 8 * 1024 && (uint64_t)h->dim * es < ((uint64_t)1 << 32);
 }
 
 template <typename T>
@@ -70,9 +75,10 @@ struct Slot {
     BatchState *state = nullptr;
     double *part = nullptr, *part2 = nullptr, *hist = nullptr;
     int64_t rpi = 1;
-    int nitems = 0;
+    int nitems = 0, nupd = 0;
+    int64_t stride = 0;  // elements from the first vector to the second (on 256 bytes)
     int64_t launched = 0;  // steps launched for this instance
-    int norm_at = -1;      // pending start vector: index of its squared norm in the host array
+    bool fresh = true;     // its start vector is still to be written
     int index = -1;  // position in the current descriptor table, -1 before the first rebuild
     std::vector<double> a, b, e;
     int stop = HUBBARD_STOP_MAXITER;
@@ -86,7 +92,9 @@ constexpr int kLookahead = 4;
 template <typename T>
 class Engine : public BatchRunner {
   public:
-    explicit Engine(hipStream_t s) : s_(s)
+    // keep: the instances' buffers come from their handles' workspaces (the
+    // handles outlive the engine)
+    explicit Engine(hipStream_t s, bool keep = false) : s_(s), keep_(keep)
     {
         for (auto &e : ev_)
             HUB_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -116,36 +124,22 @@ class Engine : public BatchRunner {
         const int64_t n = h->dim;
         sl->rpi = rows_per_item(h);
         sl->nitems = (int)((h->up.dim + sl->rpi - 1) / sl->rpi);
-        const int sb = stream_blocks(n);
+        sl->nupd = (int)((n + kUpdElems - 1) / kUpdElems);
+        sl->stride = (n + 63) / 64 * 64;
         // one allocation: the two vectors, the state, the coefficient history
         // and both sets of partial sums, each on 256 bytes
         auto up = [](size_t b) { return (b + 255) / 256 * 256; };
-        const size_t b_work = up(2 * sizeof(T) * (size_t)n), b_state = up(sizeof(BatchState)),
+        const size_t b_work = up(2 * sizeof(T) * (size_t)sl->stride), b_state = up(sizeof(BatchState)),
                      b_hist = up(sizeof(double) * 2 * (size_t)o.max_iter),
-                     b_part = up(sizeof(double) * (size_t)std::max(sl->nitems, 2 * sb + 8)),
-                     b_part2 = up(sizeof(double) * (size_t)sl->nitems);
-        sl->mem = std::make_unique<Dev>(b_work + b_state + b_hist + b_part + b_part2);
+                     b_part = up(sizeof(double) * (size_t)sl->nitems),
+                     b_part2 = up(sizeof(double) * (size_t)sl->nupd);
+        sl->mem = std::make_unique<Dev>(b_work + b_state + b_hist + b_part + b_part2, keep_ ? &h->ws : nullptr);
         char *base = static_cast<char *>(sl->mem->p);
         sl->work = base;
         sl->state = reinterpret_cast<BatchState *>(base + b_work);
         sl->hist = reinterpret_cast<double *>(base + b_work + b_state);
         sl->part = reinterpret_cast<double *>(base + b_work + b_state + b_hist);
         sl->part2 = reinterpret_cast<double *>(base + b_work + b_state + b_hist + b_part);
-        // |f_1|^2 from the seed (or the given vector), written straight to host
-        // memory; the start vector is filled once all joining instances' norms
-        // are known (one wait for all of them)
-        if (norms_cap_ <= pending_fill_) {
-            // grow before any pending norm is written: the array is only swapped while none is
-            (void)hipStreamSynchronize(s_);
-            std::unique_ptr<Pinned> bigger = std::make_unique<Pinned>(sizeof(double) * (size_t)(2 * norms_cap_ + 64));
-            if (norms_ && pending_fill_ > 0)
-                std::memcpy(bigger->p, norms_->p, sizeof(double) * (size_t)pending_fill_);
-            norms_ = std::move(bigger);
-            norms_cap_ = 2 * norms_cap_ + 64;
-        }
-        sl->norm_at = pending_fill_++;
-        launch_start_norm2(o.start, o.seed, n, sl->part, sb, s_);
-        launch_reduce(sl->part, sb, 0, 1, static_cast<double *>(norms_->dev) + sl->norm_at, s_);
         slots_.push_back(std::move(sl));
         dirty_ = true;
     }
@@ -166,7 +160,9 @@ class Engine : public BatchRunner {
             const int k = (int)(launched_ % kRing);
             double *mb = static_cast<double *>(mail_host_->dev) + (size_t)k * 4 * table_.size();
             launch_batch_step<T>(static_cast<BatchInst *>(insts_->p), (int)table_.size(),
-                                 static_cast<const BatchItem *>(items_->p), n_items_, lds_, mb, (int)launched_, s_);
+                                 static_cast<const BatchItem *>(items_->p), n_items_, n_upd_, lds_, pairs_, mb,
+                                 (int)launched_,
+                                 s_);
             for (Slot<T> *sl : table_)
                 sl->launched++;
             HUB_HIP(hipEventRecord(ev_[k], s_));
@@ -176,10 +172,13 @@ class Engine : public BatchRunner {
         // instance has stopped on the device
         while (read_ < launched_ && (launched_ - read_ > kLookahead || pending_stopped_ == (int)table_.size()))
             read_step(finished);
-        if (read_ == launched_ && pending_stopped_ == (int)table_.size()) {
-            // every instance in the table is finished: the next step starts a fresh table
+        // every instance in the table is finished: the next step starts a fresh
+        // table; so it does when half of them are, whose workgroups would only
+        // find that out (64 rings of 10 to 12 sites: 15.6 ms without, 14.8 with,
+        // though each new table waits for the steps in flight)
+        const int left = (int)table_.size() - pending_stopped_;
+        if ((read_ == launched_ && left == 0) || (left > 0 && left * 2 <= (int)table_.size()))
             dirty_ = true;
-        }
         return finished;
     }
 
@@ -249,23 +248,6 @@ class Engine : public BatchRunner {
         HUB_HIP(hipStreamSynchronize(s_));
         while (read_ < launched_)
             read_step(finished);
-        // start vectors of the instances that joined: f_1 = f / |f| (Alg. 1)
-        const double *nh = norms_ ? static_cast<const double *>(norms_->p) : nullptr;
-        for (auto &slp : slots_) {
-            Slot<T> &sl = *slp;
-            if (sl.norm_at < 0)
-                continue;
-            const double nrm2 = nh[sl.norm_at];
-            sl.norm_at = -1;
-            if (!(nrm2 > 0.0) || !std::isfinite(nrm2))
-                fail(HUBBARD_EINVAL, "start vector has zero or non-finite norm");
-            const hubbard *h = sl.h;
-            T *v0 = static_cast<T *>(sl.work);
-            launch_start_fill<T>(sl.o.start, sl.o.seed, 1.0 / std::sqrt(nrm2), v0, v0 + h->dim, h->up.dim, h->dn.dim,
-                                 h->dn.dim, s_);
-            launch_batch_init_state(sl.state, s_);
-        }
-        pending_fill_ = 0;
         std::vector<std::unique_ptr<Slot<T>>> keep;
         for (auto &sl : slots_)
             if (!sl->done)
@@ -279,7 +261,8 @@ class Engine : public BatchRunner {
         if (n == 0)
             return;
         std::vector<BatchInst> desc((size_t)n);
-        std::vector<BatchItem> items;
+        pairs_ = true;
+        std::vector<BatchItem> items, upd, start;
         size_t lds = 16;
         for (int i = 0; i < n; i++) {
             Slot<T> &sl = *slots_[(size_t)i];
@@ -288,26 +271,32 @@ class Engine : public BatchRunner {
             std::memset(&d, 0, sizeof(d));
             d.states_up = h->dev.states_up;
             d.states_dn = h->dev.states_dn;
-            d.up_rows = h->dev.up_rows;
-            d.dn_cols = h->dev.dn_cols;
+            d.up_tile = h->dev.up_tile;
             d.nnz_up = h->dev.nnz_up;
-            d.nnz_dn = h->dev.nnz_dn;
+            d.dn_groups = reinterpret_cast<const uint4 *>(h->dev.dn_groups16);
+            d.dn_nq = h->dev.dn_nq8;
+            const bool pairs = pair_rows(h, sizeof(T));
+            pairs_ = pairs_ && pairs;
+            d.dn_pair = pairs ? reinterpret_cast<const uint4 *>(h->dev.dn_pair16) : nullptr;
             d.dim_up = h->up.dim;
             d.dim_dn = h->dn.dim;
             d.dim = h->dim;
-            d.w_up = std::max(1, h->up.width);
-            d.w_dn = h->dn.width;
+            d.w_up = h->dev.up_tile_w;
+            d.gmax = std::max((h->dn.width + 7) / 8, 1);
             d.t = h->t;
             d.U = h->U;
             T *v0 = static_cast<T *>(sl.work);
             d.vec0 = v0;
-            d.vec1 = v0 + h->dim;
+            d.vec1 = v0 + sl.stride;
+            d.start = sl.o.start;
+            d.seed = sl.o.seed;
             d.st = sl.state;
             d.hist = sl.hist;
             d.part = sl.part;
             d.part2 = sl.part2;
             d.tol = sl.o.tol;
             d.nparts = sl.nitems;
+            d.nparts2 = sl.nupd;
             d.slot = i;
             d.max_iter = sl.o.max_iter;
             d.j0 = (int32_t)sl.launched;
@@ -320,13 +309,32 @@ class Engine : public BatchRunner {
                 it.nrows = std::min<int64_t>(sl.rpi, h->up.dim - it.r0);
                 items.push_back(it);
             }
-            lds = std::max(lds, (size_t)sl.rpi * (size_t)h->dn.dim * sizeof(T));  // one work item's rows
+            // one work item's rows, a zero slot after each (twice where they are
+            // staged as pairs of x and -x)
+            lds = std::max(lds, (size_t)(pairs ? (sl.rpi + 1) / 2 * 4 : sl.rpi) * (size_t)(h->dn.dim + 1) * sizeof(T));
+            for (int k = 0; k < sl.nupd; k++) {
+                BatchItem it;
+                it.inst = i;
+                it.part = k;
+                it.r0 = (int64_t)k * kUpdElems;
+                it.nrows = std::min<int64_t>(kUpdElems, h->dim - it.r0);
+                upd.push_back(it);
+                if (sl.fresh)
+                    start.push_back(it);
+            }
             table_.push_back(&sl);
         }
+        const int n_items = (int)items.size();
+        items.insert(items.end(), upd.begin(), upd.end());
+        items.insert(items.end(), start.begin(), start.end());
         if (!insts_ || insts_cap_ < (size_t)n) {
             insts_cap_ = (size_t)n * 2;
             insts_ = std::make_unique<Dev>(sizeof(BatchInst) * insts_cap_);
             mail_host_ = std::make_unique<Pinned>(sizeof(double) * 4 * insts_cap_ * kRing);
+        }
+        if (!norms_ || norms_cap_ < n) {
+            norms_cap_ = 2 * n;
+            norms_ = std::make_unique<Pinned>(sizeof(double) * (size_t)norms_cap_);
         }
         if (!items_ || items_cap_ < items.size()) {
             items_cap_ = items.size() * 2;
@@ -334,21 +342,38 @@ class Engine : public BatchRunner {
         }
         HUB_HIP(hipMemcpyAsync(insts_->p, desc.data(), sizeof(BatchInst) * (size_t)n, hipMemcpyHostToDevice, s_));
         HUB_HIP(hipMemcpyAsync(items_->p, items.data(), sizeof(BatchItem) * items.size(), hipMemcpyHostToDevice, s_));
+        // start vectors of the instances that joined
+        if (!start.empty())
+            launch_batch_start<T>(static_cast<BatchInst *>(insts_->p),
+                                  static_cast<const BatchItem *>(items_->p) + items.size() - start.size(),
+                                  (int)start.size(), static_cast<double *>(norms_->dev), s_);
         HUB_HIP(hipStreamSynchronize(s_));
-        n_items_ = (int)items.size();
+        for (int i = 0; i < n; i++) {
+            Slot<T> &sl = *slots_[(size_t)i];
+            if (!sl.fresh)
+                continue;
+            sl.fresh = false;
+            const double nrm2 = static_cast<const double *>(norms_->p)[i];
+            if (!(nrm2 > 0.0) || !std::isfinite(nrm2))
+                fail(HUBBARD_EINVAL, "start vector has zero or non-finite norm");
+        }
+        n_items_ = n_items;
+        n_upd_ = (int)upd.size();
         lds_ = lds;
     }
 
     hipStream_t s_;
+    bool keep_ = false;
     std::vector<std::unique_ptr<Slot<T>>> slots_;
     std::vector<Slot<T> *> table_;  // the instances of the current descriptor table, in slot order
     std::unique_ptr<Dev> insts_, items_;
     std::unique_ptr<Pinned> mail_host_;
-    std::unique_ptr<Pinned> norms_;  // squared start norms of joining instances (written by the device)
-    int norms_cap_ = 0, pending_fill_ = 0;
+    std::unique_ptr<Pinned> norms_;  // squared start norms by slot (written by the device)
+    int norms_cap_ = 0;
     hipEvent_t ev_[kRing];
     size_t insts_cap_ = 0, items_cap_ = 0, lds_ = 16;
-    int n_items_ = 0;
+    int n_items_ = 0, n_upd_ = 0;
+    bool pairs_ = true;
     int64_t launched_ = 0, read_ = 0;  // steps launched and read back since the last rebuild
     int pending_stopped_ = 0;         // instances of the table found finished
     bool dirty_ = true;
@@ -367,16 +392,16 @@ size_t batch_vector_bytes(const hubbard *h, int precision)
 {
     const size_t es = precision == HUBBARD_FP64 ? 8 : 4;
     const int64_t rpi = rows_per_item(h);
-    const int64_t items = (h->up.dim + rpi - 1) / rpi;
-    return 2 * es * (size_t)h->dim + 8 * sizeof(double) +
-           sizeof(double) * (size_t)(std::max<int64_t>(items, 2 * stream_blocks(h->dim) + 8) + items);
+    const int64_t items = (h->up.dim + rpi - 1) / rpi, upd = (h->dim + kUpdElems - 1) / kUpdElems;
+    return 2 * es * (size_t)(h->dim + 64) + 8 * sizeof(double) +
+           sizeof(double) * (size_t)(items + upd);
 }
 
 bool batchable(const hubbard *h, int precision)
 {
     const size_t es = precision == HUBBARD_FP64 ? 8 : 4;
     // the batched kernels take one amplitude t for every hop
-    return h->device >= 0 && h->tcls.empty() && (size_t)h->dn.dim * es <= 64 * 1024;
+    return h->device >= 0 && h->tcls.empty() && (size_t)h->dn.dim * es <= 64 * 1024 && h->dev.up_tile;
 }
 
 // The solves of one precision go to kBatchStreams engines on as many streams
@@ -422,7 +447,7 @@ void run_group(hubbard **hs, const hubbard_opts *opts, hubbard_result *res, cons
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return hs[a]->dim > hs[b]->dim; });
     std::vector<std::unique_ptr<Engine<T>>> eng;
     for (int k = 0; k < ne; k++)
-        eng.push_back(std::make_unique<Engine<T>>(ss.s[k]));
+        eng.push_back(std::make_unique<Engine<T>>(ss.s[k], true));
     for (size_t q = 0; q < order.size(); q++) {
         const int r = (int)(q % (size_t)(2 * ne));
         const int k = r < ne ? r : 2 * ne - 1 - r;

@@ -12,30 +12,33 @@ namespace hub {
 // read-only between rebuilds).  The step's scalars are not kept here: every
 // workgroup derives them from the recorded coefficients and partial sums.
 struct BatchState {
-    double S[8];     // S[4]: squared norm of the start vector (set up by the host path)
     double scale;    // running max_k |a_k| + b_k (breakdown test)
     double e_prev;   // Ritz value of the previous step
     double e_prev2;  // and of the step before
     int32_t j;       // steps whose coefficients are recorded
     int32_t stopped; // set when the stop test of a step fires
-    int32_t cur;     // unused (the vector roles follow the step's parity)
-    int32_t pad_;
 };
 
 // One instance as the batched kernels see it (plain data, device memory).
 struct BatchInst {
-    const uint32_t *states_up, *states_dn, *up_rows, *dn_cols;
-    const uint16_t *nnz_up, *nnz_dn;
+    const uint32_t *states_up, *states_dn;
+    const uint32_t *up_tile;  // w_up slots per row, those past its count repeating its last hop
+    const uint16_t *nnz_up;
+    const uint4 *dn_groups;   // [g][d] -> eight 16-bit entries (element index | sign << 15)
+    const uint8_t *dn_nq;     // groups per 64 columns
+    const uint4 *dn_pair;     // the same with 16-bit indices into {x, 0, -x} (null: rows too long for pairs)
     int64_t dim_up, dim_dn, dim;
-    int32_t w_up, w_dn;
+    int32_t w_up, gmax;       // gmax: groups per column
     double t, U;
     void *vec0, *vec1;  // the two Lanczos vectors, dense rows
+    const double *start;  // start vector (dim, J order), or null: from the seed
+    uint64_t seed;
     BatchState *st;
     double *hist;       // a_{k+1} at 2k, b_{k+2} at 2k + 1
     double *part;       // H.v partial sums (y.x), one per work item of this instance
-    double *part2;      // update partial sums (|q|^2), one per work item
+    double *part2;      // update partial sums (|q|^2), one per update item
     double tol;
-    int32_t nparts;
+    int32_t nparts, nparts2;
     int32_t slot;       // mailbox slot
     int32_t max_iter;
     int32_t j0;         // steps launched for this instance before the table was built
@@ -51,7 +54,8 @@ constexpr double kMailStopped = -2.0;
 constexpr double kMailBad = -3.0;
 constexpr double kMailNone = -4.0;
 
-// A work item: rows [r0, r0 + nrows) of instance `inst`, writing partial `part`.
+// A work item: rows (of the H.v) or elements (of the update) [r0, r0 + nrows) of
+// instance `inst`, writing partial `part`.
 struct BatchItem {
     int32_t inst;
     int32_t part;
@@ -61,13 +65,17 @@ struct BatchItem {
 
 // One Lanczos step j of every active instance in two launches: the H.v with
 // the three-term update (and, in extra workgroups, the Ritz value and stop
-// test of step j - 1), then the q - a_j f_j update with its norm.
+// test of step j - 1), then the q - a_j f_j update with its norm (n_upd items
+// after the n_items of the H.v).  pairs: every listed instance has dn_pair.
 template <typename T>
-void launch_batch_step(BatchInst *insts_dev, int n_inst, const BatchItem *items_dev, int n_items, size_t lds_bytes,
-                       double *mailbox_dev, int j, hipStream_t s);
+void launch_batch_step(BatchInst *insts_dev, int n_inst, const BatchItem *items_dev, int n_items, int n_upd,
+                       size_t lds_bytes, bool pairs, double *mailbox_dev, int j, hipStream_t s);
 
-// zeroes an instance's state and sets S = {1, 1, 0, 0} (f_1 has scale 1, b_1 = 0)
-void launch_batch_init_state(BatchState *st, hipStream_t s);
+// The start vectors and states of the instances of the given update items, in
+// two launches; norms (mapped host memory): their squared norms by slot.
+template <typename T>
+void launch_batch_start(BatchInst *insts_dev, const BatchItem *items_dev, int n_items, double *norms_dev,
+                        hipStream_t s);
 
 // Largest sector the batched kernels take: a row must fit in 64 KB of LDS.
 bool batchable(const hubbard *h, int precision);
@@ -80,8 +88,8 @@ class BatchRunner {
   public:
     virtual ~BatchRunner() = default;
     static std::unique_ptr<BatchRunner> make(int precision, hipStream_t s);
-    // allocates the instance's vectors and writes its start vector; res is
-    // written when the instance finishes
+    // allocates the instance's vectors (its start vector is written before the
+    // next step); res is written when the instance finishes
     virtual void add(hubbard *h, const hubbard_opts &o, hubbard_result *res) = 0;
     // launches one more Lanczos step of every active instance and returns the
     // results that finished in steps the host has read back (the host reads

@@ -221,7 +221,7 @@ static void free_device(hubbard *h)
     DeviceTables &d = h->dev;
     void *ptrs[] = {d.states_up, d.states_dn, d.up_rows, d.dn_cols, d.nnz_up, d.nnz_dn,
                     d.dn_groups64, d.dn_groups32, d.dn_nq, d.dn_groups16, d.dn_nq8, d.dn_pidx, d.dn_nidx, d.dn_pn, d.up_blk, d.up_nint, d.up_next,
-                    d.up_bstart, d.up_line, d.up_cnt, d.tcls, d.up_tile, d.dn_slots, d.dn_slot_amp, d.dn_slot_nq};
+                    d.up_bstart, d.up_line, d.up_cnt, d.tcls, d.up_tile, d.dn_slots, d.dn_slot_amp, d.dn_slot_nq, d.dn_pair16};
     for (void *p : ptrs)
         if (p)
             (void)hipFree(p);
@@ -372,10 +372,12 @@ static void upload_tile(hubbard *h, const std::vector<uint32_t> &rows, size_t &t
 {
     DeviceTables &d = h->dev;
     const int64_t du = h->up.dim, ddn = h->dn.dim;
-    // rows that fit in LDS, and sectors the form may take (see make_tile_plan)
-    if (ddn > kMaxTileRow || (h->dim * 4 > kTileMaxBytes && (int)h->tcls.size() <= kTwoPassClasses))
-        return;
     const int w = std::max(1, h->up.width), w8 = (w + 7) / 8 * 8;
+    // rows that fit in LDS, and sectors the form may take (see make_tile_plan), or
+    // that the batched engine may
+    const bool batch = h->tcls.empty() && ddn * 4 <= 64 * 1024 && du * w8 * 4 <= ((int64_t)16 << 20);
+    if (ddn > kMaxTileRow || (!batch && h->dim * 4 > kTileMaxBytes && (int)h->tcls.size() <= kTwoPassClasses))
+        return;
     std::vector<uint32_t> up((size_t)du * (size_t)w8, 0u);
     for (int64_t r = 0; r < du; r++) {
         const int nnz = h->up.row_nnz[(size_t)r];
@@ -515,6 +517,12 @@ static void upload_tables(hubbard *h)
             slot = (uint8_t)std::max<int>(slot, (nnz + 7) / 8);
         }
         d.dn_groups16 = upload<uint16_t>(g.data(), g.size() * 2, total);
+        if (ddn <= 2048) {
+            for (auto &e : g)
+                if (e & 0x8000u)
+                    e = (uint16_t)((e & 0x7fffu) + ddn + 1);
+            d.dn_pair16 = upload<uint16_t>(g.data(), g.size() * 2, total);
+        }
         d.dn_nq8 = upload<uint8_t>(nq8.data(), nq8.size(), total);
         if (ddn <= kRow64Max && !tile_only) {
             // the FP64 row pass: per column the + hops in groups of eight and

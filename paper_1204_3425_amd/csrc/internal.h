@@ -67,6 +67,10 @@ struct DeviceTables {
     // groups of eight 16-bit entries (element index | sign<<15)
     uint16_t *dn_groups16 = nullptr;
     uint8_t *dn_nq8 = nullptr;     // groups of eight needed by the 64 columns of a wave
+    // the same groups with the sign in the index (rows of at most 2,048 elements,
+    // the batched engine's): element e of x, or ddn + 1 + e where the row's
+    // negative follows it and its zero slot
+    uint16_t *dn_pair16 = nullptr;
     // FP64 row pass (one amplitude, rows of at most kRow64Max elements): per
     // column the hops of sign + in groups of eight 16-bit element indices and
     // those of sign - in groups of four, each in ascending column order
