@@ -707,10 +707,6 @@ struct Deflation {
 // whether Lanczos steps take the one-launch form where its plan allows it
 static bool tile_steps(const HvArgs &a, int elem_bytes)
 {
-#ifdef HUB_DEV
-    if (getenv("NO_TILE")) return false;
-    if (getenv("ALL_TILE")) return true;
-#endif
     return a.dim_up * a.dim_dn * elem_bytes <= kTileStepBytes || (a.tcls && a.ncls > kTwoPassClasses);
 }
 
