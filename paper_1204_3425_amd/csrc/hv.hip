@@ -27,10 +27,8 @@
 // hops that stay inside the block; the others read global memory.  Eight
 // lanes cover one row segment with 16-byte accesses, so a wave updates eight
 // rows.  hv_lines_kernel takes a row's entries as one 128-byte line (rows of at
-// most 32 hops); hv_blocks_kernel handles longer rows.  Rows that start on 16
-// but not on 128 bytes (a caller's dense vector) take the same passes with each
-// XCD on a contiguous range of slabs; hv_slabs_kernel serves rows not on 16
-// bytes.  The running output is read and written with non-temporal accesses.
+// most 32 hops); hv_blocks_kernel handles longer rows.  hv_slabs_kernel serves rows
+// not on 16 bytes.  The running output is read and written with non-temporal accesses.
 //
 // Epilogues (both passes together):
 //   HV_STORE    y = H x
@@ -84,6 +82,23 @@ __device__ inline float flip_sign(float v, uint32_t sg) { return __int_as_float(
 __device__ inline double flip_sign(double v, uint32_t sg)
 {
     return __longlong_as_double(__double_as_longlong(v) ^ ((long long)sg << 32));
+}
+
+// The row passes stream the vectors (x read once, the result written once) past
+// the L2, which then keeps the entry tables that every row reads again: 4x4 FP64,
+// 8 + 8, store 1303 -> 1230 us, fused step 1602 -> 1505 us.  The fused step's y
+// is read twice, staged and at its column, and goes through the L2.  (FP32 pairs of
+// rows gain nothing and go through it: store 600 -> 585 us but 12 us more in the
+// up-spin pass that reads the result next, fused step 685 -> 695 us.)
+template <typename V>
+__device__ inline V stream_load(const V *p)
+{
+    return __builtin_nontemporal_load(p);
+}
+template <typename V>
+__device__ inline void stream_store(V *p, V v)
+{
+    __builtin_nontemporal_store(v, p);
 }
 
 struct RowArgs {
@@ -187,7 +202,7 @@ __global__ __launch_bounds__(1024) void hv_rows_kernel(RowArgs p, const T *__res
                 for (int u = 0; u < CH; u++) {
                     const int d = d0 + u * nth + (int)threadIdx.x;
                     const bool ok = q < nr && d < ddn32;
-                    v[q][u] = ok ? x[(r0 + q) * ldx + d] : (T)0;
+                    v[q][u] = ok ? stream_load(x + (r0 + q) * ldx + d) : (T)0;
                     if (FUSED)
                         w[q][u] = ok ? y[(r0 + q) * ldy + d] : (T)0;
                     pg[q][u] = 0.0;
@@ -209,7 +224,7 @@ __global__ __launch_bounds__(1024) void hv_rows_kernel(RowArgs p, const T *__res
                             val = val - c_s * w[q][u];
                             if (MODE == HV_FUSED_DEFL)
                                 val = (T)((double)val - pg[q][u]);
-                            const_cast<T *>(x)[(r0 + q) * ldx + d] = val;
+                            stream_store(const_cast<T *>(x) + (r0 + q) * ldx + d, val);
                         }
                         xs[q * slot + d] = val;
                         if (p.xc)
@@ -342,13 +357,13 @@ __global__ __launch_bounds__(1024) void hv_rows_kernel(RowArgs p, const T *__res
                             T *yp = y + (r0 + q) * ldy + dd;
                             const T yv = PF ? yr[q] : (YR ? *yp : (T)0);
                             if (MODE == HV_STORE)
-                                *yp = hx;
+                                stream_store(yp, hx);
                             else if (FUSED && p.yo)
-                                static_cast<T *>(p.yo)[(r0 + q) * p.ldyo + dd] = a_s * hx + b_s * yv;
+                                stream_store(static_cast<T *>(p.yo) + (r0 + q) * p.ldyo + dd, a_s * hx + b_s * yv);
                             else if (YR)
-                                *yp = a_s * hx + b_s * yv;
+                                stream_store(yp, a_s * hx + b_s * yv);
                             else
-                                *yp = hx - a_s * xv;
+                                stream_store(yp, hx - a_s * xv);
                         }
                     }
                 }
@@ -440,7 +455,8 @@ __global__ __launch_bounds__(kRowThreads) void hv_rows64_kernel(Row64Args p, con
             gd[l] = p.defl.g[l];
     const int ddn = p.dim_dn, tid = (int)threadIdx.x, lane = tid & 63;
     // staging units: 16-byte pairs (rows 16-byte aligned) or single elements
-    typedef typename std::conditional<VEC, double2, double>::type SU;
+    typedef __attribute__((ext_vector_type(2))) double vec2;
+    typedef typename std::conditional<VEC, vec2, double>::type SU;
     const int nu = VEC ? ddn >> 1 : ddn;
     const bool tail = VEC && (ddn & 1) && tid == kRowThreads - 1;  // the odd last element of a VEC row
     SU v[CH], w[CH];
@@ -452,7 +468,7 @@ __global__ __launch_bounds__(kRowThreads) void hv_rows64_kernel(Row64Args p, con
         for (int u = 0; u < CH; u++) {
             const int i = u * kRowThreads + tid;
             if (i < nu) {
-                v[u] = src[i];
+                v[u] = stream_load(src + i);
                 if (FUSED)
                     w[u] = ysrc[i];
             }
@@ -505,7 +521,7 @@ __global__ __launch_bounds__(kRowThreads) void hv_rows64_kernel(Row64Args p, con
                     val = val - cshift * w[u];
                     if (MODE == HV_FUSED_DEFL)
                         val = val - pg[u];
-                    xw[i] = val;
+                    stream_store(xw + i, val);
                 } else if (p.xc) {
                     xc[i] = val;
                 }
@@ -631,13 +647,13 @@ __global__ __launch_bounds__(kRowThreads) void hv_rows64_kernel(Row64Args p, con
                     const double hx = fma(mt, h0 + h1, U * (double)__popc(su & sd) * xd);
                     double *yp = y + r * ldy + dd;
                     if (MODE == HV_STORE)
-                        *yp = hx;
+                        stream_store(yp, hx);
                     else if (FUSED && p.yo)
-                        p.yo[r * p.ldyo + dd] = alpha * hx + beta * yv;
+                        stream_store(p.yo + r * p.ldyo + dd, alpha * hx + beta * yv);
                     else if (YR)
-                        *yp = alpha * hx + beta * yv;
+                        stream_store(yp, alpha * hx + beta * yv);
                     else
-                        *yp = hx - alpha * xd;
+                        stream_store(yp, hx - alpha * xd);
                 }
             }
             c = cn;
@@ -1040,13 +1056,13 @@ struct BlockArgs {
     const int32_t *__restrict__ bstart;
     int64_t dim_up, dim_dn;
     int w_up, nblocks, nslab;
-    int contig;  // rows not on 128 bytes: each XCD takes a contiguous range of slabs
+    int contig;  // as in LineArgs
     double t;
     double amp[4];
 };
 
 // Blocked slab pass.  Workgroup b works on slab s and row block k, with
-// xcd = b mod 8, s = (b / 8 / nblocks) * 8 + xcd, k = (b / 8) mod nblocks: the
+// xcd = b mod 8, s the (b / 8 / nblocks)-th of that XCD's slabs, k = (b / 8) mod nblocks: the
 // dispatcher starts workgroups in index order, so each XCD moves through its
 // slabs about one at a time and the rows that other blocks' hops re-read are
 // still in that XCD's L2.  A slab is 128 bytes of every row (one cache line).
@@ -1086,13 +1102,12 @@ __global__ __launch_bounds__(1024) void hv_blocks_kernel(BlockArgs p, const T *_
     const int nwave = blockDim.x >> 6;
     const int xcd = blockIdx.x & 7;
     const int local = blockIdx.x >> 3;
-    // slab-major per XCD: XCD k takes slabs k, k + 8, ... (rows on 128 bytes),
-    // or the k-th contiguous range of slabs, so that the cache lines two
-    // neighbouring slabs share stay in one L2 (rows not on 128 bytes)
-    const int s = p.contig ? xcd * ((p.nslab + 7) / 8) + local / p.nblocks : (local / p.nblocks) * 8 + xcd;
+    // slab-major per XCD: the k-th contiguous range of slabs, or slabs k, k + 8, ...
+    const int s = p.contig ? p.nslab * xcd / 8 + local / p.nblocks : (local / p.nblocks) * 8 + xcd;
+    const int s_end = p.contig ? p.nslab * (xcd + 1) / 8 : p.nslab;
     const int blk = local % p.nblocks;
     double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
-    if (s < p.nslab) {
+    if (s < s_end) {
         const int64_t b0 = p.bstart[blk];
         const int bs = p.bstart[blk + 1] - (int)b0;
         const int64_t d0 = (int64_t)s * SL;
@@ -1239,12 +1254,13 @@ struct LineArgs {
     const int32_t *__restrict__ bstart;
     int64_t dim_up, dim_dn;
     int nblocks, nslab;
-    int contig;  // rows not on 128 bytes: each XCD takes a contiguous range of slabs
     double t;
     double amp[4];
     void *yo;      // where the result goes (y itself, or rows at stride ldyo)
     int64_t ldyo;
     int yoal;      // alignment of the result rows: 16 or 8 bytes (vector stores), else 0
+    int through;   // FP64 result rows not on 64 bytes: stored through the L2
+    int contig;    // each XCD takes a contiguous range of slabs, not every eighth slab
     HvDefl defl;   // HV_FUSED_DEFL: the lower vectors psi_l . y and psi_l . x are summed against
     int64_t pair;  // 0, or the element offset of a second vector pair (x, y, result): workgroups
                    // from gpair on take it, and the partial sums cover both
@@ -1313,13 +1329,13 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
     }
     const int xcd = bid & 7;
     const int local = bid >> 3;
-    // slab-major per XCD: XCD k takes slabs k, k + 8, ... (rows on 128 bytes),
-    // or the k-th contiguous range of slabs, so that the cache lines two
-    // neighbouring slabs share stay in one L2 (rows not on 128 bytes)
-    const int s = p.contig ? xcd * ((p.nslab + 7) / 8) + local / p.nblocks : (local / p.nblocks) * 8 + xcd;
+    // slab-major per XCD: XCD k takes the k-th contiguous range of slabs, or slabs
+    // k, k + 8, ...
+    const int s = p.contig ? p.nslab * xcd / 8 + local / p.nblocks : (local / p.nblocks) * 8 + xcd;
+    const int s_end = p.contig ? p.nslab * (xcd + 1) / 8 : p.nslab;
     const int blk = local % p.nblocks;
     double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
-    if (s < p.nslab) {
+    if (s < s_end) {
         const int64_t b0 = p.bstart[blk];
         const int bs = p.bstart[blk + 1] - (int)b0;
         const int64_t d0 = (int64_t)s * SL;
@@ -1349,8 +1365,9 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
         // FULL: the slab lies inside the rows, so every lane's vector is whole
         // (rows start on 16 bytes) and no access needs a bounds test; the slab
         // holding the rows' ends tests each lane and never touches padding
-        auto run = [&](auto full_tag) {
-            constexpr bool FULL = decltype(full_tag)::value;
+        // THROUGH: result segments are stored through the L2 (see below)
+        auto run = [&](auto full_tag, auto through_tag) {
+            constexpr bool FULL = decltype(full_tag)::value, THROUGH = decltype(through_tag)::value;
             // running output of row r (zero past the last column)
             auto load_prev = [&](int64_t r) -> vec {
                 const T *yp = y + r * ldy + d;
@@ -1522,7 +1539,16 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
                     if (MODE != HV_RESIDUAL) {
                         bool done = false;
                         if ((FULL || whole) && p.yoal == 16) {
-                            __builtin_nontemporal_store(out, reinterpret_cast<vec *>(yp));
+                            // a segment not on 64 bytes shares its first and last
+                            // 64 with the neighbouring slabs' segments: stored through
+                            // the L2, most of them leave it whole (4x4 FP64, dense
+                            // rows: 1660 us past the L2, 1570 through it; on 64
+                            // bytes 1275 and 1283, on 128 1395 and 1415; FP32 608
+                            // and 632)
+                            if constexpr (THROUGH)
+                                *reinterpret_cast<vec *>(yp) = out;
+                            else
+                                __builtin_nontemporal_store(out, reinterpret_cast<vec *>(yp));
                             done = true;
                         }
                         if constexpr (EPL == 4) {
@@ -1550,9 +1576,10 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
             }
         };
         if (d0 + SL <= p.dim_dn)
-            run(std::true_type{});
+            (EPL == 2 && p.through) ? run(std::true_type{}, std::bool_constant<EPL == 2>{})
+                                    : run(std::true_type{}, std::false_type{});
         else
-            run(std::false_type{});
+            run(std::false_type{}, std::false_type{});
     }
     if (MODE != HV_STORE) {
         // all partial sums of the workgroup in one round: wave sums, one
@@ -1953,7 +1980,12 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
     // the blocked passes load 16 bytes per lane: rows must start on 16 bytes
     // (on 128 bytes each row segment is one cache line)
     const bool on16 = ldx % v16 == 0 && ldyr % v16 == 0 && (uintptr_t)x % 16 == 0 && (uintptr_t)yr % 16 == 0;
-    const int contig = (ldx % slw != 0 || ldyr % slw != 0 || (mode != HV_RESIDUAL && ldyo % slw != 0)) ? 1 : 0;
+    // which slabs an XCD takes: rows not on 128 bytes want neighbouring slabs, which
+    // share lines, in one L2.  FP64 rows on 128 bytes do too: with slabs k, k + 8, ..
+    // the eight XCDs walk the rows side by side and meet on the same memory channels
+    // (4x4, 8 + 8, 7 + 7 and 6 + 6, fused step: 1640, 1251 and 1035 us against 1395,
+    // 1212 and 906).  FP32 rows on 128 bytes do not (605 us against 617, 730 against 737).
+    const bool contig = sizeof(T) == 8 || ldx % slw != 0 || ldyr % slw != 0 || (mode != HV_RESIDUAL && ldyo % slw != 0);
     if (pl.blk_grid > 0 && on16) {
         BlockArgs ba;
         ba.ent = a.up_blk;
@@ -1986,6 +2018,7 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
             la.dim_dn = a.dim_dn;
             la.nblocks = a.up_nblocks;
             la.nslab = pl.blk_nslab;
+            la.through = sizeof(T) == 8 && (ldyo * (int64_t)sizeof(T) % 64 != 0 || (uintptr_t)yo % 64 != 0);
             la.contig = contig;
             la.t = a.t;
             la.yo = yo;
