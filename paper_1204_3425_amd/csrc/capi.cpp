@@ -221,7 +221,8 @@ static void free_device(hubbard *h)
     DeviceTables &d = h->dev;
     void *ptrs[] = {d.states_up, d.states_dn, d.up_rows, d.dn_cols, d.nnz_up, d.nnz_dn,
                     d.dn_groups64, d.dn_groups32, d.dn_nq, d.dn_groups16, d.dn_nq8, d.dn_pidx, d.dn_nidx, d.dn_pn, d.up_blk, d.up_nint, d.up_next,
-                    d.up_bstart, d.up_line, d.up_cnt, d.tcls, d.up_tile, d.dn_slots, d.dn_slot_amp, d.dn_slot_nq, d.dn_pair16};
+                    d.up_bstart, d.up_line, d.up_cnt, d.tcls, d.up_tile, d.dn_slots, d.dn_slot_amp, d.dn_slot_nq, d.dn_pair16,
+                    d.dn_cls, d.dn_cls_n, d.up_cls_line, d.up_cls_cnt};
     for (void *p : ptrs)
         if (p)
             (void)hipFree(p);
@@ -348,6 +349,54 @@ static void upload_blocked_up(hubbard *h, size_t &total)
         d.up_cnt = upload<uint32_t>(cnt.data(), cnt.size() * 4, total);
         d.up_line_w = W;
         d.up_line_ipad = ipad ? 1 : 0;
+    }
+    if (up.width <= 64 && h->tcls.size() == 2) {
+        // a line of 32 slots per class: each class's internal hops from the
+        // front (padded with the zero row to the group's largest count), its
+        // external ones from the back
+        std::vector<uint8_t> n((size_t)du * 4, 0);  // per row and class: internal, external
+        for (int64_t r = 0; r < du; r++)
+            for (int k = 0; k < nint[(size_t)r] + next[(size_t)r]; k++)
+                n[(size_t)r * 4 + ((ent[(size_t)r * (size_t)w + (size_t)k] >> 24) & 1u) * 2 + (k >= nint[(size_t)r])]++;
+        std::vector<uint32_t> line((size_t)du * 64, 0u), cnt((size_t)du * 2, 0u);
+        bool fits = true;
+        for (int b = 0; b < nb && fits; b++)
+            for (int32_t g0 = bstart[(size_t)b]; g0 < bstart[(size_t)b + 1]; g0 += 8) {
+                const int32_t g1 = std::min(g0 + 8, bstart[(size_t)b + 1]);
+                for (int c = 0; c < 2; c++) {
+                    uint32_t mi = 0, me = 0;
+                    for (int32_t r = g0; r < g1; r++) {
+                        mi = std::max<uint32_t>(mi, n[(size_t)r * 4 + (size_t)c * 2]);
+                        me = std::max<uint32_t>(me, n[(size_t)r * 4 + (size_t)c * 2 + 1]);
+                    }
+                    for (int32_t r = g0; r < g1; r++) {
+                        const uint32_t ci = n[(size_t)r * 4 + (size_t)c * 2], ce = n[(size_t)r * 4 + (size_t)c * 2 + 1];
+                        cnt[(size_t)r * 2 + (size_t)c] = ci | ce << 8 | mi << 16 | me << 24;
+                        if (mi + ce > 32) {
+                            fits = false;
+                            continue;
+                        }
+                        uint32_t *l = line.data() + (size_t)r * 64 + (size_t)c * 32;
+                        uint32_t oi = 0, oe = 0;
+                        for (int k = 0; k < nint[(size_t)r] + next[(size_t)r]; k++) {
+                            const uint32_t e = ent[(size_t)r * (size_t)w + (size_t)k];
+                            if (((e >> 24) & 1u) != (uint32_t)c)
+                                continue;
+                            const uint32_t v = e & 0x80ffffffu;
+                            if (k < nint[(size_t)r])
+                                l[oi++] = v;
+                            else
+                                l[31 - oe++] = v;
+                        }
+                        while (oi < mi)
+                            l[oi++] = (uint32_t)(bstart[(size_t)b + 1] - bstart[(size_t)b]);
+                    }
+                }
+            }
+        if (fits) {
+            d.up_cls_line = upload<uint32_t>(line.data(), line.size() * 4, total);
+            d.up_cls_cnt = upload<uint32_t>(cnt.data(), cnt.size() * 4, total);
+        }
     }
     if (up.width > 64) {
         d.up_blk = upload<uint32_t>(ent.data(), ent.size() * 4, total);
@@ -481,8 +530,48 @@ static void upload_tables(hubbard *h)
         uint8_t &slot = nq[(size_t)(r / 64)];
         slot = (uint8_t)std::max<int>(slot, need);
     }
+    if (ddn < 32768 && h->tcls.size() == 2 && !tile_only) {
+        // groups by class (see DeviceTables), at most kClsGroups of each
+        std::vector<uint8_t> n((size_t)((ddn + 63) / 64) * 2, 0);
+        int gm[2] = {1, 1};
+        for (int64_t r = 0; r < ddn; r++) {
+            int k2[2] = {0, 0};
+            for (int k = 0; k < h->dn.row_nnz[(size_t)r]; k++)
+                k2[dn_cls((size_t)k * (size_t)ddn + (size_t)r)]++;
+            for (int c = 0; c < 2; c++) {
+                const int g = (k2[c] + 7) / 8;
+                gm[c] = std::max(gm[c], g);
+                uint8_t &slot = n[(size_t)(r / 64) * 2 + (size_t)c];
+                slot = (uint8_t)std::max<int>(slot, std::min(g, 255));
+            }
+        }
+        if (gm[0] <= kClsGroups && gm[1] <= kClsGroups) {
+            auto put = [&](std::vector<uint16_t> &g, size_t at, uint32_t idx, bool neg) {
+                g[at] = (uint16_t)(at & 1 ? idx | (neg ? 0x8000u : 0u) : idx << 1 | (neg ? 1u : 0u));
+            };
+            std::vector<uint16_t> g((size_t)(gm[0] + gm[1]) * (size_t)ddn * 8);
+            for (size_t i = 0; i < g.size(); i++)
+                put(g, i, (uint32_t)ddn, false);
+            for (int64_t r = 0; r < ddn; r++) {
+                int k2[2] = {0, 0};
+                for (int k = 0; k < h->dn.row_nnz[(size_t)r]; k++) {
+                    const size_t src = (size_t)k * (size_t)ddn + (size_t)r;
+                    const uint32_t c = dn_cls(src);
+                    const int slot = (c ? gm[0] * 8 : 0) + k2[c]++;
+                    put(g, ((size_t)(slot / 8) * (size_t)ddn + (size_t)r) * 8 + (size_t)(slot % 8),
+                        (uint32_t)h->dn.col[src], h->dn.sgn[src] < 0);
+                }
+            }
+            d.dn_cls = upload<uint16_t>(g.data(), g.size() * 2, total);
+            d.dn_cls_n = upload<uint8_t>(n.data(), n.size(), total);
+            d.dn_cls_g1 = gm[0];
+            d.dn_cls_ng = std::max(gm[0], gm[1]);
+        }
+    }
+    // the row pass by class takes every row whose FP64 pair fits the LDS
+    const bool by_class = d.dn_cls && (ddn + 1) * 16 <= 160 * 1024;
     for (int es : {8, 4}) {
-        if (tile_only)
+        if (tile_only || by_class)
             break;
         std::vector<uint32_t> g((size_t)std::max(ng, 1) * (size_t)ddn * 4, (uint32_t)(ddn * es));
         for (int64_t r = 0; r < ddn; r++)
@@ -604,6 +693,12 @@ static HvArgs hv_args(const hubbard *h)
     a.up_nblocks = h->dev.up_nblocks;
     a.up_max_block = h->dev.up_max_block;
     a.up_line = h->dev.up_line;
+    a.up_cls_line = h->dev.up_cls_line;
+    a.up_cls_cnt = h->dev.up_cls_cnt;
+    a.dn_cls = reinterpret_cast<const uint4 *>(h->dev.dn_cls);
+    a.dn_cls_n = h->dev.dn_cls_n;
+    a.dn_cls_g1 = h->dev.dn_cls_g1;
+    a.dn_cls_ng = h->dev.dn_cls_ng;
     a.up_line_w = h->dev.up_line_w;
     a.up_line_ipad = h->dev.up_line_ipad;
     a.up_cnt = h->dev.up_cnt;

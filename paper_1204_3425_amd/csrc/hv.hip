@@ -7,7 +7,8 @@
 // its own:
 //
 // Row pass (I (x) H_dn and the interaction).  hv_rows64_kernel for FP64 rows that
-// fill the LDS (one amplitude), hv_rows_kernel otherwise.  A workgroup stages whole rows of
+// fill the LDS (one amplitude), hv_rows_cls_kernel for two classes,
+// hv_rows_kernel otherwise.  A workgroup stages whole rows of
 // X in LDS (RPB rows at once, each followed by a zero slot; every thread loads
 // its chunk before writing any of it) and every lane produces the outputs of
 // its columns d by gathering X[r, e_k(d)] from LDS.  The down table is stored
@@ -160,6 +161,14 @@ __device__ inline T signed_factor(const T (&a)[4], uint32_t e)
 // the block: its last row) so that the wait counters stay exact.
 // s_waitcnt vmcnt(0) with the other counters left alone (gfx9 encoding)
 constexpr int kVmcnt0 = 0x0f70;
+
+// base + byte: a uniform base and a 32-bit offset per lane
+template <typename V>
+__device__ inline V *at_byte(V *base, uint32_t byte)
+{
+    typedef typename std::conditional<std::is_const<V>::value, const unsigned char, unsigned char>::type B;
+    return reinterpret_cast<V *>(reinterpret_cast<B *>(base) + byte);
+}
 
 template <typename T, int RPB, int MODE, bool G16, bool GT, bool PF>
 __global__ __launch_bounds__(1024) void hv_rows_kernel(RowArgs p, const T *__restrict__ x, int64_t ldx,
@@ -959,6 +968,196 @@ struct SlabArgs {
     double amp[4];
 };
 
+// Row pass of handles with two amplitude classes (the t-t' lattice), on pairs of
+// rows.
+//
+// A pair sits in LDS interleaved, element e of both rows as one V2, so a table
+// entry costs one gather for both.  A column's groups of eight entries hold hops
+// of one class each, class 0 first: the hops of a class are summed with their
+// signs alone (a factor of +-1 built by one instruction, one FMA per row) and the
+// class amplitudes multiply the two sums once.  Entries are 16 bits, two to a
+// word: the lower one has its sign in bit 0 and its index above it, the upper one
+// its sign in bit 31.  The next pair's first units are loaded into registers while
+// the current one is gathered.  4x4 t-t', 6 + 6 (8,008
+// columns), store: 880 us with the class in each entry and the rows apart, 577 so,
+// with four units ahead (six: 596) and 64 bytes of gathers in flight a lane (128:
+// 585); FP64 pairs of longer rows do not fit the LDS.
+struct RowClsArgs {
+    const uint4 *__restrict__ groups;  // [g][d] -> eight 16-bit entries
+    const uint8_t *__restrict__ cn;    // per 64 columns: groups of class 0, of class 1
+    const uint32_t *__restrict__ states_up;
+    const uint32_t *__restrict__ states_dn;
+    int64_t dim_up;
+    int dim_dn, g1;  // g1: first group slot of class 1
+    double amp[2], U;
+    void *xc;  // null, or rows at stride ldc that receive a copy of each staged row
+    int64_t ldc;
+    void *yo;  // fused mode: null (y is overwritten), or rows at stride ldyo for the result
+    int64_t ldyo;
+};
+
+template <typename T, int MODE, int NG>
+__global__ __launch_bounds__(kRowThreads) void hv_rows_cls_kernel(RowClsArgs p, const T *__restrict__ x, int64_t ldx,
+                                                                  T *__restrict__ y, int64_t ldy, double alpha,
+                                                                  double beta, const double *__restrict__ coef)
+{
+    typedef __attribute__((ext_vector_type(2))) T V2;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    V2 *xs = reinterpret_cast<V2 *>(smem_raw);
+    constexpr bool FUSED = MODE == HV_FUSED, YR = MODE == HV_LANCZOS || FUSED;
+    double cshift = 0.0;
+    if (MODE == HV_LANCZOS) {
+        alpha = coef[0];
+        beta = coef[1];
+    } else if (FUSED) {
+        alpha = coef[1];
+        beta = coef[2];
+        cshift = coef[3];
+    }
+    const T a_s = (T)alpha, b_s = (T)beta, c_s = (T)cshift, U = (T)p.U, am0 = (T)p.amp[0], am1 = (T)p.amp[1];
+    const int ddn = p.dim_dn, tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int64_t npair = (p.dim_up + 1) / 2;
+    constexpr int PFU = 4 * (8 / (int)sizeof(T));  // units (elements of both rows) a thread loads ahead
+    const T none[4] = {};
+    T v0[PFU], v1[PFU];
+    auto load_pair = [&](int64_t r, int64_t r1, int i0) {
+        const T *s0 = x + r * ldx, *s1 = x + r1 * ldx;
+#pragma unroll
+        for (int u = 0; u < PFU; u++) {
+            const uint32_t i = (uint32_t)min(i0 + u * kRowThreads + tid, ddn - 1) * (uint32_t)sizeof(T);
+            v0[u] = stream_load(at_byte(s0, i));
+            v1[u] = stream_load(at_byte(s1, i));
+        }
+    };
+    auto store_pair = [&](int64_t r, int64_t r1, bool two, int i0) {
+        T w0[PFU], w1[PFU];
+        if (FUSED) {
+            const T *s0 = y + r * ldy, *s1 = y + r1 * ldy;
+#pragma unroll
+            for (int u = 0; u < PFU; u++) {
+                const uint32_t i = (uint32_t)min(i0 + u * kRowThreads + tid, ddn - 1) * (uint32_t)sizeof(T);
+                w0[u] = *at_byte(s0, i);
+                w1[u] = *at_byte(s1, i);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PFU; u++) {
+            const int i = i0 + u * kRowThreads + tid;
+            if (i < ddn) {
+                T a = v0[u], b = v1[u];
+                if (FUSED) {
+                    // the q - a_j f_j update of the previous step, formed here and kept
+                    a = a - c_s * w0[u];
+                    b = b - c_s * w1[u];
+                    stream_store(const_cast<T *>(x) + r * ldx + i, a);
+                    if (two)
+                        stream_store(const_cast<T *>(x) + r1 * ldx + i, b);
+                } else if (p.xc) {
+                    static_cast<T *>(p.xc)[r * p.ldc + i] = a;
+                    if (two)
+                        static_cast<T *>(p.xc)[r1 * p.ldc + i] = b;
+                }
+                xs[i] = V2{a, b};
+            }
+        }
+    };
+    // group counts of a wave's column chunks, one per lane (as in hv_rows64_kernel)
+    const int nchunk = (ddn + 63) >> 6;
+    const uint32_t cnt_lane = *reinterpret_cast<const uint16_t *>(p.cn + 2 * min(wv + 16 * lane, nchunk - 1));
+    int64_t pr = blockIdx.x;
+    if (pr < npair)
+        load_pair(2 * pr, min(2 * pr + 1, p.dim_up - 1), 0);
+    for (; pr < npair; pr += gridDim.x) {
+        const int64_t r = 2 * pr, r1 = min(r + 1, p.dim_up - 1);  // r1 = r: computed, not stored
+        const bool two = r + 1 < p.dim_up;
+        store_pair(r, r1, two, 0);
+        for (int i0 = PFU * kRowThreads; i0 < ddn; i0 += PFU * kRowThreads) {
+            load_pair(r, r1, i0);
+            store_pair(r, r1, two, i0);
+        }
+        if (tid == 0)
+            xs[ddn] = V2{(T)0, (T)0};
+        __syncthreads();
+        const uint32_t su0 = p.states_up[r], su1 = p.states_up[r1];
+        if (pr + gridDim.x < npair) {
+            const int64_t rn = 2 * (pr + gridDim.x);
+            load_pair(rn, min(rn + 1, p.dim_up - 1), 0);
+        }
+        // Class 0's groups are loaded while the column before gathers its class 1,
+        // class 1's while this one gathers its class 0.  Every slot is loaded, past
+        // the counts group 0 again (unused), so that the wait counters stay exact.
+        auto count = [&](int k) -> uint32_t { return (uint32_t)__builtin_amdgcn_readlane((int)cnt_lane, k); };
+        auto load_groups = [&](uint4 (&e)[NG], int first, int n, int dd) {
+#pragma unroll
+            for (int g = 0; g < NG; g++)
+                e[g] = *at_byte(p.groups + (size_t)(first + (g < n ? g : 0)) * (size_t)ddn, (uint32_t)dd * 16u);
+        };
+        auto gather = [&](const uint4 (&e)[NG], int n, V2 &h) {
+#pragma unroll
+            for (int g = 0; g < NG; g++) {
+                if (g < n) {
+                    const uint32_t ev[4] = {e[g].x, e[g].y, e[g].z, e[g].w};
+                    constexpr int B = sizeof(T) == 8 ? 4 : 3;  // log2 of a staged pair's bytes
+                    // gathers in flight: 64 bytes a lane
+                    constexpr int F = 32 / (int)sizeof(T);
+#pragma unroll
+                    for (int u0 = 0; u0 < 8; u0 += F) {
+                        V2 v[F];
+#pragma unroll
+                        for (int u = 0; u < F; u++) {
+                            const uint32_t w = ev[(u0 + u) >> 1];
+                            const uint32_t off = (u & 1) ? (w >> (16 - B)) & (0x7fffu << B) : (w << (B - 1)) & (0x7fffu << B);
+                            v[u] = *reinterpret_cast<const V2 *>(smem_raw + off);
+                        }
+#pragma unroll
+                        for (int u = 0; u < F; u++) {
+                            const uint32_t w = ev[(u0 + u) >> 1];
+                            const T f = signed_factor<T, false>(none, (u & 1) ? w : w << 31);
+                            h.x = fma(f, v[u].x, h.x);
+                            h.y = fma(f, v[u].y, h.y);
+                        }
+                    }
+                }
+            }
+        };
+        uint4 e0[NG], e1[NG];
+        uint32_t c = count(0);
+        load_groups(e0, 0, (int)(c & 0xffu), min(tid, ddn - 1));
+        uint32_t sd = p.states_dn[min(tid, ddn - 1)];
+        int k = 0;
+        for (int d0 = 0; d0 + (wv << 6) < ddn; d0 += kRowThreads, k++) {
+            const int d = d0 + tid, dd = min(d, ddn - 1), dn = min(d + kRowThreads, ddn - 1);
+            const int n0 = (int)(c & 0xffu), n1 = (int)(c >> 8);
+            load_groups(e1, p.g1, n1, dd);
+            T y0 = (T)0, y1 = (T)0;
+            if (YR) {
+                y0 = *at_byte(y + r * ldy, (uint32_t)dd * (uint32_t)sizeof(T));
+                y1 = *at_byte(y + r1 * ldy, (uint32_t)dd * (uint32_t)sizeof(T));
+            }
+            V2 h[2] = {V2{(T)0, (T)0}, V2{(T)0, (T)0}};
+            gather(e0, n0, h[0]);
+            c = count(k + 1);
+            load_groups(e0, 0, (int)(c & 0xffu), dn);
+            const uint32_t sdn = p.states_dn[dn];
+            gather(e1, n1, h[1]);
+            if (d < ddn) {
+                const V2 xd = xs[d];
+                const T s0 = am0 * h[0].x + am1 * h[1].x, s1 = am0 * h[0].y + am1 * h[1].y;
+                const T hx0 = fma(U * (T)__popc(su0 & sd), xd.x, -s0), hx1 = fma(U * (T)__popc(su1 & sd), xd.y, -s1);
+                const T o0 = MODE == HV_STORE ? hx0 : YR ? a_s * hx0 + b_s * y0 : hx0 - a_s * xd.x;
+                const T o1 = MODE == HV_STORE ? hx1 : YR ? a_s * hx1 + b_s * y1 : hx1 - a_s * xd.y;
+                T *out0 = (FUSED && p.yo) ? static_cast<T *>(p.yo) + r * p.ldyo : y + r * ldy;
+                T *out1 = (FUSED && p.yo) ? static_cast<T *>(p.yo) + r1 * p.ldyo : y + r1 * ldy;
+                stream_store(at_byte(out0, (uint32_t)d * (uint32_t)sizeof(T)), o0);
+                if (two)
+                    stream_store(at_byte(out1, (uint32_t)d * (uint32_t)sizeof(T)), o1);
+            }
+            sd = sdn;
+        }
+        __syncthreads();
+    }
+}
+
 // Slab pass.  y holds the row-pass result and receives the complete product.
 template <typename T, int MODE, bool GT>
 __global__ __launch_bounds__(kSlabThreads) void hv_slabs_kernel(SlabArgs p, const T *__restrict__ x, int64_t ldx,
@@ -1250,7 +1449,7 @@ __global__ __launch_bounds__(1024) void hv_blocks_kernel(BlockArgs p, const T *_
 
 struct LineArgs {
     const uint4 *__restrict__ line;    // per row: 32 slots = 8 x uint4
-    const uint32_t *__restrict__ cnt;  // per row: internal, external hops, their maxima over the row's group of eight (bytes 0..3)
+    const uint32_t *__restrict__ cnt;  // per row: internal, external hops, their maxima over the row's group of eight (bytes 0..3); CLS: one word per class
     const int32_t *__restrict__ bstart;
     int64_t dim_up, dim_dn;
     int nblocks, nslab;
@@ -1284,7 +1483,13 @@ struct LineArgs {
 // rows test no bounds; the slab at the rows' ends tests each lane.
 // W = 32: one 128-byte line per row; W = 64 (rows of 33 to 64 hops): two lines,
 // lane q of a row group holding slots 4q..4q+3 of each.
-template <typename T, int MODE, bool GT, int W, bool IPAD, bool X32>
+// CLS (two amplitude classes): line c holds the hops of class c, with a count word
+// of its own, so a hop's factor is its sign alone as with one amplitude, and the
+// class amplitudes multiply the two sums once.  Taking the amplitude by each
+// entry's class bits instead (GT), about ten instructions a hop, 4x4 t-t', 6 + 6,
+// took 1285 us against 1045
+// (1100 with eight internal hops at a time).
+template <typename T, int MODE, bool GT, int W, bool IPAD, bool X32, bool CLS = false>
 __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__restrict__ x, int64_t ldx,
                                                         T *__restrict__ y, int64_t ldy, double alpha,
                                                         const double *__restrict__ coef,
@@ -1293,6 +1498,7 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
     constexpr int EPL = 16 / (int)sizeof(T);  // elements per lane
     constexpr int SL = 8 * EPL;               // slab width in elements
     constexpr int XB = 4;                     // external rows in flight per lane
+    constexpr int IC = CLS ? 4 : 8;           // internal hops at a time: a class has half as many a row
     typedef __attribute__((ext_vector_type(EPL))) T vec;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     vec *xs = reinterpret_cast<vec *>(smem_raw);  // [row in block][8], row bs = 0
@@ -1312,7 +1518,7 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
     else if (FUSED)
         alpha = coef[1];
     // y += scale * sum_k (+-x_k): -t, times alpha in the Lanczos modes
-    const double mt = GT ? -1.0 : -p.t;
+    const double mt = GT || CLS ? -1.0 : -p.t;
     const T scale = (MODE == HV_LANCZOS || FUSED) ? (T)(alpha * mt) : (T)mt;
     // deflated step: shares of psi_l . y (du) and psi_l . x (dx)
     double du[ND > 0 ? ND : 1] = {}, dx[ND > 0 ? ND : 1] = {};
@@ -1396,11 +1602,12 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
             // Lane q of a row group holds slots 4q..4q+3 of the row's line; entry
             // k reaches every lane of the group by a permute within the group.
             constexpr int NL = W / 32;  // 128-byte lines per row
+            constexpr int SP = CLS ? 2 : 1, SW = W / SP;  // spans of slots with counts of their own
             uint4 Em[NL];
 #pragma unroll
             for (int h = 0; h < NL; h++)
                 Em[h] = make_uint4(0u, 0u, 0u, 0u);
-            uint32_t C = 0;
+            uint32_t C[SP] = {};
             vec prev = (vec)(T)0;
             int rb = wave * 8;
             if (rb < bs) {
@@ -1408,7 +1615,9 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
 #pragma unroll
                 for (int h = 0; h < NL; h++)
                     Em[h] = p.line[(r * NL + h) * 8 + q];
-                C = p.cnt[r];
+#pragma unroll
+                for (int h = 0; h < SP; h++)
+                    C[h] = p.cnt[r * SP + h];
                 if (rb + sub < bs)
                     prev = load_prev(r);
             }
@@ -1435,10 +1644,6 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
                         }
                     }
                 }
-                const int ni = (int)(C & 0xffu), ne = (int)((C >> 8) & 0xffu);
-                // the largest counts of the eight rows (the same in every lane)
-                const int nim = __builtin_amdgcn_readfirstlane((int)((C >> 16) & 0xffu));
-                const int nem = __builtin_amdgcn_readfirstlane((int)(C >> 24));
                 // the next row group's entries, counts and running output, a
                 // step ahead.  The loads are unconditional (past the block they
                 // read its last row, unused), so the wait counters stay exact
@@ -1449,70 +1654,84 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
 #pragma unroll
                 for (int h = 0; h < NL; h++)
                     En[h] = p.line[(rn * NL + h) * 8 + q];
-                const uint32_t Cn = p.cnt[rn];
+                uint32_t Cn[SP];
+#pragma unroll
+                for (int h = 0; h < SP; h++)
+                    Cn[h] = p.cnt[rn * SP + h];
                 const vec prevn = load_prev(rn);
                 auto entry = [&](int k) -> uint32_t {
                     const uint4 &E = Em[k >> 5];
                     const uint32_t c = (k & 3) == 0 ? E.x : (k & 3) == 1 ? E.y : (k & 3) == 2 ? E.z : E.w;
                     return (uint32_t)__builtin_amdgcn_ds_bpermute((gbase + ((k & 31) >> 2)) << 2, (int)c);
                 };
-                vec acc = (vec)(T)0;
-                // internal hops, eight slots at a time.  Slot k past the row's
-                // count reads the zero row: with padded lines (IPAD) the line
-                // itself holds it up to the largest count of the group, so
-                // only the group's last, partial chunk selects
-                auto internal = [&](int k0, auto sel_tag) {
-                    constexpr bool SEL = decltype(sel_tag)::value;
-                    const int lim = IPAD ? nim : ni;
-                    vec v[8];
-                    uint32_t ev[8];
+                vec sums[SP];
 #pragma unroll
-                    for (int u = 0; u < 8; u++) {
-                        ev[u] = entry(k0 + u);
-                        const int li =
-                            (!SEL || k0 + u < lim) ? (int)(ev[u] & (GT ? kGtRowMask : 0x7fffffffu)) : bs;
-                        v[u] = xs[li * 8 + q];
-                    }
+                for (int h = 0; h < SP; h++) {
+                    const int S0 = h * SW;
+                    vec acc = (vec)(T)0;
+                    const int ni = (int)(C[h] & 0xffu), ne = (int)((C[h] >> 8) & 0xffu);
+                    // the largest counts of the eight rows (the same in every lane)
+                    const int nim = __builtin_amdgcn_readfirstlane((int)((C[h] >> 16) & 0xffu));
+                    const int nem = __builtin_amdgcn_readfirstlane((int)(C[h] >> 24));
+                    // internal hops, IC slots at a time.  Slot k past the row's
+                    // count reads the zero row: with padded lines (IPAD) the line
+                    // itself holds it up to the largest count of the group, so
+                    // only the group's last, partial chunk selects
+                    auto internal = [&](int k0, auto sel_tag) {
+                        constexpr bool SEL = decltype(sel_tag)::value;
+                        const int lim = IPAD ? nim : ni;
+                        vec v[IC];
+                        uint32_t ev[IC];
 #pragma unroll
-                    for (int u = 0; u < 8; u++) {
-                        const T f = signed_factor<T, GT>(am, ev[u]);
-#pragma unroll
-                        for (int c = 0; c < EPL; c++)
-                            acc[c] = fma(f, v[u][c], acc[c]);
-                    }
-                };
-#pragma unroll
-                for (int k0 = 0; k0 < W; k0 += 8) {
-                    if (k0 < nim) {
-                        if (IPAD && k0 + 8 <= nim)
-                            internal(k0, std::false_type{});
-                        else
-                            internal(k0, std::true_type{});
-                    }
-                }
-#pragma unroll
-                for (int k0 = 0; k0 < W; k0 += XB) {
-                    if (k0 < nem) {
-                        vec v[XB];
-                        uint32_t ev[XB];
-#pragma unroll
-                        for (int u = 0; u < XB; u++) {
-                            ev[u] = entry(W - 1 - (k0 + u));
-                            // slots past this row's external count issue no load
-                            v[u] = (vec)(T)0;
-                            if (k0 + u < ne)
-                                v[u] = load_ext(ev[u]);
+                        for (int u = 0; u < IC; u++) {
+                            ev[u] = entry(S0 + k0 + u);
+                            const int li =
+                                (!SEL || k0 + u < lim) ? (int)(ev[u] & (GT ? kGtRowMask : 0x7fffffffu)) : bs;
+                            v[u] = xs[li * 8 + q];
                         }
 #pragma unroll
-                        for (int u = 0; u < XB; u++) {
-                            // and add nothing (factor 0)
-                            const T f = k0 + u < ne ? signed_factor<T, GT>(am, ev[u]) : (T)0;
+                        for (int u = 0; u < IC; u++) {
+                            const T f = signed_factor<T, GT>(am, ev[u]);
 #pragma unroll
                             for (int c = 0; c < EPL; c++)
                                 acc[c] = fma(f, v[u][c], acc[c]);
                         }
+                    };
+#pragma unroll
+                    for (int k0 = 0; k0 < SW; k0 += IC) {
+                        if (k0 < nim) {
+                            if (IPAD && k0 + IC <= nim)
+                                internal(k0, std::false_type{});
+                            else
+                                internal(k0, std::true_type{});
+                        }
                     }
+#pragma unroll
+                    for (int k0 = 0; k0 < SW; k0 += XB) {
+                        if (k0 < nem) {
+                            vec v[XB];
+                            uint32_t ev[XB];
+#pragma unroll
+                            for (int u = 0; u < XB; u++) {
+                                ev[u] = entry(S0 + SW - 1 - (k0 + u));
+                                // slots past this row's external count issue no load
+                                v[u] = (vec)(T)0;
+                                if (k0 + u < ne)
+                                    v[u] = load_ext(ev[u]);
+                            }
+#pragma unroll
+                            for (int u = 0; u < XB; u++) {
+                                // and add nothing (factor 0)
+                                const T f = k0 + u < ne ? signed_factor<T, GT>(am, ev[u]) : (T)0;
+#pragma unroll
+                                for (int c = 0; c < EPL; c++)
+                                    acc[c] = fma(f, v[u][c], acc[c]);
+                            }
+                        }
+                    }
+                    sums[h] = acc;
                 }
+                const vec acc = CLS ? am[0] * sums[0] + am[1] * sums[SP - 1] : sums[0];
                 if (okr && (FULL || dok)) {
                     const vec xv = xs[rl * 8 + q];
                     const vec out = prev + scale * acc;  // in the residual mode prev = row pass of H x - alpha x
@@ -1571,7 +1790,9 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
 #pragma unroll
                 for (int h = 0; h < NL; h++)
                     Em[h] = En[h];
-                C = Cn;
+#pragma unroll
+                for (int h = 0; h < SP; h++)
+                    C[h] = Cn[h];
                 prev = prevn;
             }
         };
@@ -1883,6 +2104,57 @@ static void launch_rows32x2_mode(const Row32Args &ra, int np, int nn, const floa
         launch_rows32x2_mode<HV_RESIDUAL>(ra, np, nn, x, ldx, y, ldy, alpha, coef, s);
 }
 
+// Pairs of rows by class: two classes, a pair and its zero slot within the LDS.
+template <typename T>
+static bool rows_cls_ok(const HvArgs &a, int mode)
+{
+    return a.dn_cls && mode != HV_FUSED_DEFL && 2 * sizeof(T) * (size_t)(a.dim_dn + 1) <= (size_t)kLdsBytes;
+}
+
+template <typename T>
+static void launch_rows_cls(const HvArgs &a, const T *x, int64_t ldx, T *y, int64_t ldy, int mode, double alpha,
+                            const double *coef, hipStream_t s, void *xc, int64_t ldc, void *yo, int64_t ldyo)
+{
+    RowClsArgs ra;
+    ra.groups = a.dn_cls;
+    ra.cn = a.dn_cls_n;
+    ra.g1 = a.dn_cls_g1;
+    ra.states_up = a.states_up;
+    ra.states_dn = a.states_dn;
+    ra.dim_up = a.dim_up;
+    ra.dim_dn = (int)a.dim_dn;
+    ra.amp[0] = a.amp4[0];
+    ra.amp[1] = a.amp4[1];
+    ra.U = a.U;
+    ra.xc = xc;
+    ra.ldc = ldc;
+    ra.yo = yo;
+    ra.ldyo = ldyo;
+    const size_t lds = 2 * sizeof(T) * (size_t)(a.dim_dn + 1);
+    const int grid = (int)std::min<int64_t>((a.dim_up + 1) / 2, 256);  // one workgroup per CU
+    auto go = [&](auto kern) {
+        HUB_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kRowThreads), lds, s, ra, x, ldx, y, ldy, alpha, 0.0, coef);
+        HUB_HIP(hipGetLastError());
+    };
+    auto by_mode = [&](auto ng) {
+        constexpr int NG = decltype(ng)::value;
+        if (mode == HV_STORE)
+            go(hv_rows_cls_kernel<T, HV_STORE, NG>);
+        else if (mode == HV_LANCZOS)
+            go(hv_rows_cls_kernel<T, HV_LANCZOS, NG>);
+        else if (mode == HV_FUSED)
+            go(hv_rows_cls_kernel<T, HV_FUSED, NG>);
+        else
+            go(hv_rows_cls_kernel<T, HV_RESIDUAL, NG>);
+    };
+    // three groups of a class (rows of up to 24 hops of it), or four
+    if (a.dn_cls_ng <= 3)
+        by_mode(std::integral_constant<int, 3>{});
+    else
+        by_mode(std::integral_constant<int, kClsGroups>{});
+}
+
 template <typename T>
 int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y, int64_t ldy, T *scratch,
                int64_t lds_, int mode, double alpha, const double *coef, double *partials, hipStream_t s, T *xpad,
@@ -1950,7 +2222,7 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
             if (done)
                 launch_rows64(a, pl, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s, static_cast<T *>(ra.xc), ra.ldc,
                               dfl, static_cast<T *>(rh.yo), ldy);
-        } else {
+        } else if (!rows_cls_ok<T>(a, mode)) {
             done = rows32x2_ok(a, mode);
             if (done)
                 launch_rows32x2(a, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s, static_cast<T *>(ra.xc), ra.ldc,
@@ -1959,6 +2231,10 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
                 launch_rows_rpb<T, 3>(rh, g16, gt, pl, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s);
                 done = true;
             }
+        }
+        if (!done && rows_cls_ok<T>(a, mode)) {
+            launch_rows_cls<T>(a, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s, ra.xc, ra.ldc, rh.yo, ldy);
+            done = true;
         }
         if (done)
             continue;
@@ -2044,6 +2320,12 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
             const int64_t rowb = ldx * (int64_t)sizeof(T);
             const bool x32 = a.dim_up < (1 << 24) && rowb < (1 << 24) && a.dim_up * rowb < ((int64_t)1 << 32);
             const bool ipad = a.up_line_ipad != 0;
+            // two classes with their lines: the same rows, entries sorted by class
+            const bool cls = gt && a.up_cls_line && x32;
+            if (cls) {
+                la.line = reinterpret_cast<const uint4 *>(a.up_cls_line);
+                la.cnt = a.up_cls_cnt;
+            }
             auto pick = [&](auto mode_tag) {
                 constexpr int M = decltype(mode_tag)::value;
                 if constexpr (M == HV_FUSED_DEFL) {
@@ -2054,7 +2336,9 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
                     else
                         (ipad && x32) ? gol(hv_lines_kernel<T, M, false, 64, true, true>)
                                       : gol(hv_lines_kernel<T, M, false, 64, false, false>);
-                } else if (gt)
+                } else if (cls)
+                    gol(hv_lines_kernel<T, M, false, 64, true, true, true>);
+                else if (gt)
                     w64 ? gol(hv_lines_kernel<T, M, true, 64, false, false>)
                         : gol(hv_lines_kernel<T, M, true, 32, false, false>);
                 else if (!w64)

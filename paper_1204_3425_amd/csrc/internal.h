@@ -52,6 +52,8 @@ constexpr int kTwoPassClasses = 4;
 // longest row the FP64 row pass stages in LDS (plus one zero slot: 160 KB)
 constexpr int kRow64Max = 20000;
 
+constexpr int kClsGroups = 4;  // row pass by class: groups of eight per class and column at most
+
 struct DeviceTables {
     uint32_t *states_up = nullptr, *states_dn = nullptr;
     uint32_t *up_rows = nullptr;   // row-major: entry k of row r at r*w_up + k (row entries are wave-uniform)
@@ -78,6 +80,13 @@ struct DeviceTables {
     // group counts (one byte each); dn_np, dn_nn: the largest counts
     uint16_t *dn_pidx = nullptr, *dn_nidx = nullptr;
     uint8_t *dn_pn = nullptr;
+    // two amplitude classes: per column the hops of class 0 in groups of eight
+    // 16-bit entries, then (from group slot dn_cls_g1 on) those of class 1; the
+    // first entry of a word has its sign in bit 0 and its index above, the second
+    // its sign in bit 31.  Group counts of both per 64 columns.
+    uint16_t *dn_cls = nullptr;
+    uint8_t *dn_cls_n = nullptr;
+    int dn_cls_g1 = 0, dn_cls_ng = 0;
     int dn_np = 0, dn_nn = 0;
     // up table for the blocked slab pass: rows are grouped in blocks of equal
     // occupation of the top sites; per row the hops that stay in the block come
@@ -94,6 +103,9 @@ struct DeviceTables {
     // slots past a row's internal count, up to the largest count of its group,
     // hold the block's zero row
     uint32_t *up_line = nullptr, *up_cnt = nullptr;
+    // two amplitude classes: per row a padded line of 32 slots for each class and
+    // a count word for each (null where a row's class has no room in 32)
+    uint32_t *up_cls_line = nullptr, *up_cls_cnt = nullptr;
     // one-launch H.v: the up entries as up_tile_w slots per row (a multiple of
     // eight; slots past a row's count repeat its last hop), and for per-bond
     // handles the down entries in slots of one amplitude each: groups of eight
@@ -236,6 +248,10 @@ struct HvArgs {
     const uint4 *dn_pidx = nullptr;       // FP64 row pass: + hops, eight per group (null: not built)
     const uint2 *dn_nidx = nullptr;       // - hops, four per group
     const uint8_t *dn_pn = nullptr;       // group counts per 64 columns
+    const uint4 *dn_cls = nullptr;        // two classes: groups by class (see DeviceTables)
+    const uint8_t *dn_cls_n = nullptr;
+    int dn_cls_g1 = 0, dn_cls_ng = 0;  // first slot of class 1, most groups of a class
+    const uint32_t *up_cls_line = nullptr, *up_cls_cnt = nullptr;
     int dn_np = 0, dn_nn = 0;             // their largest values
     const uint32_t *up_blk;
     const uint16_t *up_nint, *up_next;
