@@ -1138,7 +1138,11 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
             out.a.push_back(a);
             out.b.push_back(b);
             const int j = j0 + 1;
-            const double e = tridiag_lowest(out.a.data(), out.b.data(), j);
+            // at most the step before's value (Cauchy interlacing), and near it
+            const double e1 = j >= 3 ? out.e[(size_t)j0 - 1] : 0.0;
+            const double width =
+                j >= 3 ? 4.0 * std::fabs(e1 - out.e[(size_t)j0 - 2]) + 1e-12 * std::fmax(1.0, std::fabs(e1)) : 0.0;
+            const double e = tridiag_lowest(out.a.data(), out.b.data(), j, e1, width);
             out.e.push_back(e);
             checked++;
             if (!std::isfinite(a) || !std::isfinite(b))

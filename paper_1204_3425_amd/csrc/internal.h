@@ -224,7 +224,9 @@ uint64_t binomial(int n, int k);
 
 // tridiag.cpp: symmetric tridiagonal T with diagonal d[0..m-1] and
 // off-diagonal e[i] between rows i and i+1 (i < m-1).
-double tridiag_lowest(const double *d, const double *e, int m);
+// near, width: a guess that the value lies in (near - width, near] (width 0: none); the
+// result does not depend on it.
+double tridiag_lowest(const double *d, const double *e, int m, double near = 0.0, double width = 0.0);
 void tridiag_lowest_vector(const double *d, const double *e, int m, double lam, double *y);
 // c = exp(-i tau T) e_1 (real and imaginary parts, m each); e holds the m-1 off-diagonals
 void tridiag_expm_e1(const double *d, const double *e, int m, double tau, double *c_re, double *c_im);
