@@ -846,7 +846,7 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
     // the one-launch form's sums: of the H.v (two sets where lower vectors are
     // projected out in the step, whose sums the next step reads again), reduced
     // ones, of the norms (two sets) and of the separate projection
-    const bool tdefl = nd > 0 && nd <= kTileDefl;
+    const bool tdefl = nd > 0 && nd <= tplan.defl;
     const int tsets = tdefl ? 2 : 1, tper = 1 + (tdefl ? 2 * nd : 0);
     const int tnb = nd > 0 ? tile_defl_blocks(h->up.dim) : tile_update_blocks(npad, sizeof(T));
     const int tparts = tsets * tper * (tplan.grid + 1);
@@ -922,7 +922,7 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
             launch_reduce(raw, tplan.grid, tplan.grid, tper, const_cast<double *>(st.part), s);
         launch_tile_update<T>(Q, C, Pm, h->up.dim, h->dn.dim, ld, 1, st, s, tdefl ? dfl.psi : nullptr,
                               tdefl ? nd : 0);
-        if (nd > kTileDefl)
+        if (nd > 0 && !tdefl)
             launch_tile_project<T>(Q, dfl.psi, nd, h->up.dim, h->dn.dim, ld, tdots, st.norm2_out, s);
         if (j0 + 1 == max_iter)
             launch_tile_scalar(tile_scalars(j0 + 1), 0, s);  // b of the last step

@@ -354,6 +354,7 @@ constexpr int64_t kTileStepBytes = (int64_t)160 << 20;
 struct TilePlan {
     bool ok = false;
     int threads = 64, grid = 8, nseg = 1, span = 64;
+    int defl = 0;  // lower vectors that a step's two launches project out at this row length
     size_t lds = 0;
 };
 // Lanczos step j (0-based) in two launches: the H.v (HV_LANCZOS) writes q = H x_j
@@ -363,7 +364,7 @@ struct TilePlan {
 // hist (may be mapped host memory): b_j at 2j, a_j at 2j + 1.  unit: x_0 is taken as a unit vector.  Where the
 // H.v writes more than kTileDirectParts sums the caller reduces them to one first.
 constexpr int kTileDirectParts = 4096;
-constexpr int kTileDefl = 4;  // lower vectors the two launches project out themselves
+constexpr int kTileDefl = 4;  // most lower vectors the two launches project out themselves
 struct TileStep {
     const double *norm2 = nullptr;  // partial sums of |x_j|^2
     int n_norm2 = 0;
@@ -377,7 +378,7 @@ struct TileStep {
     int unit = 0;
 };
 TilePlan make_tile_plan(const HvArgs &a, int elem_bytes);
-// HV_STORE: out = H x.  HV_LANCZOS: as above, with nd <= kTileDefl dense lower
+// HV_STORE: out = H x.  HV_LANCZOS: as above, with nd <= pl.defl dense lower
 // vectors psi.  HV_RESIDUAL: partial sums of |Hx - shift x|^2, then of x.Hx.
 // pl.grid sums of each (twice that with pair > 0: both halves of a complex
 // vector at that element offset).

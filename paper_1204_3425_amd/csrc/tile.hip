@@ -30,6 +30,14 @@ namespace hub {
 namespace {
 
 constexpr int kTileLds = 160 * 1024;
+constexpr int kTileWaves = 16;  // of the largest workgroup
+
+// Static LDS of hv_tile_kernel beside the staged row: one value per wave of each
+// of its na sums (1 + 2 ND of a step with ND lower vectors, two of a residual).
+constexpr int tile_red_bytes(int na) { return (int)sizeof(double) * kTileWaves * na; }
+// kept free of the row in every plan: the sums of a step with one lower vector
+constexpr int kTileLdsSpare = 512;
+static_assert(tile_red_bytes(1 + 2 * 1) <= kTileLdsSpare && tile_red_bytes(2) <= kTileLdsSpare, "");
 
 // sign bit of a 16-bit entry (low or high half of e) moved to bit 31
 __device__ inline uint32_t entry_sign(uint32_t e, int half) { return (half ? e : e << 16) & 0x80000000u; }
@@ -120,7 +128,7 @@ __device__ inline void tile_sums(double (&v)[N], double (*red)[N])
 // w_up slots per row, those past its count repeating its last hop; tcls:
 // amplitude of each class (GT).  ND: room for lower vectors of a deflated step.
 template <typename T, int MODE, bool GT, int ND>
-__global__ __launch_bounds__(1024, (sizeof(T) == 8 || GT || ND > 0) ? 4 : 8) void hv_tile_kernel(TileArgs p, const uint4 *__restrict__ dn,
+__global__ __launch_bounds__(64 * kTileWaves, (sizeof(T) == 8 || GT || ND > 0) ? 4 : 8) void hv_tile_kernel(TileArgs p, const uint4 *__restrict__ dn,
                                                        const uint8_t *__restrict__ dn_nq,
                                                        const double *__restrict__ dn_amp,
                                                        const uint32_t *__restrict__ up_rows,
@@ -326,7 +334,8 @@ __global__ __launch_bounds__(1024, (sizeof(T) == 8 || GT || ND > 0) ? 4 : 8) voi
         }
     }
     if (MODE != HV_STORE) {
-        __shared__ double red[16][NA];
+        __shared__ double red[kTileWaves][NA];
+        static_assert(sizeof(red) == tile_red_bytes(NA), "");
         tile_sums<NA>(acc, red);
         const int b = (int)(blockIdx.y * gridDim.x + blockIdx.x), nb = (int)(gridDim.x * gridDim.y);
         if (tid == 0)
@@ -533,7 +542,7 @@ TilePlan make_tile_plan(const HvArgs &a, int elem_bytes)
     const int64_t ddn = a.dim_dn;
     const bool gt = a.tcls != nullptr;
     pl.lds = (size_t)(ddn + 1) * (size_t)elem_bytes;
-    if ((gt ? a.dn_slots == nullptr : a.dn_groups16 == nullptr) || !a.up_tile || pl.lds > kTileLds - 512)
+    if ((gt ? a.dn_slots == nullptr : a.dn_groups16 == nullptr) || !a.up_tile || pl.lds > kTileLds - kTileLdsSpare)
         return pl;
     if (a.dim_up * ddn * elem_bytes > kTileMaxBytes && (!gt || a.ncls <= kTwoPassClasses))
         return pl;
@@ -551,6 +560,13 @@ TilePlan make_tile_plan(const HvArgs &a, int elem_bytes)
     pl.span = (int)(((ddn + seg - 1) / seg + 63) / 64 * 64);
     pl.nseg = (int)((ddn + pl.span - 1) / pl.span);
     pl.grid = 8 * (int)((a.dim_up * pl.nseg + 7) / 8);
+    // instances with room for 4, 2 and 1 lower vectors: the largest whose sums fit
+    // beside the row (FP64 rows of 20,349 elements, 21 sites with 5 electrons, leave
+    // 1,040 bytes, and the sums of four take 1,152); more lower vectors than that
+    // are projected out by launches of their own
+    pl.defl = kTileDefl;
+    while (pl.defl > 1 && pl.lds + (size_t)tile_red_bytes(1 + 2 * pl.defl) > (size_t)kTileLds)
+        pl.defl /= 2;
     pl.ok = true;
     return pl;
 }
@@ -559,6 +575,8 @@ template <typename T>
 void launch_hv_tile(const HvArgs &a, const TilePlan &pl, const T *x, int64_t ldx, T *out, int64_t ldy, int mode,
                     double shift, double *part, hipStream_t s, const double *psi, int nd, int64_t pair)
 {
+    if (nd > pl.defl)
+        fail(HUBBARD_EDEVICE, "one-launch step: more lower vectors than the row length leaves room for");
     TileArgs p;
     const bool gt = a.tcls != nullptr;
     p.nseg = pl.nseg;

@@ -11,6 +11,9 @@ with two classes, with a class per bond, and with more than 16 slots.
 Tolerance as for every H.v of this library: FP64 1e-13 of the largest element;
 FP32 (terms + 1) 2^-24 times the largest sum of magnitudes a row can have.
 """
+import itertools
+import math
+
 import numpy as np
 import pytest
 
@@ -176,6 +179,25 @@ def test_one_launch_deflated_steps(k):
     assert np.abs(E - w).max() <= 1e-10 * max(1.0, np.abs(w).max())
     P = psi.cpu().numpy()
     assert np.abs(P @ P.T - np.eye(k)).max() <= 1e-12
+
+
+def test_one_launch_deflated_steps_rows_that_fill_the_lds():
+    """Rows of 20,349 doubles leave 1,040 bytes of LDS, less than the sums of a step
+    with four lower vectors take: one and two are projected out in the step's
+    launches, three and four by their own.  Free fermions on an open chain, levels
+    -2 cos(pi j / 22) (spacing of the lowest states above 0.04): energies within
+    1e-10, orthonormal to 1e-12, residuals below 1e-6."""
+    n, nu, nd, k = 21, 1, 5, 5
+    print("deflated, 20,349 columns", flush=True)
+    lv = [-2.0 * math.cos(math.pi * j / (n + 1)) for j in range(1, n + 1)]
+    w = np.sort(np.add.outer(lv, [sum(c) for c in itertools.combinations(lv, nd)]).ravel())[:k]
+    h = hb.hubbard_build(n, workload.chain(n), nu, nd, 1.0, 0.0)
+    psi = torch.empty((k, h.dim), dtype=torch.float64, device=DEV)
+    E, res = hb.hubbard_lowest_states(h, k, tol=1e-14, max_iter=800, psi=psi)
+    assert np.abs(np.array(E) - w).max() <= 1e-10 * max(1.0, np.abs(w).max())
+    P = psi.cpu().numpy()
+    assert np.abs(P @ P.T - np.eye(k)).max() <= 1e-12
+    assert max(r["residual"] for r in res) <= 1e-6
 
 
 def test_one_launch_propagation_many_rows():
