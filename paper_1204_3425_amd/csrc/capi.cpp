@@ -714,6 +714,16 @@ static HvArgs hv_args(const hubbard *h)
     a.w_dn = h->dn.width;
     a.t = h->t;
     a.U = h->U;
+    // the power of two at or below the largest coupling, within what a double's
+    // inverse can hold
+    double big = std::fabs(h->U);
+    if (h->tcls.empty())
+        big = std::fmax(big, std::fabs(h->t));
+    for (double c : h->tcls)
+        big = std::fmax(big, std::fabs(c));
+    const int e = big > 0.0 ? std::max(-1000, std::min(std::ilogb(big), 1000)) : 0;
+    a.qscale = std::ldexp(1.0, -e);
+    a.qunscale = std::ldexp(1.0, e);
     return a;
 }
 
@@ -906,6 +916,7 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
         st.part = set(j0);
         st.part_prev = set(j0 + 1);  // of two sets the other one
         st.n_part = direct ? tplan.grid : 1;
+        st.qunscale = args.qunscale;
         st.b = B;
         st.hist = hist;
         st.j = j0;
@@ -1450,6 +1461,7 @@ int propagate_impl(hubbard *h, double *re, double *im, double t, int n_steps, in
         st.norm2_out = tnorm + ((j + 1) & 1) * tnn;
         st.part = part + (tgrid > kTileDirectParts ? tgrid : 0);
         st.n_part = tgrid > kTileDirectParts ? 1 : tgrid;
+        st.qunscale = args.qunscale;
         st.b = sc;
         st.hist = thist;
         st.j = j;

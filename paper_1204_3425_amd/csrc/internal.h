@@ -269,6 +269,8 @@ struct HvArgs {
     const double *dn_slot_amp = nullptr;
     const uint8_t *dn_slot_nq = nullptr;
     int dn_slot_groups = 0;
+    // a power of two near 1 / max(|t|, |U|), and its inverse (see TileStep)
+    double qscale = 1.0, qunscale = 1.0;
 };
 
 // Launch shape of the two-pass H.v for one element size (hv.hip).
@@ -360,7 +362,11 @@ struct TilePlan {
 // Lanczos step j (0-based) in two launches: the H.v (HV_LANCZOS) writes q = H x_j
 // and partial sums of q.x_j; the update forms b_j = |x_j| from norm2, a_j from
 // those sums, x_{j+1} = q / b_j - (a_j / b_j) x_j - (b_j / b_{j-1}) x_{j-1} in
-// place of q, and the partial sums of its square (norm2_out).  b[j] holds |x_j|;
+// place of q, and the partial sums of its square (norm2_out).  With |x_j| = b_j the
+// product q.x_j is of the order of b_j^2 |H|, three powers of the couplings where
+// |x_j|^2 has two, so the H.v sums qscale q.x_j (exact, |H| qscale near 1) and the
+// update takes the factor out of a_j: the sums then fit a double wherever the
+// norms do.  b[j] holds |x_j|;
 // hist (may be mapped host memory): b_j at 2j, a_j at 2j + 1.  unit: x_0 is taken as a unit vector.  Where the
 // H.v writes more than kTileDirectParts sums the caller reduces them to one first.
 constexpr int kTileDirectParts = 4096;
@@ -372,6 +378,7 @@ struct TileStep {
     const double *part = nullptr;       // sums of q.x_j, then psi_l.q and psi_l.x_j in turn (n_part each)
     const double *part_prev = nullptr;  // those of step j - 1 (deflated steps)
     int n_part = 0;
+    double qunscale = 1.0;  // as in HvArgs
     double *b = nullptr;
     double *hist = nullptr;
     int j = 0;

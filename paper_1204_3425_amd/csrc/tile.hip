@@ -92,7 +92,7 @@ struct TileArgs {
     int64_t dim_up;
     int dim_dn, w_up, gmax;  // slots per up row, groups per column
     int nseg, span;          // workgroups per row, columns of each (a multiple of 64)
-    double t, U;
+    double t, U, qscale;
     int64_t pair;            // element offset of the second half of a complex vector (gridDim.y = 2)
     const double *psi;       // deflated step: nd dense vectors, vector l at psi + l * pdim
     int nd;
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(64 * kTileWaves, (sizeof(T) == 8 || GT || ND > 0) ?
             if (MODE != HV_RESIDUAL)
                 out[r * ldy + d] = h;
             if (MODE == HV_LANCZOS) {
-                acc[0] += (double)h * (double)xv;
+                acc[0] += (double)h * p.qscale * (double)xv;
 #pragma unroll
                 for (int l = 0; l < ND; l++) {
                     acc[1 + 2 * l] += (double)h * pv[l];
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(kUpdThreads) void tile_update_kernel(T *__restrict_
             tot[k] = s;
     }
     __syncthreads();
-    const double bj = sqrt(tot[0]), s = recip_norm(bj), a = tot[1] * s * s;
+    const double bj = sqrt(tot[0]), s = recip_norm(bj), a = tot[1] * s * s * st.qunscale;
     const double c = a * s, e = st.j > 0 ? bj * recip_norm(st.b[st.j - 1]) : 0.0;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st.b[st.j] = bj;
@@ -521,7 +521,7 @@ __global__ __launch_bounds__(64) void tile_scalar_kernel(TileStep st, int what)
 {
     const double b = sqrt(st.j > 0 || !st.unit ? wave_total(st.norm2, st.n_norm2) : 1.0);
     const double s = recip_norm(b);
-    const double a = what ? wave_total(st.part, st.n_part) * s * s : 0.0;
+    const double a = what ? wave_total(st.part, st.n_part) * s * s * st.qunscale : 0.0;
     if (threadIdx.x == 0) {
         st.b[st.j] = b;
         st.hist[2 * st.j] = b;
@@ -589,6 +589,7 @@ void launch_hv_tile(const HvArgs &a, const TilePlan &pl, const T *x, int64_t ldx
     p.dim_dn = (int)a.dim_dn;
     p.t = a.t;
     p.U = a.U;
+    p.qscale = a.qscale;
     p.pair = pair;
     p.psi = psi;
     p.nd = nd;

@@ -221,6 +221,34 @@ def test_one_launch_propagation_many_rows():
     assert np.linalg.norm(got - want) <= 1e-11
 
 
+@pytest.mark.parametrize("ncls", [0, 2, 8], ids=["uniform", "two_classes", "class_per_bond"])
+@pytest.mark.parametrize("e", [-498, -370, 370, 498])
+def test_one_launch_steps_of_tiny_and_huge_couplings(e, ncls):
+    """H scaled by a power of two scales every product and sum of a step exactly
+    while all of them are normal numbers, and the squared norms are up to 2^+-500
+    couplings: the coefficients, energies and the evolution over the scaled time
+    are those of the unscaled H to rounding (the stop test, absolute below 1, is
+    off; the vector of a scaled H is the same vector)."""
+    print("couplings times 2 **", e, ncls, flush=True)
+    f = 2.0**e
+    edges = workload.ring(8)
+    amps = _amps(edges, ncls, 8) if ncls else [1.0] * len(edges)
+    got = []
+    for c in (1.0, f):
+        h = hb.hubbard_build_bonds(8, edges, [c * a for a in amps], 4, 3, 3.0 * c)
+        psi = torch.empty(h.dim, dtype=torch.float64, device=DEV)
+        r = hb.hubbard_lanczos_ex(h, tol=-1.0, max_iter=30, seed=5, psi=psi)
+        E, _ = hb.hubbard_lowest_states(h, 3, tol=-1.0, max_iter=30, seed=5)
+        g = torch.Generator(device=DEV)
+        g.manual_seed(4)
+        re = torch.rand(h.dim, generator=g, dtype=torch.float64, device=DEV) - 0.5
+        im = torch.rand(h.dim, generator=g, dtype=torch.float64, device=DEV) - 0.5
+        p = hb.hubbard_propagate(h, re, im, 0.25 / c, 2, 16)
+        got.append((r["a"] / c, r["b"] / c, psi.cpu().numpy(), E / c, re.cpu().numpy(), im.cpu().numpy(), p["energy"] / c))
+    for one, scaled in zip(*got):
+        assert np.abs(scaled - one).max() <= 1e-11 * max(1.0, np.abs(one).max())
+
+
 def test_kept_buffers_two_streams_and_a_batch_of_one_handle():
     """A handle's kept buffers are not shared by work in flight: solves on two
     streams in turn, and the same handle several times in one batch."""
