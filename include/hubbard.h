@@ -71,7 +71,7 @@ typedef struct {
     int64_t dim_up, dim_dn, dim; /* C(sites, N_up), C(sites, N_dn), their product (Sec. 2.1) */
     int32_t w_up, w_dn;          /* ELL widths = max entries per row (Sec. 4.2, Fig. ELL) */
     int64_t nnz_up, nnz_dn;      /* stored hopping entries per spin */
-    size_t device_bytes;         /* device memory held by the handle (tables + states) */
+    size_t device_bytes;         /* device memory of the handle's tables and states (without kept buffers) */
     size_t vector_bytes;         /* device memory of one Lanczos run (work vectors) */
     int64_t ld_pref;             /* row stride (elements) of the library's own vectors */
 } hubbard_info_t;
@@ -138,7 +138,8 @@ int hubbard_build_bonds(int sites, const int32_t *edges, const double *t, int n_
 
 /* Releases the handle and its device memory: its tables, and the device
  * buffers of its calls that it keeps for the next one (at most 1 GiB per handle,
- * 8 GiB over all handles).  NULL is accepted. */
+ * 8 GiB over all handles; an allocation of this library that finds the device
+ * full frees those of every handle and tries again).  NULL is accepted. */
 int hubbard_free(hubbard_h h);
 
 /* Stream for every later call on this handle (a hipStream_t; NULL = the null

@@ -33,7 +33,7 @@ struct Pinned {
     void *dev = nullptr;  // the same memory's device address
     explicit Pinned(size_t bytes)
     {
-        HUB_HIP(hipHostMalloc(&p, bytes ? bytes : 16, hipHostMallocMapped | hipHostMallocCoherent));
+        p = host_alloc(bytes ? bytes : 16);
         HUB_HIP(hipHostGetDevicePointer(&dev, p, 0));
     }
     ~Pinned()

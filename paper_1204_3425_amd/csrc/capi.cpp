@@ -15,12 +15,10 @@
 // behind the device, computes the lowest eigenvalue of T_j (eq. Tmatrix) and
 // applies the energy test of Sec. 2.2.
 #include <algorithm>
-#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <exception>
 #include <memory>
 #include <string>
 #include <vector>
@@ -61,151 +59,6 @@ static int guarded(F &&f)
     }
 }
 
-void *Workspace::take(size_t bytes, size_t *got)
-{
-    bytes = (std::max<size_t>(bytes, 16) + 65535) / 65536 * 65536;
-    {
-        std::lock_guard<std::mutex> lk(mu_);
-        size_t best = dev_.size();
-        for (size_t k = 0; k < dev_.size(); k++)
-            if (dev_[k].bytes >= bytes && dev_[k].bytes <= 2 * bytes &&
-                (best == dev_.size() || dev_[k].bytes < dev_[best].bytes))
-                best = k;
-        if (best < dev_.size()) {
-            const Block b = dev_[best];
-            drop(best);
-            *got = b.bytes;
-            return b.p;
-        }
-    }
-    void *p = nullptr;
-    *got = bytes;
-    if (hipMalloc(&p, bytes) == hipSuccess)
-        return p;
-    (void)hipGetLastError();
-    release();
-    HUB_HIP(hipMalloc(&p, bytes));
-    return p;
-}
-
-// bytes kept by all handles of the process
-static std::atomic<size_t> g_kept{0};
-
-void Workspace::drop(size_t k)
-{
-    held_ -= dev_[k].bytes;
-    g_kept -= dev_[k].bytes;
-    dev_.erase(dev_.begin() + (std::ptrdiff_t)k);
-}
-
-void Workspace::give(void *p, size_t bytes)
-{
-    if (bytes > kKeepBytes) {
-        (void)hipFree(p);
-        return;
-    }
-    std::lock_guard<std::mutex> lk(mu_);
-    dev_.push_back(Block{p, bytes});
-    held_ += bytes;
-    g_kept += bytes;
-    while (!dev_.empty() && (held_ > kKeepBytes || g_kept.load() > kKeepAll)) {
-        (void)hipFree(dev_.front().p);
-        drop(0);
-    }
-}
-
-void *Workspace::take_host(size_t bytes, size_t *got)
-{
-    bytes = (bytes + 16383) / 16384 * 16384;
-    {
-        std::lock_guard<std::mutex> lk(mu_);
-        for (size_t k = 0; k < host_.size(); k++)
-            if (host_[k].bytes >= bytes) {
-                void *p = host_[k].p;
-                *got = host_[k].bytes;
-                host_.erase(host_.begin() + (std::ptrdiff_t)k);
-                return p;
-            }
-    }
-    void *p = nullptr;
-    *got = bytes;
-    HUB_HIP(hipHostMalloc(&p, bytes, hipHostMallocMapped | hipHostMallocCoherent));
-    return p;
-}
-
-void Workspace::give_host(void *p, size_t bytes)
-{
-    {
-        std::lock_guard<std::mutex> lk(mu_);
-        // one or two small blocks serve every call
-        if (host_.size() < 2 && bytes <= (1 << 20)) {
-            host_.push_back(Block{p, bytes});
-            return;
-        }
-    }
-    (void)hipHostFree(p);
-}
-
-void Workspace::release()
-{
-    std::lock_guard<std::mutex> lk(mu_);
-    for (const Block &b : dev_)
-        (void)hipFree(b.p);
-    for (const Block &b : host_)
-        (void)hipHostFree(b.p);
-    g_kept -= held_;
-    dev_.clear();
-    host_.clear();
-    held_ = 0;
-}
-
-DevBuf::DevBuf(size_t n, Workspace *w) : ws(w)
-{
-    if (!n)
-        return;
-    bytes = n;
-    if (ws)
-        p = ws->take(n, &bytes);
-    else
-        HUB_HIP(hipMalloc(&p, n));
-}
-
-DevBuf::~DevBuf()
-{
-    if (!p)
-        return;
-    if (!ws) {
-        (void)hipFree(p);
-        return;
-    }
-    // a call that ends in an error may have left work in flight
-    if (std::uncaught_exceptions() > 0)
-        (void)hipDeviceSynchronize();
-    ws->give(p, bytes);
-}
-
-PinnedBuf::PinnedBuf(size_t n, Workspace *w) : bytes(n), ws(w)
-{
-    if (ws)
-        p = ws->take_host(n, &bytes);
-    else
-        HUB_HIP(hipHostMalloc(&p, n, hipHostMallocMapped | hipHostMallocCoherent));
-    HUB_HIP(hipHostGetDevicePointer(&dev, p, 0));
-}
-
-PinnedBuf::~PinnedBuf()
-{
-    if (!p)
-        return;
-    if (!ws) {
-        (void)hipHostFree(p);
-        return;
-    }
-    if (std::uncaught_exceptions() > 0)
-        (void)hipDeviceSynchronize();
-    ws->give_host(p, bytes);
-}
-
 static void free_device(hubbard *h)
 {
     h->ws.release();
@@ -232,8 +85,7 @@ static void free_device(hubbard *h)
 template <typename T>
 static T *upload(const void *src, size_t bytes, size_t &total)
 {
-    void *p = nullptr;
-    HUB_HIP(hipMalloc(&p, bytes ? bytes : 16));
+    void *p = device_alloc(bytes ? bytes : 16);
     if (bytes)
         HUB_HIP(hipMemcpy(p, src, bytes, hipMemcpyHostToDevice));
     total += bytes;
@@ -1819,7 +1671,7 @@ static int apply_impl(hubbard_h h, const void *x, int64_t ldx, void *y, int64_t 
                 h->apply_work = nullptr;
                 h->apply_work_bytes = 0;
             }
-            HUB_HIP(hipMalloc(&h->apply_work, need));
+            h->apply_work = device_alloc(need);
             h->apply_work_bytes = need;
         }
         if (!h->apply_ev)

@@ -130,19 +130,23 @@ struct DeviceTables {
 // and hipFree, and 16 ms after some two hundred calls, when the driver no longer
 // keeps up with clearing freed memory (2.9 -> 19.4 ms a solve).  Blocks given
 // back are kept up to kKeepBytes per handle and kKeepAll over all handles of the
-// process, a handle's oldest going first, and freed with the handle.  take() hands out a kept block of at least the size asked
-// for and at most twice that, else allocates (freeing the kept blocks if the
-// device is full).  Safe from several threads; the work that used a block has
-// to be complete when it is given back.
+// process, a handle's oldest going first, and freed with the handle.  take()
+// hands out a kept block of at least the size asked for and at most twice that,
+// else allocates.  Where the device is full, an allocation of the library frees
+// the kept blocks of every handle and tries again.  Safe from several threads;
+// the work that used a block has to be complete when it is given back.
 constexpr size_t kKeepBytes = (size_t)1 << 30, kKeepAll = (size_t)8 << 30;
 class Workspace {
   public:
+    Workspace();
+    Workspace(const Workspace &) = delete;
+    Workspace &operator=(const Workspace &) = delete;
     void *take(size_t bytes, size_t *got);
     void give(void *p, size_t bytes);
     void *take_host(size_t bytes, size_t *got);
     void give_host(void *p, size_t bytes);
     void release();
-    ~Workspace() { release(); }
+    ~Workspace();
 
   private:
     struct Block {
@@ -154,6 +158,13 @@ class Workspace {
     std::vector<Block> dev_, host_;
     size_t held_ = 0;
 };
+
+// Allocations of the library (pinned host memory: mapped and coherent); out of
+// memory, they free what handles keep before they fail.
+void *device_alloc(size_t bytes);
+void *host_alloc(size_t bytes);
+// Frees every handle's kept blocks.
+void release_kept();
 
 // Device buffer, from a handle's workspace or (null) an allocation of its own.
 struct DevBuf {

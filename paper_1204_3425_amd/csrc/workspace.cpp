@@ -1,0 +1,215 @@
+// Device and pinned host memory: the buffers that handles keep between their
+// calls, and the allocations that may take them back.
+#include <algorithm>
+#include <atomic>
+#include <exception>
+#include <mutex>
+#include <vector>
+
+#include "internal.h"
+
+namespace hub {
+
+// bytes kept by all handles of the process
+static std::atomic<size_t> g_kept{0};
+
+// Every workspace alive.  Taken before a workspace's own lock, never inside it.
+struct Registry {
+    std::mutex mu;
+    std::vector<Workspace *> all;
+};
+static Registry &registry()
+{
+    static Registry *r = new Registry;  // outlives handles freed at exit
+    return *r;
+}
+
+Workspace::Workspace()
+{
+    Registry &r = registry();
+    std::lock_guard<std::mutex> lk(r.mu);
+    r.all.push_back(this);
+}
+
+Workspace::~Workspace()
+{
+    {
+        Registry &r = registry();
+        std::lock_guard<std::mutex> lk(r.mu);
+        r.all.erase(std::remove(r.all.begin(), r.all.end(), this), r.all.end());
+    }
+    release();
+}
+
+void release_kept()
+{
+    Registry &r = registry();
+    std::lock_guard<std::mutex> lk(r.mu);
+    for (Workspace *w : r.all)
+        w->release();
+}
+
+static bool out_of_memory(hipError_t e) { return e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation; }
+
+void *device_alloc(size_t bytes)
+{
+    void *p = nullptr;
+    hipError_t e = hipMalloc(&p, bytes);
+    if (out_of_memory(e)) {
+        (void)hipGetLastError();
+        release_kept();
+        e = hipMalloc(&p, bytes);
+    }
+    hip_check(e, "hipMalloc");
+    return p;
+}
+
+void *host_alloc(size_t bytes)
+{
+    const unsigned flags = hipHostMallocMapped | hipHostMallocCoherent;
+    void *p = nullptr;
+    hipError_t e = hipHostMalloc(&p, bytes, flags);
+    if (out_of_memory(e)) {
+        (void)hipGetLastError();
+        release_kept();
+        e = hipHostMalloc(&p, bytes, flags);
+    }
+    hip_check(e, "hipHostMalloc");
+    return p;
+}
+
+void *Workspace::take(size_t bytes, size_t *got)
+{
+    bytes = (std::max<size_t>(bytes, 16) + 65535) / 65536 * 65536;
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        size_t best = dev_.size();
+        for (size_t k = 0; k < dev_.size(); k++)
+            if (dev_[k].bytes >= bytes && dev_[k].bytes <= 2 * bytes &&
+                (best == dev_.size() || dev_[k].bytes < dev_[best].bytes))
+                best = k;
+        if (best < dev_.size()) {
+            const Block b = dev_[best];
+            drop(best);
+            *got = b.bytes;
+            return b.p;
+        }
+    }
+    *got = bytes;
+    return device_alloc(bytes);
+}
+
+void Workspace::drop(size_t k)
+{
+    held_ -= dev_[k].bytes;
+    g_kept -= dev_[k].bytes;
+    dev_.erase(dev_.begin() + (std::ptrdiff_t)k);
+}
+
+void Workspace::give(void *p, size_t bytes)
+{
+    if (bytes > kKeepBytes) {
+        (void)hipFree(p);
+        return;
+    }
+    std::lock_guard<std::mutex> lk(mu_);
+    dev_.push_back(Block{p, bytes});
+    held_ += bytes;
+    g_kept += bytes;
+    while (!dev_.empty() && (held_ > kKeepBytes || g_kept.load() > kKeepAll)) {
+        (void)hipFree(dev_.front().p);
+        drop(0);
+    }
+}
+
+void *Workspace::take_host(size_t bytes, size_t *got)
+{
+    bytes = (bytes + 16383) / 16384 * 16384;
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        for (size_t k = 0; k < host_.size(); k++)
+            if (host_[k].bytes >= bytes) {
+                void *p = host_[k].p;
+                *got = host_[k].bytes;
+                host_.erase(host_.begin() + (std::ptrdiff_t)k);
+                return p;
+            }
+    }
+    *got = bytes;
+    return host_alloc(bytes);
+}
+
+void Workspace::give_host(void *p, size_t bytes)
+{
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        // one or two small blocks serve every call
+        if (host_.size() < 2 && bytes <= (1 << 20)) {
+            host_.push_back(Block{p, bytes});
+            return;
+        }
+    }
+    (void)hipHostFree(p);
+}
+
+void Workspace::release()
+{
+    std::lock_guard<std::mutex> lk(mu_);
+    for (const Block &b : dev_)
+        (void)hipFree(b.p);
+    for (const Block &b : host_)
+        (void)hipHostFree(b.p);
+    g_kept -= held_;
+    dev_.clear();
+    host_.clear();
+    held_ = 0;
+}
+
+DevBuf::DevBuf(size_t n, Workspace *w) : ws(w)
+{
+    if (!n)
+        return;
+    bytes = n;
+    if (ws)
+        p = ws->take(n, &bytes);
+    else
+        p = device_alloc(n);
+}
+
+DevBuf::~DevBuf()
+{
+    if (!p)
+        return;
+    if (!ws) {
+        (void)hipFree(p);
+        return;
+    }
+    // a call that ends in an error may have left work in flight
+    if (std::uncaught_exceptions() > 0)
+        (void)hipDeviceSynchronize();
+    ws->give(p, bytes);
+}
+
+PinnedBuf::PinnedBuf(size_t n, Workspace *w) : bytes(n), ws(w)
+{
+    if (ws)
+        p = ws->take_host(n, &bytes);
+    else
+        p = host_alloc(n);
+    HUB_HIP(hipHostGetDevicePointer(&dev, p, 0));
+}
+
+PinnedBuf::~PinnedBuf()
+{
+    if (!p)
+        return;
+    if (!ws) {
+        (void)hipHostFree(p);
+        return;
+    }
+    if (std::uncaught_exceptions() > 0)
+        (void)hipDeviceSynchronize();
+    ws->give_host(p, bytes);
+}
+
+}  // namespace hub
