@@ -606,54 +606,6 @@ struct LanczosOut {
 // sectors from this size on take the fused Lanczos step
 constexpr int64_t kFusedMinDim = 1 << 16;
 
-// Slots for a resident Lanczos basis, allocated in chunks of kBasisChunk
-// vectors as a run needs them and reusable by the next run of the same call.
-constexpr size_t kBasisChunk = 32;
-struct BasisPool {
-    Workspace *ws = nullptr;
-    std::vector<std::unique_ptr<DevBuf>> chunks;
-    size_t vb = 0;  // bytes per vector
-    // the padding of the rows (bytes pad_off..pitch of each row, rows per vector):
-    // zeroed when a chunk is allocated, since the kernels write only the row
-    // elements and the fix-up of a flagged fused step reads whole padded rows
-    size_t pitch = 0, pad_off = 0;
-    int64_t rows = 0;
-    size_t capacity() const { return chunks.size() * kBasisChunk; }
-    void *slot(size_t j) const { return static_cast<char *>(chunks[j / kBasisChunk]->p) + (j % kBasisChunk) * vb; }
-    // room for vector j within limit (bytes the pool may hold in total); false
-    // when it cannot grow.  Memory from the device leaves 2 GiB of it free.
-    bool reserve(size_t j, size_t limit, hipStream_t s)
-    {
-        const size_t cb = kBasisChunk * vb, spare = (size_t)2 << 30;
-        while (j >= capacity()) {
-            if ((chunks.size() + 1) * cb > limit)
-                return false;
-            if (cb > kKeepBytes || !seen_free || free_left < cb + spare) {
-                // (re)read the free memory; small chunks go by the last reading
-                size_t fr = 0, tot = 0;
-                HUB_HIP(hipMemGetInfo(&fr, &tot));
-                seen_free = true;
-                free_left = fr;
-                if (fr < cb + spare)
-                    return false;
-            }
-            free_left -= cb;
-            try {
-                chunks.emplace_back(new DevBuf(cb, ws));
-            } catch (const Error &) {
-                (void)hipGetLastError();
-                return false;
-            }
-            if (pitch > pad_off)
-                HUB_HIP(hipMemset2DAsync(static_cast<char *>(chunks.back()->p) + pad_off, pitch, 0, pitch - pad_off,
-                                         (size_t)rows * kBasisChunk, s));
-        }
-        return true;
-    }
-    bool seen_free = false;
-    size_t free_left = 0;
-};
-
 // Lower eigenvectors to project out of every Lanczos vector (FP64, dense J
 // order, vector l at psi + l * dim), nd of them.
 struct Deflation {

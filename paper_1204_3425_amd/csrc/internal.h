@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -142,6 +143,7 @@ class Workspace {
     Workspace(const Workspace &) = delete;
     Workspace &operator=(const Workspace &) = delete;
     void *take(size_t bytes, size_t *got);
+    void *take_kept(size_t bytes, size_t *got);  // as take, or null where no kept block fits
     void give(void *p, size_t bytes);
     void *take_host(size_t bytes, size_t *got);
     void give_host(void *p, size_t bytes);
@@ -173,6 +175,7 @@ struct DevBuf {
     Workspace *ws = nullptr;
     DevBuf() = default;
     explicit DevBuf(size_t n, Workspace *w = nullptr);
+    static std::unique_ptr<DevBuf> kept(size_t n, Workspace *w);  // null where w keeps none that fits
     ~DevBuf();
     DevBuf(const DevBuf &) = delete;
     DevBuf &operator=(const DevBuf &) = delete;
@@ -193,6 +196,30 @@ struct PinnedBuf {
     PinnedBuf &operator=(const PinnedBuf &) = delete;
     template <typename T>
     T *as() const { return static_cast<T *>(p); }
+};
+
+// Slots for a resident Lanczos basis, allocated in chunks of kBasisChunk
+// vectors as a run needs them and reusable by the next run of the same call.
+constexpr size_t kBasisChunk = 32;
+struct BasisPool {
+    Workspace *ws = nullptr;
+    std::vector<std::unique_ptr<DevBuf>> chunks;
+    size_t vb = 0;  // bytes per vector
+    // the padding of the rows (bytes pad_off..pitch of each row, rows per vector):
+    // zeroed when a chunk is allocated, since the kernels write only the row
+    // elements and the fix-up of a flagged fused step reads whole padded rows
+    size_t pitch = 0, pad_off = 0;
+    int64_t rows = 0;
+    size_t capacity() const { return chunks.size() * kBasisChunk; }
+    void *slot(size_t j) const { return static_cast<char *>(chunks[j / kBasisChunk]->p) + (j % kBasisChunk) * vb; }
+    // room for vector j within limit (bytes the pool may hold in total); false
+    // when it cannot grow.  A chunk that the handle keeps is taken as it is; memory
+    // from the device leaves 2 GiB of it free, kept buffers counting as free.
+    bool reserve(size_t j, size_t limit, hipStream_t s);
+
+  private:
+    bool seen_free = false;
+    size_t free_left = 0;
 };
 
 }  // namespace hub

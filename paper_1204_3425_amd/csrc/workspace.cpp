@@ -78,25 +78,31 @@ void *host_alloc(size_t bytes)
     return p;
 }
 
+static size_t rounded(size_t bytes) { return (std::max<size_t>(bytes, 16) + 65535) / 65536 * 65536; }
+
+void *Workspace::take_kept(size_t bytes, size_t *got)
+{
+    bytes = rounded(bytes);
+    std::lock_guard<std::mutex> lk(mu_);
+    size_t best = dev_.size();
+    for (size_t k = 0; k < dev_.size(); k++)
+        if (dev_[k].bytes >= bytes && dev_[k].bytes <= 2 * bytes &&
+            (best == dev_.size() || dev_[k].bytes < dev_[best].bytes))
+            best = k;
+    if (best == dev_.size())
+        return nullptr;
+    const Block b = dev_[best];
+    drop(best);
+    *got = b.bytes;
+    return b.p;
+}
+
 void *Workspace::take(size_t bytes, size_t *got)
 {
-    bytes = (std::max<size_t>(bytes, 16) + 65535) / 65536 * 65536;
-    {
-        std::lock_guard<std::mutex> lk(mu_);
-        size_t best = dev_.size();
-        for (size_t k = 0; k < dev_.size(); k++)
-            if (dev_[k].bytes >= bytes && dev_[k].bytes <= 2 * bytes &&
-                (best == dev_.size() || dev_[k].bytes < dev_[best].bytes))
-                best = k;
-        if (best < dev_.size()) {
-            const Block b = dev_[best];
-            drop(best);
-            *got = b.bytes;
-            return b.p;
-        }
-    }
-    *got = bytes;
-    return device_alloc(bytes);
+    if (void *p = take_kept(bytes, got))
+        return p;
+    *got = rounded(bytes);
+    return device_alloc(*got);
 }
 
 void Workspace::drop(size_t k)
@@ -176,6 +182,17 @@ DevBuf::DevBuf(size_t n, Workspace *w) : ws(w)
         p = device_alloc(n);
 }
 
+std::unique_ptr<DevBuf> DevBuf::kept(size_t n, Workspace *w)
+{
+    std::unique_ptr<DevBuf> b(new DevBuf());
+    b->ws = w;
+    if (w)
+        b->p = w->take_kept(n, &b->bytes);
+    if (!b->p)
+        b.reset();
+    return b;
+}
+
 DevBuf::~DevBuf()
 {
     if (!p)
@@ -210,6 +227,43 @@ PinnedBuf::~PinnedBuf()
     if (std::uncaught_exceptions() > 0)
         (void)hipDeviceSynchronize();
     ws->give_host(p, bytes);
+}
+
+bool BasisPool::reserve(size_t j, size_t limit, hipStream_t s)
+{
+    const size_t cb = kBasisChunk * vb, spare = (size_t)2 << 30;
+    auto read_free = [&] {
+        size_t fr = 0, tot = 0;
+        HUB_HIP(hipMemGetInfo(&fr, &tot));
+        seen_free = true;
+        free_left = fr;
+        return fr >= cb + spare;
+    };
+    while (j >= capacity()) {
+        if ((chunks.size() + 1) * cb > limit)
+            return false;
+        std::unique_ptr<DevBuf> c = DevBuf::kept(cb, ws);
+        if (!c) {
+            // (re)read the free memory; small chunks go by the last reading
+            if ((cb > kKeepBytes || !seen_free || free_left < cb + spare) && !read_free()) {
+                release_kept();
+                if (!read_free())
+                    return false;
+            }
+            free_left -= cb;
+            try {
+                c.reset(new DevBuf(cb, ws));
+            } catch (const Error &) {
+                (void)hipGetLastError();
+                return false;
+            }
+        }
+        chunks.push_back(std::move(c));
+        if (pitch > pad_off)
+            HUB_HIP(hipMemset2DAsync(static_cast<char *>(chunks.back()->p) + pad_off, pitch, 0, pitch - pad_off,
+                                     (size_t)rows * kBasisChunk, s));
+    }
+    return true;
 }
 
 }  // namespace hub

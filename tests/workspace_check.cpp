@@ -150,10 +150,45 @@ static void threads()
     need(used == 0 && live.empty(), "everything is freed");
 }
 
+// a resident basis grows on what its handle keeps, and on what others do, where
+// the device itself has less than a chunk and the 2 GiB left free
+static void basis()
+{
+    constexpr size_t G = (size_t)1 << 30;
+    capacity = 3 * G;
+    Workspace a, b;
+    auto grow = [&](size_t vectors, size_t vb, size_t limit) {
+        BasisPool p;
+        p.ws = &a;
+        p.vb = vb;
+        p.pitch = p.pad_off = vb;
+        p.rows = 1;
+        for (size_t j = 0; j < vectors; j++)
+            if (!p.reserve(j, limit, nullptr))
+                return j;
+        return vectors;
+    };
+    const size_t vb = 16 * M, chunk = kBasisChunk * vb;  // chunks of 512 MiB: two fit
+    need(grow(200, vb, 10 * G) == 64, "two chunks, then less than 2 GiB would be left");
+    need(used == 2 * chunk, "both are kept");
+    void *outside = device_alloc(G + 3 * G / 4);  // another program's memory: 256 MiB left
+    need(grow(200, vb, 10 * G) == 64, "the kept chunks serve the next run");
+    need(grow(200, vb, chunk + 1) == 32, "within the handle's limit");
+    (void)hipFree(outside);
+    a.release();
+    { DevBuf x(G, &b); }  // another handle's kept gigabyte
+    need(grow(200, vb, 10 * G) == 64, "counts as free");
+    a.release();
+    outside = device_alloc(G);
+    need(grow(200, vb, 10 * G) == 0, "no kept chunk, less than 2 GiB beside one");
+    (void)hipFree(outside);
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> all = {
-        {"others_make_room", others_make_room}, {"lifetimes", lifetimes}, {"threads", threads}};
+        {"others_make_room", others_make_room}, {"lifetimes", lifetimes}, {"threads", threads},
+        {"basis", basis}};
     need(argc == 2 && all.count(argv[1]), "a check's name");
     all.at(argv[1])();
     std::printf("ok\n");
