@@ -96,8 +96,6 @@ static T *upload(const void *src, size_t bytes, size_t &total)
 // of low sites such that rows sharing the occupation of sites p.. form blocks
 // of at most kMaxBlockRows rows (configurations in ascending order keep each
 // block contiguous).
-constexpr int kMaxBlockRows = 1024;
-
 static void upload_blocked_up(hubbard *h, size_t &total)
 {
     DeviceTables &d = h->dev;
@@ -264,11 +262,6 @@ static void upload_blocked_up(hubbard *h, size_t &total)
 // for per-bond handles the down entries in slots of one amplitude: class c
 // takes as many slots as the column with most hops of that class needs.
 constexpr int64_t kMaxTileRow = 32767;  // 16-bit entries
-// Sectors up to this size (and rows of at most 64 KB in FP64) take the
-// one-launch form in every call and precision; the server batches them.
-constexpr int64_t kTileOnlyDim = 16000000;
-static_assert(kTileOnlyDim * 8 <= kTileStepBytes && kTileOnlyDim * 8 <= kTileMaxBytes, "");
-
 static void upload_tile(hubbard *h, const std::vector<uint32_t> &rows, size_t &total)
 {
     DeviceTables &d = h->dev;
@@ -369,7 +362,7 @@ static void upload_tables(hubbard *h)
     // Sectors whose every call takes the one-launch form need no two-pass tables
     // (a server's run of a larger sector takes the two-pass form).
     const int64_t ddn = h->dn.dim;
-    d.tile_only = d.up_tile && h->dim <= kTileOnlyDim && ddn * 8 <= 64 * 1024;
+    d.tile_only = d.up_tile && tile_only_sector((long double)h->dim, (uint64_t)ddn);
     const bool tile_only = d.tile_only;
     // class bits of an entry of the down table (per-bond handles)
     auto dn_cls = [&](size_t src) -> uint32_t { return gen ? (uint32_t)h->bond_cls[h->dn.bond[src]] : 0u; };

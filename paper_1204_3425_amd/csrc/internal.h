@@ -53,6 +53,7 @@ constexpr int kTwoPassClasses = 4;
 // longest row the FP64 row pass stages in LDS (plus one zero slot: 160 KB)
 constexpr int kRow64Max = 20000;
 
+constexpr int kMaxBlockRows = 1024;  // rows of a block of the up-spin pass at most
 constexpr int kClsGroups = 4;  // row pass by class: groups of eight per class and column at most
 
 struct DeviceTables {
@@ -391,6 +392,14 @@ constexpr int64_t kTileMaxBytes = (int64_t)192 << 20;
 // 17.4, 3x4 6u6d 48.4 / 29.1, 14-site ring 180 / 162, 4x4 5u5d (19 M, 153 MB) 415 /
 // 384, 4x4 8u4d (187 MB) 429 / 503; FP32 14-site ring 114 / 98, 4x4 8u4d 264 / 242.
 constexpr int64_t kTileStepBytes = (int64_t)160 << 20;
+// Sectors up to this size (and rows of at most 64 KB in FP64) take the
+// one-launch form in every call and precision; the server batches them.
+constexpr int64_t kTileOnlyDim = 16000000;
+static_assert(kTileOnlyDim * 8 <= kTileStepBytes && kTileOnlyDim * 8 <= kTileMaxBytes, "");
+inline bool tile_only_sector(long double dim, uint64_t dim_dn)
+{
+    return dim <= (long double)kTileOnlyDim && dim_dn * 8 <= 64 * 1024;
+}
 struct TilePlan {
     bool ok = false;
     int threads = 64, grid = 8, nseg = 1, span = 64;

@@ -38,26 +38,61 @@ struct Job {
     hubbard_completion done{};
 };
 
+// Largest sector of the batched executor.
+constexpr int64_t kBatchDim = 16 * 1024 * 1024;
+
+// Row blocks of the up-spin pass (see upload_blocked_up): rows of equal
+// occupation of the sites from p on, p the largest with blocks of at most
+// kMaxBlockRows rows.
+uint64_t up_row_blocks(int sites, int n)
+{
+    for (int p = sites;; p--) {
+        uint64_t longest = 0, blocks = 0;
+        for (int low = std::max(0, n - (sites - p)); low <= std::min(p, n); low++) {
+            longest = std::max(longest, binomial(p, low));
+            blocks += binomial(sites - p, n - low);
+        }
+        if (longest <= (uint64_t)kMaxBlockRows)
+            return blocks;
+    }
+}
+
 // Upper bound of the device bytes a request needs: the two work vectors on
-// padded rows, partial sums, the batched engine's coefficient history, and the
-// tables with at most n_edges entries per row: up side (row-major entries,
-// blocked entries, the entry lines: up to two 128-byte lines per row when a
-// row has at most 64 hops (one when 32 slots hold the row and its padding),
-// none beyond; counts, states)
-// and down side (column-major entries, 64- and 32-bit offset groups, 16-bit
-// groups, counts, states, and the FP64 row pass's 16-bit indices split by
-// sign: at most w/8 groups of eight + hops and w/4 groups of four - hops).
+// padded rows (on 64 elements each, dense, in the batched engine), the
+// coefficient history, partial sums and work items, and the tables with at most
+// n_edges entries per row: up side (row-major entries; slots of the one-launch
+// H.v and the batched engine, eight to a group; counts, states, block starts)
+// and down side (column-major entries, 16-bit groups, the same again with signs
+// in the index where rows are short, counts, states).  Sectors that take the
+// one-launch form in every call have no more than that.  Others have the
+// two-pass tables as well: up-spin entry lines (up to two 128-byte lines per row
+// when a row has at most 64 hops, else the entries by block), 64- and 32-bit
+// offset groups, and the FP64 row pass's 16-bit indices split by sign (at most
+// w/8 groups of eight + hops and w/4 groups of four - hops).
 size_t footprint(const hubbard_request &r)
 {
     const uint64_t du = binomial(r.sites, r.n_up), dd = binomial(r.sites, r.n_dn);
     const size_t es = r.precision == HUBBARD_FP64 ? 8 : 4;
     const size_t ld = (size_t)((dd + 63) / 64 * 64);
-    const size_t vecs = 2 * es * (size_t)du * ld + 64 * 1024 + 16 * (size_t)std::max(1, r.max_iter);
-    const size_t w = (size_t)std::max(1, r.n_edges);
-    const size_t lines = w <= 64 ? 256 : 0;  // one or two 128-byte lines
-    const size_t up = (size_t)du * (8 * w + 14 + lines);
+    const size_t w = (size_t)std::max(1, r.n_edges), w8 = (w + 7) / 8 * 8;
     const size_t g8 = (w + 7) / 8, g4 = (w + 3) / 4;  // groups of eight or four entries per column
-    const size_t dn = (size_t)dd * (14 * w + 56 + 16 * g8 + 16 * g8 + 8 * g4 + 1);
+    size_t vecs = 2 * es * (size_t)du * ld + 64 * 1024 + 16 * (size_t)std::max(1, r.max_iter);
+    size_t up = (size_t)du * (4 * w + 4 * w8 + 6);
+    size_t dn = (size_t)dd * (4 * w + 8 + 16 * g8 + (dd <= 2048 ? 16 * g8 : 0));
+    const long double dim = (long double)du * (long double)dd;
+    // batched: items of whole rows, a row or more than 1,024 elements each, and
+    // of 8,192 elements, in a table with room for twice as many, a partial sum each
+    if (dim <= (long double)kBatchDim)
+        vecs += 64 * std::min((size_t)du, (size_t)dim / 1024 + 1) + (size_t)dim / 64;
+    if (!tile_only_sector(dim, dd)) {
+        // partial sums of the largest launch of either pass, or one per row
+        const size_t slabs = (size_t)((dd + 15) / 16);
+        const size_t blocks = 8 * ((slabs + 7) / 8) * (size_t)up_row_blocks(r.sites, r.n_up);
+        const size_t tall = 8 * (256 + 3 * (size_t)du * (4 * w + 4) / (48 * 1024));
+        vecs += 8 * (size_t)(3 + 2 * kFusedDefl) * std::max({blocks, tall, (size_t)2048}) + 8 * (size_t)du;
+        up += (size_t)du * (8 + (w <= 64 ? 256 : 4 * w));
+        dn += (size_t)dd * (2 * 16 * g4 + 16 * g8 + 8 * g4 + 8);
+    }
     return vecs + up + dn;
 }
 
@@ -159,7 +194,7 @@ void build_loop(hubbard_server *S)
             continue;
         }
         job->h = h;
-        job->batch = batchable(h, r.precision) && h->dim <= (int64_t)16 * 1024 * 1024;
+        job->batch = batchable(h, r.precision) && h->dim <= kBatchDim;
         std::lock_guard<std::mutex> lk(S->mu);
         (job->batch ? S->ready_batch : S->ready_solo).push_back(std::move(job));
         S->cv.notify_all();

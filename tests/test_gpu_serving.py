@@ -112,3 +112,35 @@ def test_server_rejects_malformed_requests():
     with pytest.raises(hb.HubbardError):
         hb.hubbard_server_submit(srv, 4, workload.ring(4), 2, 2, max_iter=0)
     hb.hubbard_server_destroy(srv)
+
+
+BIPARTITE = [(i, 10 + j) for i in range(10) for j in range(10)]
+FOOTPRINTS = [
+    # sites, edges, n_up, n_dn
+    (8, workload.ring(8), 4, 4),
+    (12, workload.ring(12), 6, 6),               # one-launch tables
+    (12, workload.torus(3, 4), 6, 0),            # one column
+    (11, [(i, j) for i in range(11) for j in range(i)], 5, 6),  # rows of 30 hops, 55 edges
+    (20, BIPARTITE, 10, 1),                      # up rows of 100 hops, one-launch tables
+    (20, BIPARTITE, 10, 2),                      # 35 million states: two-pass tables, up rows of 100 hops
+    (16, workload.torus(4, 4), 5, 7),            # 50 million states: two-pass tables, entry lines
+]
+
+
+@pytest.mark.parametrize("precision", [hb.HUBBARD_FP64, hb.HUBBARD_MIXED], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("n,edges,nu,nd", FOOTPRINTS)
+def test_server_footprint_bounds_the_tables_and_vectors(n, edges, nu, nd, precision):
+    """The bytes reserved for a request are at least those of its handle's tables
+    and the two work vectors (dense, the least any executor takes) together, and
+    no more than three times that and 1 MiB."""
+    print("footprint", n, len(edges), nu, nd, precision, flush=True)
+    h = hb.hubbard_build(n, edges, nu, nd, 1.0, 2.0)
+    need = hb.hubbard_info(h)["device_bytes"] + 2 * (8 if precision == hb.HUBBARD_FP64 else 4) * h.dim
+    del h
+    srv = hb.hubbard_server_create(16 << 30, 1)
+    hb.hubbard_server_submit(srv, n, edges, nu, nd, 1.0, 2.0, tol=-1.0, max_iter=2, precision=precision)
+    (res,) = _collect(srv, 1).values()
+    st = hb.hubbard_server_stats(srv)
+    hb.hubbard_server_destroy(srv)
+    assert res["status"] == hb.HUBBARD_OK
+    assert need <= st["peak_reserved"] <= 3 * need + (1 << 20), (need, st["peak_reserved"])
