@@ -625,26 +625,41 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
     // and the update (TileStep), with the scalars formed inside them.
     const TilePlan tplan = make_tile_plan(args, sizeof(T));
     const TilePlan tplan64 = make_tile_plan(args, sizeof(double));
-    const bool tile = tplan.ok && tile_steps(args, sizeof(T)) && (!two_vectors || h->dev.tile_only);
+    bool tile = tplan.ok && tile_steps(args, sizeof(T)) && (!two_vectors || h->dev.tile_only);
+    // Work vectors: two (three in the one-launch form), or with psi requested the
+    // two padded vectors of the FP64 residual if those are more.  Vectors beyond
+    // the Infinity Cache (handles of many amplitude classes) are allocated at once,
+    // and where three do not fit the device the run takes the one-pass step's two.
+    std::unique_ptr<DevBuf> work;
+    auto alloc_work = [&](int64_t stride) {
+        work.reset(new DevBuf(std::max((tile ? 3 : 2) * sizeof(T), o.psi && !tplan64.ok ? (size_t)16 : (size_t)0) *
+                                  (size_t)h->up.dim * (size_t)stride,
+                              &h->ws));
+    };
+    const int64_t ld_tile = (h->dn.dim + 63) / 64 * 64;
+    if (tile && n * (int64_t)sizeof(T) > kTileStepBytes) {
+        try {
+            alloc_work(ld_tile);
+        } catch (const Error &e) {
+            if (e.code != HUBBARD_ENOMEM)
+                throw;
+            (void)hipGetLastError();
+            tile = false;
+        }
+    }
     // padded row stride of the work vectors
-    const int64_t ld = tile ? (h->dn.dim + 63) / 64 * 64 : plan.ld;
+    const int64_t ld = tile ? ld_tile : plan.ld;
     const int64_t npad = h->up.dim * ld;
     const int hb = plan.nparts;
     const int sb = stream_blocks(npad);
     const int max_iter = o.max_iter;
 
-    // one allocation for both work vectors (three in the one-launch form);
-    // after the replay it is reused as the FP64 scratch of the residual
-    // (2 * npad * sizeof(T) >= npad * 8 bytes); with psi requested it also holds
-    // the FP64 residual's two padded vectors
-    std::unique_ptr<DevBuf> work;
+    // after the replay the work vectors are reused as the FP64 scratch of the
+    // residual (2 * npad * sizeof(T) >= npad * 8 bytes)
     T *vecs[3] = {nullptr, nullptr, nullptr};
     auto need_work = [&] {
-        if (work)
-            return;
-        work.reset(new DevBuf(std::max((tile ? 3 : 2) * sizeof(T), o.psi && !tplan64.ok ? (size_t)16 : (size_t)0) *
-                                  (size_t)npad,
-                              &h->ws));
+        if (!work)
+            alloc_work(ld);
         for (int k = 0; k < (tile ? 3 : 2); k++)
             vecs[k] = work->as<T>() + k * npad;
     };
@@ -869,7 +884,7 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
     // costs no copy.  When the pool cannot grow, the two live vectors move to
     // the work vectors and the run goes on as without psi (psi by replay).
     bool inslot = resident && (tile || (fused && args.up_line)) && pool.reserve(1, basis_budget, s);
-    if (!inslot || !tile)
+    if (!inslot || !tile || work)
         need_work();
     auto slotp = [&](int j) { return static_cast<T *>(pool.slot((size_t)j)); };
     T *bufs[3] = {vecs[0], vecs[1], vecs[2]};

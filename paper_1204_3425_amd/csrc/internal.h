@@ -385,12 +385,16 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
 // 4x4 8u4d (23.4 M) 390 / 342, 4x4 6u5d (35 M, 280 MB) 551 / 547, 4x4 6u6d (64 M)
 // 1076 / 1224; FP32 14-site ring 96 / 60, 4x4 6u5d 326 / 273, 6u6d 598 / 625.
 // Handles of more than four amplitude classes have no two-pass form and take it
-// at any size where a row fits in LDS.
+// at any size where a row fits in LDS (a class per bond, apply, one-pass kernel /
+// one launch in us: FP64 4x4 6u6d, 513 MB, 2530 / 1420, 4x4 8u8d, 1.3 GB, 7720 / 4180,
+// 16-site ring 8u8d 4260 / 2420; FP32 2130 / 720, 6460 / 2310, 3740 / 1260).
 constexpr int64_t kTileMaxBytes = (int64_t)192 << 20;
 // Lanczos steps (vectors of one H.v, two launches a step against the fused
 // two-pass step's five; us a step, fused / one-launch form): FP64 3x4 4u4d 30.3 /
 // 17.4, 3x4 6u6d 48.4 / 29.1, 14-site ring 180 / 162, 4x4 5u5d (19 M, 153 MB) 415 /
 // 384, 4x4 8u4d (187 MB) 429 / 503; FP32 14-site ring 114 / 98, 4x4 8u4d 264 / 242.
+// More than four classes again at any size: FP64 4x4 6u6d 3040 / 1700, 8u8d 9080 /
+// 5090, FP32 2410 / 1060 and 7210 / 3230; three vectors to the one-pass step's two.
 constexpr int64_t kTileStepBytes = (int64_t)160 << 20;
 // Sectors up to this size (and rows of at most 64 KB in FP64) take the
 // one-launch form in every call and precision; the server batches them.

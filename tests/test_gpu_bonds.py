@@ -225,3 +225,35 @@ def test_per_bond_up_rows_over_64_hops():
     r = hb.hubbard_lanczos_ex(h, tol=-1.0, max_iter=20, precision=hb.HUBBARD_FP64, seed=workload.BASE_SEED)
     assert np.allclose(r["a"], ro["a"], rtol=1e-12, atol=1e-12)
     assert np.allclose(r["b"], ro["b"], rtol=1e-10, atol=1e-12)
+
+
+def test_many_classes_where_three_vectors_do_not_fit():
+    """An amplitude per bond on 35 million states (280 MB vectors): with room for two
+    and a half vectors left on the device the run takes the step on two vectors;
+    its coefficients are those of the three-vector step to the rounding of a dot
+    product over dim terms (64 sqrt(dim) eps of |H|)."""
+    edges = workload.torus(4, 4)
+    amps = np.random.default_rng(4).uniform(0.5, 1.5, len(edges)).tolist()
+    _say("35M states, an amplitude per bond, a nearly full device")
+    # the one-pass step once on a small sector
+    ring = workload.ring(24)
+    small = hb.hubbard_build_bonds(24, ring, np.linspace(0.5, 1.5, 24).tolist(), 1, 1, 2.0)
+    hb.hubbard_lanczos_ex(small, tol=-1.0, max_iter=4)
+    h = hb.hubbard_build_bonds(16, edges, amps, 6, 5, 3.0)
+    want = hb.hubbard_lanczos_ex(h, tol=-1.0, max_iter=6, seed=3)
+    hb.hubbard_free(h)
+    h = hb.hubbard_build_bonds(16, edges, amps, 6, 5, 3.0)
+    left, fill = 5 * h.dim * 8 // 2, []
+    torch.cuda.empty_cache()
+    while True:
+        free = torch.cuda.mem_get_info()[0]
+        if free <= left + (4 << 20):
+            break
+        fill.append(torch.empty(min(free - left, 32 << 30), dtype=torch.uint8, device=DEV))
+    _say("left", torch.cuda.mem_get_info()[0] >> 20, "MiB")
+    got = hb.hubbard_lanczos_ex(h, tol=-1.0, max_iter=6, seed=3)
+    del fill
+    torch.cuda.empty_cache()
+    scale = np.abs(want["a"]).max() + want["b"].max()
+    tol = 64 * np.sqrt(h.dim) * np.finfo(float).eps * scale
+    assert np.abs(got["a"] - want["a"]).max() <= tol and np.abs(got["b"] - want["b"]).max() <= tol
