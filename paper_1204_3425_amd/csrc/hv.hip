@@ -87,7 +87,10 @@ __device__ inline double flip_sign(double v, uint32_t sg)
 
 // The row passes stream the vectors (x read once, the result written once) past
 // the L2, which then keeps the entry tables that every row reads again: 4x4 FP64,
-// 8 + 8, store 1303 -> 1230 us, fused step 1602 -> 1505 us.  The fused step's y
+// 8 + 8, store 1303 -> 1230 us, fused step 1602 -> 1505 us (hv_rows64_kernel); whole
+// H.v and fused step of the shorter rows that hv_rows_kernel takes, 8 + 6 1433 ->
+// 1397 and 1752 -> 1711 us, 6 + 5 556 -> 541 and 672 -> 662, three classes 8 + 6
+// 3332 -> 3252 and 3582 -> 3548, in FP32 1837 -> 1787 and 1982 -> 1963.  The fused step's y
 // is read twice, staged and at its column, and goes through the L2.  (FP32 pairs of
 // rows gain nothing and go through it: store 600 -> 585 us but 12 us more in the
 // up-spin pass that reads the result next, fused step 685 -> 695 us.)
@@ -1857,8 +1860,9 @@ HvPlan make_hv_plan(const HvArgs &a, int elem_bytes)
     pl.elem_bytes = elem_bytes;
     const int64_t ddn = a.dim_dn;
     const size_t one_row = (size_t)(ddn + 1) * (size_t)elem_bytes;
-    // per-bond amplitudes with more than four classes run the one-pass kernel:
-    // the two-pass tables have room for two class bits
+    // per-bond amplitudes with more than four classes have no two-pass form (its
+    // tables have room for two class bits): the one-launch form where its plan
+    // takes them, else the one-pass kernel
     pl.two_pass = one_row <= (size_t)kLdsBytes && (!a.tcls || a.ncls <= kTwoPassClasses);
     if (!pl.two_pass) {
         pl.ld = ddn;
