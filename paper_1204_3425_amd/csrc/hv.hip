@@ -1251,6 +1251,17 @@ __global__ __launch_bounds__(kSlabThreads) void hv_slabs_kernel(SlabArgs p, cons
 }
 
 
+// First slab of an XCD's contiguous range.  FP64: ranges as equal as they can be
+// (4x4, 6 + 5, 273 slabs: H.v 532 us and step 674, 535 and 680 with the last XCD
+// taking the remainder; other sectors even).  FP32: 1/8 rounded up, the last XCD
+// the remainder (4x4 dense, 8 + 8, 7 + 7 and 6 + 6: 1496, 1081 and 600 us against
+// 1510, 1094 and 606).
+template <typename T>
+__device__ inline int first_slab(int nslab, int xcd)
+{
+    return sizeof(T) == 8 ? nslab * xcd / 8 : min((nslab + 7) / 8 * xcd, nslab);
+}
+
 struct BlockArgs {
     const uint32_t *__restrict__ ent;    // per row: block-local internal hops, then external rows
     const uint16_t *__restrict__ nint;
@@ -1305,8 +1316,8 @@ __global__ __launch_bounds__(1024) void hv_blocks_kernel(BlockArgs p, const T *_
     const int xcd = blockIdx.x & 7;
     const int local = blockIdx.x >> 3;
     // slab-major per XCD: the k-th contiguous range of slabs, or slabs k, k + 8, ...
-    const int s = p.contig ? p.nslab * xcd / 8 + local / p.nblocks : (local / p.nblocks) * 8 + xcd;
-    const int s_end = p.contig ? p.nslab * (xcd + 1) / 8 : p.nslab;
+    const int s = p.contig ? first_slab<T>(p.nslab, xcd) + local / p.nblocks : (local / p.nblocks) * 8 + xcd;
+    const int s_end = p.contig ? first_slab<T>(p.nslab, xcd + 1) : p.nslab;
     const int blk = local % p.nblocks;
     double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
     if (s < s_end) {
@@ -1540,8 +1551,8 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
     const int local = bid >> 3;
     // slab-major per XCD: XCD k takes the k-th contiguous range of slabs, or slabs
     // k, k + 8, ...
-    const int s = p.contig ? p.nslab * xcd / 8 + local / p.nblocks : (local / p.nblocks) * 8 + xcd;
-    const int s_end = p.contig ? p.nslab * (xcd + 1) / 8 : p.nslab;
+    const int s = p.contig ? first_slab<T>(p.nslab, xcd) + local / p.nblocks : (local / p.nblocks) * 8 + xcd;
+    const int s_end = p.contig ? first_slab<T>(p.nslab, xcd + 1) : p.nslab;
     const int blk = local % p.nblocks;
     double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
     if (s < s_end) {
