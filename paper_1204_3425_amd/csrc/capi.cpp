@@ -262,6 +262,12 @@ static void upload_blocked_up(hubbard *h, size_t &total)
 // for per-bond handles the down entries in slots of one amplitude: class c
 // takes as many slots as the column with most hops of that class needs.
 constexpr int64_t kMaxTileRow = 32767;  // 16-bit entries
+static SectorShape shape_of(const hubbard *h)
+{
+    return SectorShape{h->up.dim, h->dn.dim, (double)h->up.nnz / (double)h->up.dim,
+                       (double)h->dn.nnz / (double)h->dn.dim, (int)h->tcls.size()};
+}
+
 static void upload_tile(hubbard *h, const std::vector<uint32_t> &rows, size_t &total)
 {
     DeviceTables &d = h->dev;
@@ -362,7 +368,7 @@ static void upload_tables(hubbard *h)
     // Sectors whose every call takes the one-launch form need no two-pass tables
     // (a server's run of a larger sector takes the two-pass form).
     const int64_t ddn = h->dn.dim;
-    d.tile_only = d.up_tile && tile_only_sector((long double)h->dim, (uint64_t)ddn);
+    d.tile_only = d.up_tile && tile_only_sector(shape_of(h));
     const bool tile_only = d.tile_only;
     // class bits of an entry of the down table (per-bond handles)
     auto dn_cls = [&](size_t src) -> uint32_t { return gen ? (uint32_t)h->bond_cls[h->dn.bond[src]] : 0u; };
@@ -559,6 +565,9 @@ static HvArgs hv_args(const hubbard *h)
     a.w_dn = h->dn.width;
     a.t = h->t;
     a.U = h->U;
+    const SectorShape sh = shape_of(h);
+    a.hops_up = sh.hu;
+    a.hops_dn = sh.hd;
     // the power of two at or below the largest coupling, within what a double's
     // inverse can hold
     double big = std::fabs(h->U);
@@ -606,10 +615,16 @@ struct Deflation {
     int nd = 0;
 };
 
+static SectorShape shape_of(const HvArgs &a)
+{
+    return SectorShape{a.dim_up, a.dim_dn, a.hops_up, a.hops_dn, a.ncls};
+}
+
 // whether Lanczos steps take the one-launch form where its plan allows it
 static bool tile_steps(const HvArgs &a, int elem_bytes)
 {
-    return a.dim_up * a.dim_dn * elem_bytes <= kTileStepBytes || (a.tcls && a.ncls > kTwoPassClasses);
+    return (a.dim_up * a.dim_dn * elem_bytes <= kTileStepBytes || (a.tcls && a.ncls > kTwoPassClasses)) &&
+           !two_pass_better(shape_of(a), elem_bytes, false);
 }
 
 template <typename T>
@@ -1608,7 +1623,9 @@ static int apply_impl(hubbard_h h, const void *x, int64_t ldx, void *y, int64_t 
     if (!pl.two_pass && (ldx != ddn || ldy != ddn))
         fail(HUBBARD_EINVAL, "rows too wide for the staged kernels: only dense rows (ld = dim_dn) are supported");
     const TilePlan tp = make_tile_plan(a, (int)es);
-    if (tp.ok) {
+    const int64_t slw = 128 / (int64_t)es;
+    const bool dense = ldx % slw != 0 || ldy % slw != 0;
+    if (tp.ok && !two_pass_better(shape_of(a), (int)es, dense)) {
         if (h->precision == HUBBARD_FP64)
             launch_hv_tile<double>(a, tp, static_cast<const double *>(x), ldx, static_cast<double *>(y), ldy, HV_STORE,
                                    0.0, nullptr, h->stream);
@@ -1619,9 +1636,8 @@ static int apply_impl(hubbard_h h, const void *x, int64_t ldx, void *y, int64_t 
     }
     // rows not on 128 bytes: the H.v routes through two padded work vectors
     // (the row pass writes them, the up-spin pass reads them and writes y)
-    const int64_t slw = 128 / (int64_t)es;
     void *wx = nullptr, *wy = nullptr;
-    if (pl.two_pass && pl.blk_grid > 0 && a.up_line && (ldx % slw != 0 || ldy % slw != 0)) {
+    if (pl.two_pass && pl.blk_grid > 0 && a.up_line && dense) {
         const size_t npad = (size_t)h->up.dim * (size_t)pl.ld;
         const size_t need = 2 * npad * es;
         if (h->apply_work_bytes < need) {

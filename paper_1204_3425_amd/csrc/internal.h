@@ -308,6 +308,7 @@ struct HvArgs {
     const double *dn_slot_amp = nullptr;
     const uint8_t *dn_slot_nq = nullptr;
     int dn_slot_groups = 0;
+    double hops_up = 0.0, hops_dn = 0.0;  // mean hops of a row
     // a power of two near 1 / max(|t|, |U|), and its inverse (see TileStep)
     double qscale = 1.0, qunscale = 1.0;
 };
@@ -396,13 +397,62 @@ constexpr int64_t kTileMaxBytes = (int64_t)192 << 20;
 // More than four classes again at any size: FP64 4x4 6u6d 3040 / 1700, 8u8d 9080 /
 // 5090, FP32 2410 / 1060 and 7210 / 3230; three vectors to the one-pass step's two.
 constexpr int64_t kTileStepBytes = (int64_t)160 << 20;
+// Sectors within those sizes whose steps (and products on rows on 128 bytes), or
+// products on other rows (dense), the two-pass form is faster with.  What the
+// one-launch form spends is the up-spin rows it reads again, the vector's bytes
+// times its mean hops hu; what the two-pass form is good at depends on the rows and
+// the precision.  Two-pass / one launch, us:
+//   FP64, one amplitude, du >= dd: beyond 2,200 MB * hops steps lose (3x5 7u5d, 2,359:
+//     279 / 308; 4x4 7u4d, 2,669: 391 / 432; with diagonals 7u4d, 5,337: 520 / 649),
+//     below they gain (4x4 6u4d, 1,779: 292 / 280; 3x6 6u3d, 1,958: 296 / 239); dense
+//     products lose beyond 5,000 (diagonals 7u4d 461 / 506, 6u4d, 3,558: 347 / 332).  With
+//     du < dd they do not (diagonals 4u7d, 4,067: 615 / 577)
+//   FP32, one amplitude, rows of 4,096 and more: steps beyond 1,400 (3x5 6u6d, 1,474: 240 /
+//     258; 7u7d, 2,527: 390 / 456; 16-site ring 6u5d, 1,067: 281 / 250); with many
+//     down-spin hops (hd >= 24: diagonals) du >= dd beyond 2,400 in both kinds (8u4d, 3,050:
+//     326 / 377, dense 265 / 314; 6u4d, 1,779: 247 / 231)
+//   FP32, two classes: steps beyond 2,300 (3x5 7u5d, 2,359: 341 / 372; 4x4 4u8d, 2,287: 585 /
+//     512), dense products beyond 3,900; three and four classes: steps beyond 3,000
+//   one row to a CU and few of them (11,000 <= dd <= 13,312, 256 < du < 1,024) with many
+//     hops: 4x4 3u7d FP64, product on its rows 89 / 97; diagonals 3u7d 148 / 168; two
+//     classes 3u8d FP32 150 / 173 a step (two classes FP64, 3u8d: 262 / 216)
+struct SectorShape {
+    int64_t du = 0, dd = 0;
+    double hu = 0.0, hd = 0.0;  // mean hops of an up and a down row
+    int ncls = 0;               // amplitude classes (0: one amplitude)
+};
+inline bool two_pass_better(const SectorShape &s, int elem_bytes, bool dense)
+{
+    if (s.ncls > kTwoPassClasses)
+        return false;
+    const bool fp32 = elem_bytes == 4, diag = s.hd >= 24.0;
+    const double read = (double)s.du * (double)s.dd * elem_bytes / (1 << 20) * s.hu;
+    if (s.du > 256 && s.du < 1024 && s.dd >= 11000 && s.dd <= 13312 && s.hu + s.hd >= 24.0 && (fp32 || s.ncls == 0))
+        return diag || !dense;
+    if (!fp32)
+        return s.ncls == 0 && s.du >= s.dd && read > (dense ? 5000.0 : 2200.0);
+    if (s.ncls > 2)
+        return !dense && read > 3000.0;
+    if (s.ncls == 2)
+        return read > (dense ? 3900.0 : 2300.0);
+    if (diag)
+        return s.du >= s.dd && read > 2400.0;
+    return !dense && s.dd >= 4096 && read > 1400.0;
+}
 // Sectors up to this size (and rows of at most 64 KB in FP64) take the
-// one-launch form in every call and precision; the server batches them.
+// one-launch form in every call and precision, but for those above; the server
+// batches them.
 constexpr int64_t kTileOnlyDim = 16000000;
 static_assert(kTileOnlyDim * 8 <= kTileStepBytes && kTileOnlyDim * 8 <= kTileMaxBytes, "");
-inline bool tile_only_sector(long double dim, uint64_t dim_dn)
+inline bool tile_only_sector(const SectorShape &s)
 {
-    return dim <= (long double)kTileOnlyDim && dim_dn * 8 <= 64 * 1024;
+    if ((long double)s.du * (long double)s.dd > (long double)kTileOnlyDim || s.dd * 8 > 64 * 1024)
+        return false;
+    for (int es : {8, 4})
+        for (bool dense : {false, true})
+            if (two_pass_better(s, es, dense))
+                return false;
+    return true;
 }
 struct TilePlan {
     bool ok = false;

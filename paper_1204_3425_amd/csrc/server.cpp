@@ -84,7 +84,12 @@ size_t footprint(const hubbard_request &r)
     // of 8,192 elements, in a table with room for twice as many, a partial sum each
     if (dim <= (long double)kBatchDim)
         vecs += 64 * std::min((size_t)du, (size_t)dim / 1024 + 1) + (size_t)dim / 64;
-    if (!tile_only_sector(dim, dd)) {
+    // a bond connects the configurations that hold one electron on its sites
+    auto hops = [&](int n) {
+        return n > 0 && n < r.sites ? (double)(2 * (uint64_t)r.n_edges * binomial(r.sites - 2, n - 1)) : 0.0;
+    };
+    if (du && dd &&
+        !tile_only_sector(SectorShape{(int64_t)du, (int64_t)dd, hops(r.n_up) / (double)du, hops(r.n_dn) / (double)dd, 0})) {
         // partial sums of the largest launch of either pass, or one per row
         const size_t slabs = (size_t)((dd + 15) / 16);
         const size_t blocks = 8 * ((slabs + 7) / 8) * (size_t)up_row_blocks(r.sites, r.n_up);

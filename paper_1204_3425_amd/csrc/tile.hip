@@ -127,8 +127,17 @@ __device__ inline void tile_sums(double (&v)[N], double (*red)[N])
 // per 64 columns, dn_amp: amplitude of each slot (GT, eight per group); up_rows:
 // w_up slots per row, those past its count repeating its last hop; tcls:
 // amplitude of each class (GT).  ND: room for lower vectors of a deflated step.
+// Waves a SIMD has to hold.  FP32 with amplitudes: 88 registers in a step where a
+// product has 80, and a CU then held two workgroups of rows that leave it room for
+// three (4x4 t-t' 3u8d, 51 KB rows: 223 us a step's H.v against a product's 154).
+template <typename T, bool GT, int ND>
+constexpr int tile_simd_waves()
+{
+    return sizeof(T) == 8 || ND > 0 ? 4 : GT ? 6 : 8;
+}
+
 template <typename T, int MODE, bool GT, int ND>
-__global__ __launch_bounds__(64 * kTileWaves, (sizeof(T) == 8 || GT || ND > 0) ? 4 : 8) void hv_tile_kernel(TileArgs p, const uint4 *__restrict__ dn,
+__global__ __launch_bounds__(64 * kTileWaves, (tile_simd_waves<T, GT, ND>())) void hv_tile_kernel(TileArgs p, const uint4 *__restrict__ dn,
                                                        const uint8_t *__restrict__ dn_nq,
                                                        const double *__restrict__ dn_amp,
                                                        const uint32_t *__restrict__ up_rows,
@@ -535,7 +544,17 @@ __global__ __launch_bounds__(64) void tile_scalar_kernel(TileStep st, int what)
 // One row per workgroup.  Threads: 512; 256 where FP32 rows leave room for
 // eight workgroups or more on a CU (14-site ring 62 -> 60 us, 4x4 8u4d 206 ->
 // 182); 1024 where a row takes more than half of the LDS (FP64 4x4 4u8d, rows
-// of 12,870: 1024 threads 347 us, 512 508).
+// of 12,870: 1024 threads 347 us, 512 508), in FP32 without amplitudes a third
+// (3x6 3u6d, rows of 18,564: 152 -> 121).  Many short rows are another matter:
+// one or two passes of the threads leave the loads of the next pass nothing to hide
+// behind, and half of the last pass idle.  They take the number of at most 256
+// (twice that at most the row) with the fewest idle lanes in the last pass, the
+// larger one of two (FP64, before / after: 16 sites with diagonals 8u3d, 560
+// columns, 280 / 156 us; 17-site ring 8u3d, 680, 225 / 139; 20-site ring 5u3d, 1,140,
+// 170 / 124; 18-site ring 9u2d, 153, 108 / 76; FP32 114 / 92, 91 / 77, 80 / 79 and 93 /
+// 51).  Rows of 1,287 elements and more are even, and so are fewer rows than a
+// few per CU (3x4 6u6d, 924 rows of 924: 192 threads 19.1 us, 512 17.9).
+constexpr int64_t kTileManyRows = 1024, kTileShortRow = 1280;
 TilePlan make_tile_plan(const HvArgs &a, int elem_bytes)
 {
     TilePlan pl;
@@ -551,8 +570,18 @@ TilePlan make_tile_plan(const HvArgs &a, int elem_bytes)
     // hops, 11.6 us against 10.7 in the one-pass kernel)
     if (gt && a.dn_slot_groups * 8 > 4 * std::max(a.w_dn, 4) && a.ncls > kTwoPassClasses)
         return pl;
-    const int64_t want = pl.lds > kTileLds / 2 ? 1024 : elem_bytes == 4 && pl.lds <= kTileLds / 8 ? 256 : 512;
+    const bool fp32 = elem_bytes == 4;
+    const int64_t want = pl.lds > kTileLds / 2 || (fp32 && !gt && pl.lds > kTileLds / 3) ? 1024
+                         : fp32 && pl.lds <= kTileLds / 12                               ? 256
+                                                                                         : 512;
     pl.threads = (int)std::min<int64_t>(want, (ddn + 63) / 64 * 64);
+    if (a.dim_up >= kTileManyRows && ddn < kTileShortRow) {
+        int64_t least = (ddn + 63) / 64 * 64;
+        pl.threads = 64;
+        for (int t = 128; t <= 256 && 2 * t <= ddn; t += 64)
+            if ((ddn + t - 1) / t * t <= least)
+                pl.threads = t;
+    }
     // fewer rows than two workgroups per CU: split the columns, down to one
     // pass of the threads each (4x4 1u8d 27 -> 10 us)
     const int64_t most = (ddn + pl.threads - 1) / pl.threads;
