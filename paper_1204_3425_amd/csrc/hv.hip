@@ -79,8 +79,8 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
-__device__ inline float flip_sign(float v, uint32_t sg) { return __int_as_float(__float_as_int(v) ^ (int)sg); }
-__device__ inline double flip_sign(double v, uint32_t sg)
+[[maybe_unused]] __device__ inline float flip_sign(float v, uint32_t sg) { return __int_as_float(__float_as_int(v) ^ (int)sg); }
+[[maybe_unused]] __device__ inline double flip_sign(double v, uint32_t sg)
 {
     return __longlong_as_double(__double_as_longlong(v) ^ ((long long)sg << 32));
 }
@@ -94,6 +94,16 @@ __device__ inline double flip_sign(double v, uint32_t sg)
 // is read twice, staged and at its column, and goes through the L2.  (FP32 pairs of
 // rows gain nothing and go through it: store 600 -> 585 us but 12 us more in the
 // up-spin pass that reads the result next, fused step 685 -> 695 us.)
+//
+// Not so a product whose vectors stay in the Infinity Cache and whose result the
+// up-spin pass reads from there (HV_STORE_NEAR, in hv_rows_kernel and
+// hv_rows64_kernel): FP64 on its own rows, streamed / through the L2, 4x4 6u4d, 111 MB,
+// 252 / 223 us, 7u4d 325 / 302, 3x6 7u3d, 198 MB, 514 / 503; 17-site ring 6u4d, 225 MB,
+// 378 / 385, 4x4 6u5d, 267 MB, 532 / 554.  Steps, and products through padded work rows,
+// stream at any size (7u4d 372 / 392 a step).
+constexpr int HV_STORE_NEAR = 16;
+constexpr int64_t kNearBytes = (int64_t)208 << 20;
+
 template <typename V>
 __device__ inline V stream_load(const V *p)
 {
@@ -103,6 +113,19 @@ template <typename V>
 __device__ inline void stream_store(V *p, V v)
 {
     __builtin_nontemporal_store(v, p);
+}
+template <int MODE, typename V>
+__device__ inline V row_load(const V *p)
+{
+    return MODE == HV_STORE_NEAR ? *p : __builtin_nontemporal_load(p);
+}
+template <int MODE, typename V>
+__device__ inline void row_store(V *p, V v)
+{
+    if (MODE == HV_STORE_NEAR)
+        *p = v;
+    else
+        __builtin_nontemporal_store(v, p);
 }
 
 struct RowArgs {
@@ -214,7 +237,7 @@ __global__ __launch_bounds__(1024) void hv_rows_kernel(RowArgs p, const T *__res
                 for (int u = 0; u < CH; u++) {
                     const int d = d0 + u * nth + (int)threadIdx.x;
                     const bool ok = q < nr && d < ddn32;
-                    v[q][u] = ok ? stream_load(x + (r0 + q) * ldx + d) : (T)0;
+                    v[q][u] = ok ? row_load<MODE>(x + (r0 + q) * ldx + d) : (T)0;
                     if (FUSED)
                         w[q][u] = ok ? y[(r0 + q) * ldy + d] : (T)0;
                     pg[q][u] = 0.0;
@@ -368,8 +391,8 @@ __global__ __launch_bounds__(1024) void hv_rows_kernel(RowArgs p, const T *__res
                             const T hx = fma(mt, h[q], U * (T)__popc(su[q] & sd) * xv);
                             T *yp = y + (r0 + q) * ldy + dd;
                             const T yv = PF ? yr[q] : (YR ? *yp : (T)0);
-                            if (MODE == HV_STORE)
-                                stream_store(yp, hx);
+                            if (MODE == HV_STORE || MODE == HV_STORE_NEAR)
+                                row_store<MODE>(yp, hx);
                             else if (FUSED && p.yo)
                                 stream_store(static_cast<T *>(p.yo) + (r0 + q) * p.ldyo + dd, a_s * hx + b_s * yv);
                             else if (YR)
@@ -480,7 +503,7 @@ __global__ __launch_bounds__(kRowThreads) void hv_rows64_kernel(Row64Args p, con
         for (int u = 0; u < CH; u++) {
             const int i = u * kRowThreads + tid;
             if (i < nu) {
-                v[u] = stream_load(src + i);
+                v[u] = row_load<MODE>(src + i);
                 if (FUSED)
                     w[u] = ysrc[i];
             }
@@ -658,8 +681,8 @@ __global__ __launch_bounds__(kRowThreads) void hv_rows64_kernel(Row64Args p, con
                     const double xd = xs[dd];
                     const double hx = fma(mt, h0 + h1, U * (double)__popc(su & sd) * xd);
                     double *yp = y + r * ldy + dd;
-                    if (MODE == HV_STORE)
-                        stream_store(yp, hx);
+                    if (MODE == HV_STORE || MODE == HV_STORE_NEAR)
+                        row_store<MODE>(yp, hx);
                     else if (FUSED && p.yo)
                         stream_store(p.yo + r * p.ldyo + dd, alpha * hx + beta * yv);
                     else if (YR)
@@ -1472,7 +1495,7 @@ struct LineArgs {
     void *yo;      // where the result goes (y itself, or rows at stride ldyo)
     int64_t ldyo;
     int yoal;      // alignment of the result rows: 16 or 8 bytes (vector stores), else 0
-    int through;   // FP64 result rows not on 64 bytes: stored through the L2
+    int through;   // FP64 result rows not on 32 bytes: stored through the L2
     int contig;    // each XCD takes a contiguous range of slabs, not every eighth slab
     HvDefl defl;   // HV_FUSED_DEFL: the lower vectors psi_l . y and psi_l . x are summed against
     int64_t pair;  // 0, or the element offset of a second vector pair (x, y, result): workgroups
@@ -1772,12 +1795,13 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
                     if (MODE != HV_RESIDUAL) {
                         bool done = false;
                         if ((FULL || whole) && p.yoal == 16) {
-                            // a segment not on 64 bytes shares its first and last
-                            // 64 with the neighbouring slabs' segments: stored through
+                            // a segment not on 32 bytes shares its first and last
+                            // 32 with the neighbouring slabs' segments: stored through
                             // the L2, most of them leave it whole (4x4 FP64, dense
-                            // rows: 1660 us past the L2, 1570 through it; on 64
-                            // bytes 1275 and 1283, on 128 1395 and 1415; FP32 608
-                            // and 632)
+                            // rows on 16 bytes: 1660 us past the L2, 1570 through it; on
+                            // 64 bytes 1275 and 1283, on 128 1395 and 1415; whole product
+                            // of the 17-site ring 5u5d, on 32: 664 and 680; FP32 608 and
+                            // 632)
                             if constexpr (THROUGH)
                                 *reinterpret_cast<vec *>(yp) = out;
                             else
@@ -1951,6 +1975,8 @@ static void launch_rows_rpb(const RowArgs &ra, bool g16, bool gt, const HvPlan &
     auto by_mode = [&](auto g16c, auto gtc) {
         if (mode == HV_STORE)
             pick(std::integral_constant<int, HV_STORE>(), g16c, gtc);
+        else if (mode == HV_STORE_NEAR)
+            pick(std::integral_constant<int, HV_STORE_NEAR>(), g16c, gtc);
         else if (mode == HV_LANCZOS)
             pick(std::integral_constant<int, HV_LANCZOS>(), g16c, gtc);
         else if (mode == HV_FUSED)
@@ -2033,7 +2059,9 @@ static void launch_rows64_mode(const Row64Args &ra, int np, int nn, const HvPlan
     ra.t = a.t;
     ra.U = a.U;
     const int np = a.dn_np, nn = a.dn_nn;
-    if (mode == HV_STORE)
+    if (mode == HV_STORE_NEAR)
+        launch_rows64_mode<HV_STORE_NEAR>(ra, np, nn, pl, x, ldx, y, ldy, alpha, coef, s);
+    else if (mode == HV_STORE)
         launch_rows64_mode<HV_STORE>(ra, np, nn, pl, x, ldx, y, ldy, alpha, coef, s);
     else if (mode == HV_LANCZOS)
         launch_rows64_mode<HV_LANCZOS>(ra, np, nn, pl, x, ldx, y, ldy, alpha, coef, s);
@@ -2225,6 +2253,8 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
         yr = ypad;
         ldyr = pl.ld;
     }
+    const bool near = mode == HV_STORE && !repad && a.dim_up * a.dim_dn * (int64_t)sizeof(T) <= kNearBytes;
+    const int rmode = near ? HV_STORE_NEAR : mode;
     // the row pass, once per vector pair
     for (int half = 0; half < (pair ? 2 : 1); half++) {
         const int64_t o = half ? pair : 0;
@@ -2235,7 +2265,7 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
         if constexpr (sizeof(T) == 8) {
             done = row64_ok(a, pl);
             if (done)
-                launch_rows64(a, pl, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s, static_cast<T *>(ra.xc), ra.ldc,
+                launch_rows64(a, pl, x + o, ldx, yr + o, ldyr, rmode, alpha, coef, s, static_cast<T *>(ra.xc), ra.ldc,
                               dfl, static_cast<T *>(rh.yo), ldy);
         } else if (!rows_cls_ok<T>(a, mode)) {
             done = rows32x2_ok(a, mode);
@@ -2243,7 +2273,7 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
                 launch_rows32x2(a, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s, static_cast<T *>(ra.xc), ra.ldc,
                                 static_cast<T *>(rh.yo), ldy);
             else if (pl.rows_rpb == 3) {
-                launch_rows_rpb<T, 3>(rh, g16, gt, pl, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s);
+                launch_rows_rpb<T, 3>(rh, g16, gt, pl, x + o, ldx, yr + o, ldyr, rmode, alpha, coef, s);
                 done = true;
             }
         }
@@ -2254,9 +2284,9 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
         if (done)
             continue;
         if (pl.rows_rpb == 2)
-            launch_rows_rpb<T, 2>(rh, g16, gt, pl, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s);
+            launch_rows_rpb<T, 2>(rh, g16, gt, pl, x + o, ldx, yr + o, ldyr, rmode, alpha, coef, s);
         else
-            launch_rows_rpb<T, 1>(rh, g16, gt, pl, x + o, ldx, yr + o, ldyr, mode, alpha, coef, s);
+            launch_rows_rpb<T, 1>(rh, g16, gt, pl, x + o, ldx, yr + o, ldyr, rmode, alpha, coef, s);
     }
     if (yout) {
         // the up-spin pass adds to the result rows
@@ -2309,7 +2339,7 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
             la.dim_dn = a.dim_dn;
             la.nblocks = a.up_nblocks;
             la.nslab = pl.blk_nslab;
-            la.through = sizeof(T) == 8 && (ldyo * (int64_t)sizeof(T) % 64 != 0 || (uintptr_t)yo % 64 != 0);
+            la.through = sizeof(T) == 8 && (ldyo * (int64_t)sizeof(T) % 32 != 0 || (uintptr_t)yo % 32 != 0);
             la.contig = contig;
             la.t = a.t;
             la.yo = yo;
