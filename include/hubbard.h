@@ -137,9 +137,9 @@ int hubbard_build_bonds(int sites, const int32_t *edges, const double *t, int n_
                         hubbard_h *out);
 
 /* Releases the handle and its device memory: its tables, and the device
- * buffers of its calls that it keeps for the next one (at most 1 GiB per handle,
- * 8 GiB over all handles; an allocation of this library that finds the device
- * full frees those of every handle and tries again).  NULL is accepted. */
+ * buffers of its calls that it keeps for the next one (at most 8 GiB over all
+ * handles, the oldest going first; an allocation of this library that finds the
+ * device full frees those of every handle and tries again).  NULL is accepted. */
 int hubbard_free(hubbard_h h);
 
 /* Stream for every later call on this handle (a hipStream_t; NULL = the null

@@ -131,13 +131,17 @@ struct DeviceTables {
 // the 227 MB chunks of a resident basis (3x4 6u6d) cost 1 ms a call in hipMalloc
 // and hipFree, and 16 ms after some two hundred calls, when the driver no longer
 // keeps up with clearing freed memory (2.9 -> 19.4 ms a solve).  Blocks given
-// back are kept up to kKeepBytes per handle and kKeepAll over all handles of the
-// process, a handle's oldest going first, and freed with the handle.  take()
-// hands out a kept block of at least the size asked for and at most twice that,
-// else allocates.  Where the device is full, an allocation of the library frees
+// back are kept up to kKeepAll over all handles of the process, the oldest going
+// first, and freed with the handle; a call that finds no block of its own handle
+// takes one that another handle of the device keeps.  (With at most 1 GiB a handle the chunks of
+// mid-sized sectors were allocated by every solve, faster than the driver clears
+// them: 20-site ring 10u1d, 40 steps with psi, 12 to 1,800 ms a call; the slower
+// steps before took 21.)  take()
+// hands out a kept block of at least the size asked for and at most twice that (a
+// quarter more from 64 MiB on), else allocates.  Where the device is full, an allocation of the library frees
 // the kept blocks of every handle and tries again.  Safe from several threads;
 // the work that used a block has to be complete when it is given back.
-constexpr size_t kKeepBytes = (size_t)1 << 30, kKeepAll = (size_t)8 << 30;
+constexpr size_t kKeepAll = (size_t)8 << 30;
 class Workspace {
   public:
     Workspace();
@@ -145,16 +149,22 @@ class Workspace {
     Workspace &operator=(const Workspace &) = delete;
     void *take(size_t bytes, size_t *got);
     void *take_kept(size_t bytes, size_t *got);  // as take, or null where no kept block fits
+    void *take_own(size_t bytes, size_t most, int device, size_t *got);
     void give(void *p, size_t bytes);
     void *take_host(size_t bytes, size_t *got);
     void give_host(void *p, size_t bytes);
     void release();
     ~Workspace();
+    // age of the oldest kept block (0: none), and freeing that one
+    uint64_t oldest();
+    void drop_oldest();
 
   private:
     struct Block {
         void *p;
         size_t bytes;
+        uint64_t age;  // order of giving back over all handles, from 1
+        int device;
     };
     void drop(size_t k);
     std::mutex mu_;

@@ -10,8 +10,9 @@
 
 namespace hub {
 
-// bytes kept by all handles of the process
+// bytes kept by all handles of the process, and blocks given back so far
 static std::atomic<size_t> g_kept{0};
+static std::atomic<uint64_t> g_given{0};
 
 // Every workspace alive.  Taken before a workspace's own lock, never inside it.
 struct Registry {
@@ -80,13 +81,38 @@ void *host_alloc(size_t bytes)
 
 static size_t rounded(size_t bytes) { return (std::max<size_t>(bytes, 16) + 65535) / 65536 * 65536; }
 
+// the current device (kept blocks serve the device they were allocated on)
+static int current_device()
+{
+    int d = 0;
+    return hipGetDevice(&d) == hipSuccess ? d : -1;
+}
+
 void *Workspace::take_kept(size_t bytes, size_t *got)
 {
     bytes = rounded(bytes);
+    const size_t most = bytes < ((size_t)64 << 20) ? 2 * bytes : bytes + bytes / 4;
+    const int device = current_device();
+    if (void *p = take_own(bytes, most, device, got))
+        return p;
+    // small blocks are not worth a walk over the handles
+    if (bytes < ((size_t)1 << 20) || g_kept.load() < bytes)
+        return nullptr;
+    Registry &r = registry();
+    std::lock_guard<std::mutex> lk(r.mu);
+    for (Workspace *w : r.all)
+        if (w != this)
+            if (void *p = w->take_own(bytes, most, device, got))
+                return p;
+    return nullptr;
+}
+
+void *Workspace::take_own(size_t bytes, size_t most, int device, size_t *got)
+{
     std::lock_guard<std::mutex> lk(mu_);
     size_t best = dev_.size();
     for (size_t k = 0; k < dev_.size(); k++)
-        if (dev_[k].bytes >= bytes && dev_[k].bytes <= 2 * bytes &&
+        if (dev_[k].device == device && dev_[k].bytes >= bytes && dev_[k].bytes <= most &&
             (best == dev_.size() || dev_[k].bytes < dev_[best].bytes))
             best = k;
     if (best == dev_.size())
@@ -114,18 +140,49 @@ void Workspace::drop(size_t k)
 
 void Workspace::give(void *p, size_t bytes)
 {
-    if (bytes > kKeepBytes) {
+    if (bytes > kKeepAll) {
         (void)hipFree(p);
         return;
     }
-    std::lock_guard<std::mutex> lk(mu_);
-    dev_.push_back(Block{p, bytes});
-    held_ += bytes;
-    g_kept += bytes;
-    while (!dev_.empty() && (held_ > kKeepBytes || g_kept.load() > kKeepAll)) {
-        (void)hipFree(dev_.front().p);
-        drop(0);
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        dev_.push_back(Block{p, bytes, ++g_given, current_device()});
+        held_ += bytes;
+        g_kept += bytes;
     }
+    if (g_kept.load() <= kKeepAll)
+        return;
+    Registry &r = registry();
+    std::lock_guard<std::mutex> lk(r.mu);
+    while (g_kept.load() > kKeepAll) {
+        Workspace *w = nullptr;
+        uint64_t first = 0;
+        for (Workspace *x : r.all) {
+            const uint64_t age = x->oldest();
+            if (age && (!w || age < first)) {
+                w = x;
+                first = age;
+            }
+        }
+        if (!w)
+            break;
+        w->drop_oldest();
+    }
+}
+
+uint64_t Workspace::oldest()
+{
+    std::lock_guard<std::mutex> lk(mu_);
+    return dev_.empty() ? 0 : dev_.front().age;
+}
+
+void Workspace::drop_oldest()
+{
+    std::lock_guard<std::mutex> lk(mu_);
+    if (dev_.empty())
+        return;
+    (void)hipFree(dev_.front().p);
+    drop(0);
 }
 
 void *Workspace::take_host(size_t bytes, size_t *got)
@@ -151,7 +208,7 @@ void Workspace::give_host(void *p, size_t bytes)
         std::lock_guard<std::mutex> lk(mu_);
         // one or two small blocks serve every call
         if (host_.size() < 2 && bytes <= (1 << 20)) {
-            host_.push_back(Block{p, bytes});
+            host_.push_back(Block{p, bytes, 0, 0});
             return;
         }
     }
@@ -244,8 +301,8 @@ bool BasisPool::reserve(size_t j, size_t limit, hipStream_t s)
             return false;
         std::unique_ptr<DevBuf> c = DevBuf::kept(cb, ws);
         if (!c) {
-            // (re)read the free memory; small chunks go by the last reading
-            if ((cb > kKeepBytes || !seen_free || free_left < cb + spare) && !read_free()) {
+            // (re)read the free memory; chunks of up to 1 GiB go by the last reading
+            if ((cb > ((size_t)1 << 30) || !seen_free || free_left < cb + spare) && !read_free()) {
                 release_kept();
                 if (!read_free())
                     return false;

@@ -23,7 +23,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["others_make_room", "lifetimes", "threads", "basis"])
+@pytest.mark.parametrize("check", ["others_make_room", "lifetimes", "threads", "basis", "bound", "turns"])
 def test_workspace(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "ok\n", r.stdout + r.stderr

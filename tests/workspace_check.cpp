@@ -16,6 +16,7 @@ std::mutex mu;
 std::map<void *, size_t> live;
 size_t used = 0, capacity = 0;
 int mallocs = 0;
+thread_local int device = 0;
 }  // namespace
 
 extern "C" {
@@ -43,6 +44,11 @@ hipError_t hipHostFree(void *p) { return hipFree(p); }
 hipError_t hipHostGetDevicePointer(void **d, void *p, unsigned)
 {
     *d = p;
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int *d)
+{
+    *d = device;
     return hipSuccess;
 }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -83,8 +89,7 @@ static void others_make_room()
 {
     capacity = 64 * M;
     Workspace a, b;
-    { DevBuf x(24 * M, &a); }
-    { DevBuf x(24 * M, &b); }
+    { DevBuf x(24 * M, &a), y(24 * M, &b); }
     need(used == 48 * M, "both blocks are kept");
     { DevBuf x(40 * M, &a); }  // neither fits nor is there room beside them
     need(used == 40 * M, "the other handle's block went");
@@ -124,6 +129,48 @@ static void lifetimes()
         code = e.code;
     }
     need(code == HUBBARD_ENOMEM && used == 16 * M && live.count(held.p), "a buffer in use stays");
+}
+
+// what all handles keep is bounded, and the oldest block goes first, whosever it is
+static void bound()
+{
+    constexpr size_t G = (size_t)1 << 30;
+    capacity = 64 * G;
+    Workspace a, b;
+    { DevBuf x(3 * G, &a); }
+    { DevBuf x(2 * G, &b); }
+    { DevBuf x(G, &a); }
+    need(used == 6 * G, "one handle may keep most of it");
+    const int before = mallocs;
+    { DevBuf x(3 * G, &a), y(2 * G, &b), z(G, &a); }
+    need(mallocs == before && used == 6 * G, "a repeated call allocates nothing");
+    // the order of giving back is now z, y, x
+    { DevBuf x(4 * G, &b); }
+    need(used == 4 * G + 3 * G, "the oldest two went: a's gigabyte and b's two");
+    { DevBuf x(9 * G, &b); }
+    need(used == 7 * G, "more than the bound is not kept");
+    { DevBuf x(3 * G, &a); }
+    need(used == 7 * G, "a's three are still there");
+}
+
+// handles that take turns share what they keep, on one device
+static void turns()
+{
+    capacity = 64 * 1024 * M;
+    std::vector<std::unique_ptr<Workspace>> w;
+    for (int k = 0; k < 24; k++)
+        w.emplace_back(new Workspace);
+    for (int round = 0; round < 3; round++)
+        for (auto &x : w)
+            DevBuf a(900 * M, x.get()), b(800 * M, x.get()), c(3 * M, x.get());
+    need(mallocs == 3, "one call's blocks serve all of them");
+    device = 1;
+    { DevBuf a(900 * M, w[0].get()); }
+    need(mallocs == 4, "a block of the other device does not");
+    { DevBuf a(900 * M, w[1].get()); }
+    need(mallocs == 4, "its own does");
+    w.clear();
+    need(used == 0, "freed with the handles");
 }
 
 // several threads whose handles take, give and run out at once
@@ -188,7 +235,9 @@ int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> all = {
         {"others_make_room", others_make_room}, {"lifetimes", lifetimes}, {"threads", threads},
-        {"basis", basis}};
+        {"basis", basis},
+        {"bound", bound},
+        {"turns", turns}};
     need(argc == 2 && all.count(argv[1]), "a check's name");
     all.at(argv[1])();
     std::printf("ok\n");
