@@ -160,9 +160,8 @@ class Engine : public BatchRunner {
             const int k = (int)(launched_ % kRing);
             double *mb = static_cast<double *>(mail_host_->dev) + (size_t)k * 4 * table_.size();
             launch_batch_step<T>(static_cast<BatchInst *>(insts_->p), (int)table_.size(),
-                                 static_cast<const BatchItem *>(items_->p), n_items_, n_upd_, lds_, pairs_, mb,
-                                 (int)launched_,
-                                 s_);
+                                 static_cast<const BatchItem *>(items_->p), n_items_, n_upd_, lds_, pairs_, narrow_,
+                                 mb, (int)launched_, s_);
             for (Slot<T> *sl : table_)
                 sl->launched++;
             HUB_HIP(hipEventRecord(ev_[k], s_));
@@ -262,6 +261,7 @@ class Engine : public BatchRunner {
             return;
         std::vector<BatchInst> desc((size_t)n);
         pairs_ = true;
+        narrow_ = false;
         std::vector<BatchItem> items, upd, start;
         size_t lds = 16;
         for (int i = 0; i < n; i++) {
@@ -277,6 +277,7 @@ class Engine : public BatchRunner {
             d.dn_nq = h->dev.dn_nq8;
             const bool pairs = pair_rows(h, sizeof(T));
             pairs_ = pairs_ && pairs;
+            narrow_ = narrow_ || (pairs && h->dn.dim <= kBatchNarrow);
             d.dn_pair = pairs ? reinterpret_cast<const uint4 *>(h->dev.dn_pair16) : nullptr;
             d.dim_up = h->up.dim;
             d.dim_dn = h->dn.dim;
@@ -373,7 +374,7 @@ class Engine : public BatchRunner {
     hipEvent_t ev_[kRing];
     size_t insts_cap_ = 0, items_cap_ = 0, lds_ = 16;
     int n_items_ = 0, n_upd_ = 0;
-    bool pairs_ = true;
+    bool pairs_ = true, narrow_ = false;
     int64_t launched_ = 0, read_ = 0;  // steps launched and read back since the last rebuild
     int pending_stopped_ = 0;         // instances of the table found finished
     bool dirty_ = true;

@@ -63,13 +63,17 @@ struct BatchItem {
     int64_t nrows;
 };
 
+// Rows of pairs up to which a wave takes several pairs at a time.
+constexpr int kBatchNarrow = 32;
+
 // One Lanczos step j of every active instance in two launches: the H.v with
 // the three-term update (and, in extra workgroups, the Ritz value and stop
 // test of step j - 1), then the q - a_j f_j update with its norm (n_upd items
-// after the n_items of the H.v).  pairs: every listed instance has dn_pair.
+// after the n_items of the H.v).  pairs: every listed instance has dn_pair; narrow:
+// one of them has such short rows.
 template <typename T>
 void launch_batch_step(BatchInst *insts_dev, int n_inst, const BatchItem *items_dev, int n_items, int n_upd,
-                       size_t lds_bytes, bool pairs, double *mailbox_dev, int j, hipStream_t s);
+                       size_t lds_bytes, bool pairs, bool narrow, double *mailbox_dev, int j, hipStream_t s);
 
 // The start vectors and states of the instances of the given update items, in
 // two launches; norms (mapped host memory): their squared norms by slot.

@@ -95,8 +95,13 @@ struct Pair<double> {
 // element and entry one FMA and half an address, against six instructions with
 // the sign in the entry.  A row's up-spin factors are scalars (+-t, 0 past its
 // count: a non-finite x makes the step's coefficients non-finite either way).
+// A wave takes 64 columns of a pair at a time; with rows of at most kBatchNarrow
+// elements (NARROW, a row's up-spin entries then differ from lane to lane) as many
+// pairs as fill its lanes.  One row at a time, 2,048 rows of one column were 256
+// steps of each wave (20 FP64 steps, ms: 4x4 8u0d 12.2 / 0.85, 20-site ring 10u0d
+// 15.5 / 1.1, 16 solves of 10u1d 55 / 33; element by element, before pairs, 1.9, 2.5, 40).
 // Returns the thread's share of q.x.
-template <typename T>
+template <typename T, bool NARROW>
 __device__ __forceinline__ double batch_pairs(const BatchInst &in, const BatchItem &it, const T *__restrict__ x,
                                               T *__restrict__ y, const typename Pair<T>::type *xp, T a_s, T b_s)
 {
@@ -109,11 +114,14 @@ __device__ __forceinline__ double batch_pairs(const BatchInst &in, const BatchIt
     double acc = 0.0;
     // tasks of a wave: 64 columns by a share of the pairs, as many shares as
     // leave the four waves about the same number of tasks
-    const int lane = (int)threadIdx.x & 63, nch = (ddn + 63) >> 6;
-    const int shares = min(npair, nch % 4 == 0 ? 1 : nch % 2 == 0 ? 2 : 4);
+    const int lane = (int)threadIdx.x & 63, nch = NARROW ? 1 : (ddn + 63) >> 6;
+    int cols = 64;  // lanes to a pair
+    while (NARROW && cols >= 2 * ddn)
+        cols >>= 1;
+    const int shares = NARROW ? kThreads / 64 : min(npair, nch % 4 == 0 ? 1 : nch % 2 == 0 ? 2 : 4);
     for (int task = (int)threadIdx.x >> 6; task < nch * shares; task += kThreads / 64) {
         const int c = __builtin_amdgcn_readfirstlane(task % nch), sh = __builtin_amdgcn_readfirstlane(task / nch);
-        const int d = c * 64 + lane;
+        const int d = NARROW ? lane & (cols - 1) : c * 64 + lane;
         const bool ok = d < ddn;
         const int dc = ok ? d : ddn - 1;
         const int nq = __builtin_amdgcn_readfirstlane((int)in.dn_nq[c]);
@@ -124,7 +132,9 @@ __device__ __forceinline__ double batch_pairs(const BatchInst &in, const BatchIt
             e4[g] = dn[(size_t)(g < in.gmax ? g : 0) * (size_t)ddn];
         const uint32_t sd = in.states_dn[dc];
         const uint32_t off = (uint32_t)dc * (uint32_t)sizeof(T);
-        for (int pl = sh * npair / shares; pl < (sh + 1) * npair / shares; pl++) {
+        const int p0 = NARROW ? (int)threadIdx.x / cols : sh * npair / shares;
+        const int p1 = NARROW ? npair : (sh + 1) * npair / shares, pstep = NARROW ? kThreads / cols : 1;
+        for (int pl = p0; pl < p1; pl += pstep) {
             const bool two = 2 * pl + 1 < nrows;
             const int64_t r0 = it.r0 + 2 * pl, r1 = two ? r0 + 1 : r0;
             const uint32_t *__restrict__ ur[2] = {in.up_tile + r0 * in.w_up, in.up_tile + r1 * in.w_up};
@@ -202,8 +212,9 @@ __device__ __forceinline__ double batch_pairs(const BatchInst &in, const BatchIt
 // 32 rings of 10 to 12 sites (8.3 M FP32 elements; two such launches at a time);
 // this form, on pairs of rows, 95 us, about half of it instruction issue and the
 // rest the staging and the up-spin rows' trips to the L2.
-// PAIRS: every listed instance takes the form on row pairs.
-template <typename T, bool PAIRS>
+// PAIRS: every listed instance takes the form on row pairs; NARROW: some of them
+// have rows of at most kBatchNarrow elements.
+template <typename T, bool PAIRS, bool NARROW>
 __global__ __launch_bounds__(kThreads) void batch_hv_kernel(const BatchInst *__restrict__ insts,
                                                             const BatchItem *__restrict__ items, int n_inst, int k,
                                                             double *__restrict__ mailbox)
@@ -232,7 +243,36 @@ __global__ __launch_bounds__(kThreads) void batch_hv_kernel(const BatchInst *__r
     const int64_t base = it.r0 * in.dim_dn;
     typedef typename Pair<T>::type V2;
     const int npair = (nrows + 1) >> 1, width = 2 * (ddn + 1);
-    if (PAIRS || in.dn_pair) {
+    const bool narrow = NARROW && ddn <= kBatchNarrow && in.dn_pair;
+    if (narrow) {
+        // rows are contiguous: element by element, each to its half of a pair
+        V2 *xp = reinterpret_cast<V2 *>(smem_raw);
+        int rl = (int)threadIdx.x / ddn, d = (int)threadIdx.x - rl * ddn;
+        for (int i0 = 0; i0 < n; i0 += 8 * kThreads) {
+            T v[8];
+#pragma unroll
+            for (int u = 0; u < 8; u++) {
+                const int i = i0 + u * kThreads + (int)threadIdx.x;
+                v[u] = x[base + (i < n ? i : 0)];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; u++) {
+                if (i0 + u * kThreads + (int)threadIdx.x < n) {
+                    T *half = reinterpret_cast<T *>(xp + (rl >> 1) * width) + (rl & 1);
+                    half[2 * d] = v[u];
+                    half[2 * (d + ddn + 1)] = -v[u];
+                }
+                rl += kThreads / ddn;
+                d += kThreads % ddn;
+                if (d >= ddn) {
+                    d -= ddn;
+                    rl++;
+                }
+            }
+        }
+        for (int r = threadIdx.x; r < npair; r += kThreads)
+            xp[r * width + ddn] = V2{(T)0, (T)0};
+    } else if (PAIRS || in.dn_pair) {
         V2 *xp = reinterpret_cast<V2 *>(smem_raw);
         // the threads as rows of a power of two of columns, each taking a pair
         int cols = kThreads;
@@ -301,7 +341,8 @@ __global__ __launch_bounds__(kThreads) void batch_hv_kernel(const BatchInst *__r
     const T a_s = scal[0], b_s = scal[1], tm = (T)(-in.t), U = (T)in.U;
     double acc = 0.0;
     if (PAIRS || in.dn_pair) {
-        acc = batch_pairs<T>(in, it, x, y, reinterpret_cast<const V2 *>(smem_raw), a_s, b_s);
+        const V2 *xp = reinterpret_cast<const V2 *>(smem_raw);
+        acc = narrow ? batch_pairs<T, NARROW>(in, it, x, y, xp, a_s, b_s) : batch_pairs<T, false>(in, it, x, y, xp, a_s, b_s);
         const double s = wg_sum(acc, red);
         if (threadIdx.x == 0)
             in.part[it.part] = s;
@@ -731,9 +772,10 @@ __global__ __launch_bounds__(kThreads) void batch_fill_kernel(const BatchInst *_
 
 template <typename T>
 void launch_batch_step(BatchInst *insts_dev, int n_inst, const BatchItem *items_dev, int n_items, int n_upd,
-                       size_t lds_bytes, bool pairs, double *mailbox_dev, int k, hipStream_t s)
+                       size_t lds_bytes, bool pairs, bool narrow, double *mailbox_dev, int k, hipStream_t s)
 {
-    auto hv = pairs ? batch_hv_kernel<T, true> : batch_hv_kernel<T, false>;
+    auto hv = narrow ? (pairs ? batch_hv_kernel<T, true, true> : batch_hv_kernel<T, false, true>)
+                     : (pairs ? batch_hv_kernel<T, true, false> : batch_hv_kernel<T, false, false>);
     if (lds_bytes > 64 * 1024)
         HUB_HIP(hipFuncSetAttribute((const void *)hv, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
     hipLaunchKernelGGL(hv, dim3(n_inst + n_items), dim3(kThreads), lds_bytes, s, insts_dev, items_dev, n_inst, k,
@@ -743,9 +785,9 @@ void launch_batch_step(BatchInst *insts_dev, int n_inst, const BatchItem *items_
     HUB_HIP(hipGetLastError());
 }
 
-template void launch_batch_step<double>(BatchInst *, int, const BatchItem *, int, int, size_t, bool, double *, int,
+template void launch_batch_step<double>(BatchInst *, int, const BatchItem *, int, int, size_t, bool, bool, double *, int,
                                          hipStream_t);
-template void launch_batch_step<float>(BatchInst *, int, const BatchItem *, int, int, size_t, bool, double *, int,
+template void launch_batch_step<float>(BatchInst *, int, const BatchItem *, int, int, size_t, bool, bool, double *, int,
                                         hipStream_t);
 
 template <typename T>

@@ -69,3 +69,34 @@ def test_batch_ritz_value_of_many_steps():
     for m in (1, 2, 3, 17, 100, 511, 512, 513, 600):
         w = eigh_tridiagonal(r["a"][:m], r["b"][:m - 1], eigvals_only=True, select="i", select_range=(0, 0))[0]
         assert abs(r["e_hist"][m - 1] - w) <= 1e-13 * max(1.0, np.abs(r["a"][:m]).max() + 2 * r["b"][:m].max()), m
+
+
+NARROW = [
+    # sites, edges, n_up, n_dn: rows a wave takes several pairs of at a time, and some it does not
+    (13, workload.ring(13), 6, 0),       # 1,716 rows of one column
+    (12, workload.torus(3, 4), 5, 1),    # 12 columns, 170 rows to an item, an odd last pair
+    (16, DIAG, 3, 1),                    # 16 columns, down rows of one, up rows of three groups of eight
+    (17, workload.ring(17), 4, 16),      # 17 columns
+    (8, workload.ring(8), 4, 2),         # 28 columns
+    (7, workload.ring(7), 3, 4),         # 35 columns: one pair at a time
+    (15, workload.ring(15), 1, 7),       # long rows beside them
+]
+
+
+@pytest.mark.parametrize("precision", [hb.HUBBARD_FP64, hb.HUBBARD_MIXED], ids=["fp64", "mixed"])
+def test_batch_of_narrow_rows(precision):
+    """Each sector alone and all of them in one batch: the coefficients of the oracle,
+    and the same bits either way."""
+    print("narrow rows", precision, flush=True)
+    hs = [hb.hubbard_build(*c, 1.0, 3.0) for c in NARROW]
+    seeds = list(range(60, 60 + len(hs)))
+    opt = dict(tol=-1.0, max_iter=10, precision=precision, history=True)
+    for c, h, seed, g in zip(NARROW, hs, seeds, hb.hubbard_lanczos_batch(hs, seeds=seeds, **opt)):
+        m = oracle.Model(*c, 1.0, 3.0)
+        ref = m.lanczos(oracle.start_vector(seed, m.dim), tol=-1.0, max_iter=10)
+        scale = np.abs(ref["a"]).max() + ref["b"].max()
+        tol = 1e-4 if precision == hb.HUBBARD_MIXED else 64 * np.sqrt(h.dim) * np.finfo(float).eps
+        assert np.abs(g["a"] - ref["a"]).max() <= tol * scale, c
+        assert np.abs(g["b"] - ref["b"]).max() <= tol * scale, c
+        alone = hb.hubbard_lanczos_batch([h], seeds=[seed], **opt)[0]
+        assert np.array_equal(alone["a"], g["a"]) and np.array_equal(alone["b"], g["b"]), c
