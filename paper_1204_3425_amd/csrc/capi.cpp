@@ -569,13 +569,16 @@ static HvArgs hv_args(const hubbard *h)
     a.hops_up = sh.hu;
     a.hops_dn = sh.hd;
     // the power of two at or below the largest coupling, within what a double's
-    // inverse can hold
+    // inverse can hold; 1 where the third powers of the couplings fit a double with
+    // room for the vector's squares
     double big = std::fabs(h->U);
     if (h->tcls.empty())
         big = std::fmax(big, std::fabs(h->t));
     for (double c : h->tcls)
         big = std::fmax(big, std::fabs(c));
-    const int e = big > 0.0 ? std::max(-1000, std::min(std::ilogb(big), 1000)) : 0;
+    int e = big > 0.0 ? std::max(-1000, std::min(std::ilogb(big), 1000)) : 0;
+    if (std::abs(e) <= 200)
+        e = 0;
     a.qscale = std::ldexp(1.0, -e);
     a.qunscale = std::ldexp(1.0, e);
     return a;
@@ -1524,6 +1527,7 @@ static int build_impl(int sites, const int32_t *edges, const double *amp, int n_
             h->device = -1;  // host tables only: info and export work, device calls fail
         } else {
             HUB_HIP(hipGetDevice(&h->device));
+            h->ws.device = h->device;
             try {
                 upload_tables(h.get());
             } catch (...) {

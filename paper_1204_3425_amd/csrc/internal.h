@@ -149,12 +149,13 @@ class Workspace {
     Workspace &operator=(const Workspace &) = delete;
     void *take(size_t bytes, size_t *got);
     void *take_kept(size_t bytes, size_t *got);  // as take, or null where no kept block fits
-    void *take_own(size_t bytes, size_t most, int device, size_t *got);
+    void *take_own(size_t bytes, size_t most, size_t *got);
     void give(void *p, size_t bytes);
     void *take_host(size_t bytes, size_t *got);
     void give_host(void *p, size_t bytes);
     void release();
     ~Workspace();
+    int device = 0;  // of the handle: its calls run, and allocate, there
     // age of the oldest kept block (0: none), and freeing that one
     uint64_t oldest();
     void drop_oldest();
@@ -164,7 +165,6 @@ class Workspace {
         void *p;
         size_t bytes;
         uint64_t age;  // order of giving back over all handles, from 1
-        int device;
     };
     void drop(size_t k);
     std::mutex mu_;
@@ -319,7 +319,8 @@ struct HvArgs {
     const uint8_t *dn_slot_nq = nullptr;
     int dn_slot_groups = 0;
     double hops_up = 0.0, hops_dn = 0.0;  // mean hops of a row
-    // a power of two near 1 / max(|t|, |U|), and its inverse (see TileStep)
+    // a power of two near 1 / max(|t|, |U|) where those are very small or large (else
+    // 1), and its inverse (see TileStep)
     double qscale = 1.0, qunscale = 1.0;
 };
 
@@ -475,9 +476,9 @@ struct TilePlan {
 // those sums, x_{j+1} = q / b_j - (a_j / b_j) x_j - (b_j / b_{j-1}) x_{j-1} in
 // place of q, and the partial sums of its square (norm2_out).  With |x_j| = b_j the
 // product q.x_j is of the order of b_j^2 |H|, three powers of the couplings where
-// |x_j|^2 has two, so the H.v sums qscale q.x_j (exact, |H| qscale near 1) and the
-// update takes the factor out of a_j: the sums then fit a double wherever the
-// norms do.  b[j] holds |x_j|;
+// |x_j|^2 has two, so with extreme couplings the H.v sums qscale q.x_j (exact,
+// |H| qscale near 1) and the update takes the factor out of a_j: the sums then fit
+// a double wherever the norms do.  b[j] holds |x_j|;
 // hist (may be mapped host memory): b_j at 2j, a_j at 2j + 1.  unit: x_0 is taken as a unit vector.  Where the
 // H.v writes more than kTileDirectParts sums the caller reduces them to one first.
 constexpr int kTileDirectParts = 4096;

@@ -93,6 +93,7 @@ struct TileArgs {
     int dim_dn, w_up, gmax;  // slots per up row, groups per column
     int nseg, span;          // workgroups per row, columns of each (a multiple of 64)
     double t, U, qscale;
+    int scaled;              // qscale is not 1
     int64_t pair;            // element offset of the second half of a complex vector (gridDim.y = 2)
     const double *psi;       // deflated step: nd dense vectors, vector l at psi + l * pdim
     int nd;
@@ -329,7 +330,10 @@ __global__ __launch_bounds__(64 * kTileWaves, (tile_simd_waves<T, GT, ND>())) vo
             if (MODE != HV_RESIDUAL)
                 out[r * ldy + d] = h;
             if (MODE == HV_LANCZOS) {
-                acc[0] += (double)h * p.qscale * (double)xv;
+                double hs = (double)h;
+                if (p.scaled)
+                    hs *= p.qscale;
+                acc[0] += hs * (double)xv;
 #pragma unroll
                 for (int l = 0; l < ND; l++) {
                     acc[1 + 2 * l] += (double)h * pv[l];
@@ -619,6 +623,7 @@ void launch_hv_tile(const HvArgs &a, const TilePlan &pl, const T *x, int64_t ldx
     p.t = a.t;
     p.U = a.U;
     p.qscale = a.qscale;
+    p.scaled = a.qscale != 1.0;
     p.pair = pair;
     p.psi = psi;
     p.nd = nd;

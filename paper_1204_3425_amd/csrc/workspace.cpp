@@ -81,19 +81,11 @@ void *host_alloc(size_t bytes)
 
 static size_t rounded(size_t bytes) { return (std::max<size_t>(bytes, 16) + 65535) / 65536 * 65536; }
 
-// the current device (kept blocks serve the device they were allocated on)
-static int current_device()
-{
-    int d = 0;
-    return hipGetDevice(&d) == hipSuccess ? d : -1;
-}
-
 void *Workspace::take_kept(size_t bytes, size_t *got)
 {
     bytes = rounded(bytes);
     const size_t most = bytes < ((size_t)64 << 20) ? 2 * bytes : bytes + bytes / 4;
-    const int device = current_device();
-    if (void *p = take_own(bytes, most, device, got))
+    if (void *p = take_own(bytes, most, got))
         return p;
     // small blocks are not worth a walk over the handles
     if (bytes < ((size_t)1 << 20) || g_kept.load() < bytes)
@@ -101,18 +93,18 @@ void *Workspace::take_kept(size_t bytes, size_t *got)
     Registry &r = registry();
     std::lock_guard<std::mutex> lk(r.mu);
     for (Workspace *w : r.all)
-        if (w != this)
-            if (void *p = w->take_own(bytes, most, device, got))
+        if (w != this && w->device == device)
+            if (void *p = w->take_own(bytes, most, got))
                 return p;
     return nullptr;
 }
 
-void *Workspace::take_own(size_t bytes, size_t most, int device, size_t *got)
+void *Workspace::take_own(size_t bytes, size_t most, size_t *got)
 {
     std::lock_guard<std::mutex> lk(mu_);
     size_t best = dev_.size();
     for (size_t k = 0; k < dev_.size(); k++)
-        if (dev_[k].device == device && dev_[k].bytes >= bytes && dev_[k].bytes <= most &&
+        if (dev_[k].bytes >= bytes && dev_[k].bytes <= most &&
             (best == dev_.size() || dev_[k].bytes < dev_[best].bytes))
             best = k;
     if (best == dev_.size())
@@ -146,7 +138,7 @@ void Workspace::give(void *p, size_t bytes)
     }
     {
         std::lock_guard<std::mutex> lk(mu_);
-        dev_.push_back(Block{p, bytes, ++g_given, current_device()});
+        dev_.push_back(Block{p, bytes, ++g_given});
         held_ += bytes;
         g_kept += bytes;
     }
@@ -208,7 +200,7 @@ void Workspace::give_host(void *p, size_t bytes)
         std::lock_guard<std::mutex> lk(mu_);
         // one or two small blocks serve every call
         if (host_.size() < 2 && bytes <= (1 << 20)) {
-            host_.push_back(Block{p, bytes, 0, 0});
+            host_.push_back(Block{p, bytes, 0});
             return;
         }
     }

@@ -16,7 +16,6 @@ std::mutex mu;
 std::map<void *, size_t> live;
 size_t used = 0, capacity = 0;
 int mallocs = 0;
-thread_local int device = 0;
 }  // namespace
 
 extern "C" {
@@ -44,11 +43,6 @@ hipError_t hipHostFree(void *p) { return hipFree(p); }
 hipError_t hipHostGetDevicePointer(void **d, void *p, unsigned)
 {
     *d = p;
-    return hipSuccess;
-}
-hipError_t hipGetDevice(int *d)
-{
-    *d = device;
     return hipSuccess;
 }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -164,7 +158,7 @@ static void turns()
         for (auto &x : w)
             DevBuf a(900 * M, x.get()), b(800 * M, x.get()), c(3 * M, x.get());
     need(mallocs == 3, "one call's blocks serve all of them");
-    device = 1;
+    w[0]->device = w[1]->device = 1;  // (they keep nothing)
     { DevBuf a(900 * M, w[0].get()); }
     need(mallocs == 4, "a block of the other device does not");
     { DevBuf a(900 * M, w[1].get()); }
