@@ -93,7 +93,6 @@ struct TileArgs {
     int dim_dn, w_up, gmax;  // slots per up row, groups per column
     int nseg, span;          // workgroups per row, columns of each (a multiple of 64)
     double t, U, qscale;
-    int scaled;              // qscale is not 1
     int64_t pair;            // element offset of the second half of a complex vector (gridDim.y = 2)
     const double *psi;       // deflated step: nd dense vectors, vector l at psi + l * pdim
     int nd;
@@ -128,6 +127,10 @@ __device__ inline void tile_sums(double (&v)[N], double (*red)[N])
 // per 64 columns, dn_amp: amplitude of each slot (GT, eight per group); up_rows:
 // w_up slots per row, those past its count repeating its last hop; tcls:
 // amplitude of each class (GT).  ND: room for lower vectors of a deflated step.
+// HV_LANCZOS with the factor qscale on q.x (in the common kernel the factor would
+// cost registers it does not have: 3x4 6u6d solve 2121 -> 2157 us).
+constexpr int HV_LANCZOS_SCALED = 16;
+
 // Waves a SIMD has to hold.  FP32 with amplitudes: 88 registers in a step where a
 // product has 80, and a CU then held two workgroups of rows that leave it room for
 // three (4x4 t-t' 3u8d, 51 KB rows: 223 us a step's H.v against a product's 154).
@@ -147,6 +150,7 @@ __global__ __launch_bounds__(64 * kTileWaves, (tile_simd_waves<T, GT, ND>())) vo
                                                        const T *__restrict__ x, int64_t ldx, T *__restrict__ out,
                                                        int64_t ldy, double shift, double *__restrict__ part)
 {
+    constexpr bool SCALED = MODE == HV_LANCZOS_SCALED, LANCZOS = MODE == HV_LANCZOS || SCALED;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T *xs = reinterpret_cast<T *>(smem_raw);
     const int ddn = p.dim_dn, nth = (int)blockDim.x, tid = (int)threadIdx.x;
@@ -234,7 +238,7 @@ __global__ __launch_bounds__(64 * kTileWaves, (tile_simd_waves<T, GT, ND>())) vo
         if (tid == 0)
             xs[ddn] = (T)0;  // the zero slot that padding entries point at
         // the result rows' padding, which the update pass reads
-        if (MODE == HV_LANCZOS && mine && c1 == ddn && ddn + tid < ldy)
+        if (LANCZOS && mine && c1 == ddn && ddn + tid < ldy)
             out[r * ldy + ddn + tid] = (T)0;
     }
     __syncthreads();
@@ -329,11 +333,8 @@ __global__ __launch_bounds__(64 * kTileWaves, (tile_simd_waves<T, GT, ND>())) vo
         if (ok) {
             if (MODE != HV_RESIDUAL)
                 out[r * ldy + d] = h;
-            if (MODE == HV_LANCZOS) {
-                double hs = (double)h;
-                if (p.scaled)
-                    hs *= p.qscale;
-                acc[0] += hs * (double)xv;
+            if (LANCZOS) {
+                acc[0] += (SCALED ? (double)h * p.qscale : (double)h) * (double)xv;
 #pragma unroll
                 for (int l = 0; l < ND; l++) {
                     acc[1 + 2 * l] += (double)h * pv[l];
@@ -623,7 +624,6 @@ void launch_hv_tile(const HvArgs &a, const TilePlan &pl, const T *x, int64_t ldx
     p.t = a.t;
     p.U = a.U;
     p.qscale = a.qscale;
-    p.scaled = a.qscale != 1.0;
     p.pair = pair;
     p.psi = psi;
     p.nd = nd;
@@ -636,20 +636,28 @@ void launch_hv_tile(const HvArgs &a, const TilePlan &pl, const T *x, int64_t ldx
                            a.tcls, a.states_dn, x, ldx, out, ldy, shift, part);
         HUB_HIP(hipGetLastError());
     };
+    auto step = [&](auto gtc, auto mc) {
+        constexpr bool GT = decltype(gtc)::value;
+        constexpr int M = decltype(mc)::value;
+        if (nd > 2)
+            go(hv_tile_kernel<T, M, GT, kTileDefl>);
+        else if (nd == 2)
+            go(hv_tile_kernel<T, M, GT, 2>);
+        else if (nd == 1)
+            go(hv_tile_kernel<T, M, GT, 1>);
+        else
+            go(hv_tile_kernel<T, M, GT, 0>);
+    };
     auto by_mode = [&](auto gtc) {
         constexpr bool GT = decltype(gtc)::value;
         if (mode == HV_STORE)
             go(hv_tile_kernel<T, HV_STORE, GT, 0>);
         else if (mode == HV_RESIDUAL)
             go(hv_tile_kernel<T, HV_RESIDUAL, GT, 0>);
-        else if (nd > 2)
-            go(hv_tile_kernel<T, HV_LANCZOS, GT, kTileDefl>);
-        else if (nd == 2)
-            go(hv_tile_kernel<T, HV_LANCZOS, GT, 2>);
-        else if (nd == 1)
-            go(hv_tile_kernel<T, HV_LANCZOS, GT, 1>);
+        else if (a.qscale != 1.0)
+            step(gtc, std::integral_constant<int, HV_LANCZOS_SCALED>());
         else
-            go(hv_tile_kernel<T, HV_LANCZOS, GT, 0>);
+            step(gtc, std::integral_constant<int, HV_LANCZOS>());
     };
     if (gt)
         by_mode(std::true_type());
