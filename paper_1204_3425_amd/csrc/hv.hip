@@ -1274,15 +1274,13 @@ __global__ __launch_bounds__(kSlabThreads) void hv_slabs_kernel(SlabArgs p, cons
 }
 
 
-// First slab of an XCD's contiguous range.  FP64: ranges as equal as they can be
-// (4x4, 6 + 5, 273 slabs: H.v 532 us and step 674, 535 and 680 with the last XCD
-// taking the remainder; other sectors even).  FP32: 1/8 rounded up, the last XCD
-// the remainder (4x4 dense, 8 + 8, 7 + 7 and 6 + 6: 1496, 1081 and 600 us against
-// 1510, 1094 and 606).
-template <typename T>
-__device__ inline int first_slab(int nslab, int xcd)
+// Which slabs an XCD takes: every eighth one, or a contiguous range, an eighth of
+// them rounded down or up or an eighth rounded up with the remainder on the last
+// XCD.  (The rule is in launch_hv2.)
+enum SlabOrder { SLAB_STRIDED = 0, SLAB_EVEN = 1, SLAB_CEIL = 2 };
+__device__ inline int first_slab(int nslab, int xcd, int order)
 {
-    return sizeof(T) == 8 ? nslab * xcd / 8 : min((nslab + 7) / 8 * xcd, nslab);
+    return order == SLAB_EVEN ? nslab * xcd / 8 : min((nslab + 7) / 8 * xcd, nslab);
 }
 
 struct BlockArgs {
@@ -1339,8 +1337,8 @@ __global__ __launch_bounds__(1024) void hv_blocks_kernel(BlockArgs p, const T *_
     const int xcd = blockIdx.x & 7;
     const int local = blockIdx.x >> 3;
     // slab-major per XCD: the k-th contiguous range of slabs, or slabs k, k + 8, ...
-    const int s = p.contig ? first_slab<T>(p.nslab, xcd) + local / p.nblocks : (local / p.nblocks) * 8 + xcd;
-    const int s_end = p.contig ? first_slab<T>(p.nslab, xcd + 1) : p.nslab;
+    const int s = p.contig ? first_slab(p.nslab, xcd, p.contig) + local / p.nblocks : (local / p.nblocks) * 8 + xcd;
+    const int s_end = p.contig ? first_slab(p.nslab, xcd + 1, p.contig) : p.nslab;
     const int blk = local % p.nblocks;
     double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
     if (s < s_end) {
@@ -1574,8 +1572,8 @@ __global__ __launch_bounds__(1024) void hv_lines_kernel(LineArgs p, const T *__r
     const int local = bid >> 3;
     // slab-major per XCD: XCD k takes the k-th contiguous range of slabs, or slabs
     // k, k + 8, ...
-    const int s = p.contig ? first_slab<T>(p.nslab, xcd) + local / p.nblocks : (local / p.nblocks) * 8 + xcd;
-    const int s_end = p.contig ? first_slab<T>(p.nslab, xcd + 1) : p.nslab;
+    const int s = p.contig ? first_slab(p.nslab, xcd, p.contig) + local / p.nblocks : (local / p.nblocks) * 8 + xcd;
+    const int s_end = p.contig ? first_slab(p.nslab, xcd + 1, p.contig) : p.nslab;
     const int blk = local % p.nblocks;
     double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
     if (s < s_end) {
@@ -2302,11 +2300,19 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
     // (on 128 bytes each row segment is one cache line)
     const bool on16 = ldx % v16 == 0 && ldyr % v16 == 0 && (uintptr_t)x % 16 == 0 && (uintptr_t)yr % 16 == 0;
     // which slabs an XCD takes: rows not on 128 bytes want neighbouring slabs, which
-    // share lines, in one L2.  FP64 rows on 128 bytes do too: with slabs k, k + 8, ..
-    // the eight XCDs walk the rows side by side and meet on the same memory channels
-    // (4x4, 8 + 8, 7 + 7 and 6 + 6, fused step: 1640, 1251 and 1035 us against 1395,
-    // 1212 and 906).  FP32 rows on 128 bytes do not (605 us against 617, 730 against 737).
-    const bool contig = sizeof(T) == 8 || ldx % slw != 0 || ldyr % slw != 0 || (mode != HV_RESIDUAL && ldyo % slw != 0);
+    // share lines, in one L2, in ranges of an eighth rounded up (with even ranges 4x4
+    // FP32 dense, 8 + 8, 7 + 7 and 6 + 6, 1510, 1094 and 606 us against 1496, 1081 and 600;
+    // FP64 16 sites with diagonals 8u4d 545 against 526) unless there are so few slabs that
+    // this leaves XCDs without one (20-site ring 10u2d, 12 slabs, 796 against 780).  FP64
+    // rows on 128 bytes want contiguous ranges too: with slabs k, k + 8, .. the eight XCDs
+    // walk the rows side by side and meet on the same memory channels (4x4, 8 + 8, 7 + 7
+    // and 6 + 6, fused step: 1640, 1251 and 1035 us against 1395, 1212 and 906; even ranges,
+    // 6 + 5 532 us a product, rounded up 535).  FP32 rows on 128 bytes do not (605 us
+    // against 617, 730 against 737).
+    const bool odd = ldx % slw != 0 || ldyr % slw != 0 || (mode != HV_RESIDUAL && ldyo % slw != 0);
+    const int contig = odd && (sizeof(T) == 4 || pl.blk_nslab >= 64) ? SLAB_CEIL
+                       : sizeof(T) == 8                              ? SLAB_EVEN
+                                                                     : SLAB_STRIDED;
     if (pl.blk_grid > 0 && on16) {
         BlockArgs ba;
         ba.ent = a.up_blk;
