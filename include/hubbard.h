@@ -125,9 +125,10 @@ int hubbard_build(int sites, const int32_t *edges, int n_edges, int n_up, int n_
  * handle is exactly the hubbard_build one.  Otherwise the amplitudes are
  * grouped into classes of equal value (at most 127) whose index each table
  * entry carries.  With at most four classes the two-pass H.v kernels run (the
- * class takes two bits of their entries); with more, the one-pass kernel runs
- * every call and hubbard_apply_ld takes only dense rows (ld = dim_dn, which
- * hubbard_info then reports as ld_pref).  Such a handle runs unbatched in
+ * class takes two bits of their entries), or the one-launch form on the sectors
+ * that it is faster on; with more, the one-launch form where a row fits the LDS,
+ * else the one-pass kernel, and hubbard_apply_ld takes only dense rows (ld =
+ * dim_dn, which hubbard_info then reports as ld_pref).  Such a handle runs unbatched in
  * hubbard_lanczos_batch and reports t = NaN in hubbard_info.
  * Errors: as hubbard_build; EINVAL also for more than 127 distinct
  * amplitudes or a non-finite one; ERANGE also when non-uniform amplitudes meet
@@ -153,8 +154,8 @@ int hubbard_set_precision(hubbard_h h, int precision);
 /* Device bytes that a solve with psi requested may hold for its resident
  * Lanczos basis (default: no limit beyond the free memory less 2 GiB).  While
  * the basis fits, every Lanczos vector is kept in a slot of its own as the
- * first pass runs (on large sectors formed there by the step itself, elsewhere
- * copied) and psi = sum_j y_j f_j is one pass over them (Sec. 2.2 obtains psi
+ * first pass runs (formed there by the step itself, or copied where the steps
+ * run in place) and psi = sum_j y_j f_j is one pass over them (Sec. 2.2 obtains psi
  * from the same sum); otherwise, or with 0, the slots are freed and the
  * recurrence is replayed to accumulate psi, as without the basis.  Both give
  * psi to rounding; hubbard_result.psi_resident tells which ran.  Slots are
@@ -165,14 +166,15 @@ int hubbard_set_basis_limit(hubbard_h h, size_t bytes);
 int hubbard_set_seed(hubbard_h h, uint64_t seed);
 
 /* y = H x (Sec. 4.3: H_up (x) I, I (x) H_dn and the interaction term; one
- * launch where x takes at most 192 MB, else two passes over the rows of the
- * dim_up x dim_dn view, the down-spin hops and the interaction from rows staged
- * in LDS, then the up-spin hops as row combinations).  x, y: device arrays of dim elements in J order, double under
- * HUBBARD_FP64 and float under HUBBARD_MIXED; y is overwritten and must not
- * overlap x.  Asynchronous on the handle's stream.  When two passes run and the rows of x or y do
- * not start on 128 bytes (dim_dn not a multiple of 16 doubles or 32 floats)
- * and the up-spin rows have at most 64 hops, the product routes through two work vectors at the stride ld_pref that the
- * handle allocates on the first such call (2 * dim_up * ld_pref elements of the
+ * launch for most sectors where x takes at most 192 MB, else two passes over the
+ * rows of the dim_up x dim_dn view, the down-spin hops and the interaction from
+ * rows staged in LDS, then the up-spin hops as row combinations).  x, y: device
+ * arrays of dim elements in J order, double under HUBBARD_FP64 and float under
+ * HUBBARD_MIXED; y is overwritten and must not overlap x.  Asynchronous on the
+ * handle's stream.  When two passes run and the rows of x or y do not start on
+ * 128 bytes (dim_dn not a multiple of 16 doubles or 32 floats) and the up-spin
+ * rows have at most 64 hops, the product routes through two work vectors at the
+ * stride ld_pref that the handle allocates on the first such call (2 * dim_up * ld_pref elements of the
  * current precision, kept until hubbard_free; ENOMEM if they do not fit): the
  * row pass writes its result and a copy of x there, and the up-spin pass reads
  * them and writes y.  Calls share these vectors: a call on another stream

@@ -859,9 +859,9 @@ static void run_lanczos(hubbard *h, const hubbard_opts &o, LanczosOut &out, cons
         }
     } evguard{ev};
 
-    // Resident basis: with psi requested, every stored Lanczos vector (and its
-    // scale) is copied to a slot of its own while the device has room (and the
-    // handle's basis limit allows), so psi is one combination pass over them
+    // Resident basis: with psi requested, every stored Lanczos vector has a slot
+    // of its own (formed there, or copied) while the device has room and the
+    // handle's basis limit allows, so psi is one combination pass over them
     // instead of a replay of the whole recurrence.  Running out of room frees
     // the slots and falls back to the replay.
     BasisPool local_pool;

@@ -133,14 +133,14 @@ struct DeviceTables {
 // keeps up with clearing freed memory (2.9 -> 19.4 ms a solve).  Blocks given
 // back are kept up to kKeepAll over all handles of the process, the oldest going
 // first, and freed with the handle; a call that finds no block of its own handle
-// takes one that another handle of the device keeps.  (With at most 1 GiB a handle the chunks of
-// mid-sized sectors were allocated by every solve, faster than the driver clears
-// them: 20-site ring 10u1d, 40 steps with psi, 12 to 1,800 ms a call; the slower
-// steps before took 21.)  take()
-// hands out a kept block of at least the size asked for and at most twice that (a
-// quarter more from 64 MiB on), else allocates.  Where the device is full, an allocation of the library frees
-// the kept blocks of every handle and tries again.  Safe from several threads;
-// the work that used a block has to be complete when it is given back.
+// takes one that another handle of the device keeps.  (With at most 1 GiB a
+// handle the chunks of mid-sized sectors were allocated by every solve, faster
+// than the driver clears them: 20-site ring 10u1d, 40 steps with psi, 12 to 1,800
+// ms a call, now 11.)  take() hands out a kept block of at least the size asked
+// for and at most twice that (a quarter more from 64 MiB on), else allocates.
+// Where the device is full, an allocation of the library frees the kept blocks of
+// every handle and tries again.  Safe from several threads; the work that used a
+// block has to be complete when it is given back.
 constexpr size_t kKeepAll = (size_t)8 << 30;
 class Workspace {
   public:
@@ -393,7 +393,7 @@ int launch_hv2(const HvArgs &a, const HvPlan &pl, const T *x, int64_t ldx, T *y,
 // tile.hip: the one-launch H.v of small and medium sectors.  It reads the x rows
 // of the up-spin hops from the Infinity Cache, so x has to fit there beside what
 // else is live (192 MB of the 256).  Dense apply, two-pass / one launch in us:
-// FP64 3x4 6u6d (853,776 states) 36.4 / 16.6, 14-site ring (11.8 M) 156 / 98,
+// FP64 3x4 6u6d (853,776 states) 36.4 / 16.6, 14-site ring (11.8 M) 156 / 95,
 // 4x4 8u4d (23.4 M) 390 / 342, 4x4 6u5d (35 M, 280 MB) 551 / 547, 4x4 6u6d (64 M)
 // 1076 / 1224; FP32 14-site ring 96 / 60, 4x4 6u5d 326 / 273, 6u6d 598 / 625.
 // Handles of more than four amplitude classes have no two-pass form and take it

@@ -326,7 +326,7 @@ void launch_observables(const double *psi, const uint32_t *states_up, const uint
 }
 
 // Scratch of the entry point that allocates nothing (hubbard_observables_noalloc):
-// the workgroups' partial sums, their group sums and the final sums live in this
+// the workgroups' partial sums and the final sums live in this
 // array, one copy per device for the life of the process.  Host code never
 // passes the array's name to a kernel: its device address comes from
 // hipGetSymbolAddress, taken once per device with that device current.

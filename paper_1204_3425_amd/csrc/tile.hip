@@ -9,7 +9,7 @@
 // (and, for a caller's dense rows, the copy to padded ones) that the two-pass
 // form needs.
 //
-// What bounds it (14-site ring, 11.8 M states, FP64, 98 us): the lines the
+// What bounds it (14-site ring, 11.8 M states, FP64, 95 us): the lines the
 // up-spin hops miss in the L2s, 0.7 GB per H.v at about 7 TB/s, and beside them
 // the L1, busy 64 % of the time with the row segments and the table entries;
 // the LDS is busy 16 % and the vector units 36 %.  So the loads are what is
@@ -141,7 +141,8 @@ constexpr int tile_simd_waves()
 }
 
 template <typename T, int MODE, bool GT, int ND>
-__global__ __launch_bounds__(64 * kTileWaves, (tile_simd_waves<T, GT, ND>())) void hv_tile_kernel(TileArgs p, const uint4 *__restrict__ dn,
+__global__ __launch_bounds__(64 * kTileWaves, (tile_simd_waves<T, GT, ND>()))
+void hv_tile_kernel(TileArgs p, const uint4 *__restrict__ dn,
                                                        const uint8_t *__restrict__ dn_nq,
                                                        const double *__restrict__ dn_amp,
                                                        const uint32_t *__restrict__ up_rows,
